@@ -581,11 +581,8 @@ bool try_wide_raw(const SplitPlan &p, const uint32_t *items, const int32_t *dest
 {
     const size_t lds = dev::wide_raw_lds_bytes_c<NW, R, W>(p.D) + 64;
     if (p.D > dev::kStagedMaxD || lds > dev::kStagedLdsPerCu) return false;
-    // readable words: the array, rounded up to whole 16-byte pieces where
-    // the allocation is padded for that
-    uint64_t words = p.n * (uint64_t)NW;
-    if (p.padded) words = (words + 3) & ~3ull;
-    if (words % 4 != 0 || words < 4) return false;
+    const uint64_t words = p.n * (uint64_t)NW;
+    if (words < 4) return false;
     int nbits = 1;
     while ((1 << nbits) < p.D) ++nbits;
     hipLaunchKernelGGL((scatter_wide_raw_kernel<NW, R, W>), dim3(p.n_tiles), dim3(64 * W), lds, s, items, dest, p.n,
@@ -623,9 +620,7 @@ bool try_lock_raw(const SplitPlan &p, const uint32_t *items, const int32_t *dest
     constexpr int R = 4, W = 8;
     const size_t lds = dev::wide_raw_lds_bytes_c<NW, R, W>(p.D) + 64;
     if (p.lock != kLockTile || p.D > dev::kStagedMaxD || lds > dev::kStagedLdsPerCu) return false;
-    uint64_t words = p.n * (uint64_t)NW;
-    if (p.padded) words = (words + 3) & ~3ull;
-    if (words % 4 != 0 || words < 4) return false;
+    const uint64_t words = p.n * (uint64_t)NW;  // n >= kLockMinN: at least 4
     int nbits = 1;
     while ((1 << nbits) < p.D) ++nbits;
     hipLaunchKernelGGL((scatter_lock_raw_kernel<NW, R, W>), dim3(kLockXcds * kLockTile), dim3(64 * W), lds, s,

@@ -166,6 +166,17 @@ def test_split_raw_staged_shape(orc, variant, n, D, words, dist):
 
 
 @pytest.mark.parametrize("n,D,words", [
+    (1, 1024, 11), (2, 1000, 10), (3, 1024, 7), (2049, 1024, 11), (4095, 1024, 10), (2050, 600, 11),
+    (2_097_153, 1024, 10), (2_099_201, 600, 11), (2_097_154, 1024, 11), (2_097_155, 700, 3)])
+def test_split_raw_shapes_ragged_end(orc, n, D, words):
+    """Arrays that end 1 to 3 words past a whole 16-byte piece, through the
+    raw-staged and lockstep shapes: the last words of the last item, alone in
+    their chunk or after full ones."""
+    _run_split(orc, n, D, words, seed=n + D + 9, dist="uniform")
+    _run_split(orc, n, D, words, seed=n + D + 10, dist="mixed")
+
+
+@pytest.mark.parametrize("n,D,words", [
     (16_777_216, 64, 4), (16_777_220, 64, 4),      # 16-byte items: shape 4 up to 2^28 bytes
     (8_388_608, 128, 8), (8_388_612, 128, 8),      # 32-byte items: shape 2 up to 2^28 bytes
     (1_525_201, 64, 11), (1_525_204, 64, 11),      # 44-byte items: plain scatter up to 2^26 bytes
