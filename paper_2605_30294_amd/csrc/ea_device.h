@@ -131,7 +131,7 @@ __device__ inline Tri tri_setup_small(int32_t n, const float p[3])
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const float u = __builtin_amdgcn_fmed3f(p[a] - 0.5f, 0.0f, hi);
-        const float fl = fminf(floorf(u), top);
+        const float fl = __builtin_amdgcn_fmed3f(floorf(u), 0.0f, top);
         i0[a] = (uint32_t)fl;
         f[a] = u - fl;
     }
@@ -146,15 +146,14 @@ __device__ inline Tri tri_setup_small(int32_t n, const float p[3])
 // Larger |s|, or a NaN, take the library call.
 __device__ inline float one_minus_exp_neg(float s)
 {
-    if (fabsf(s) < 0.0625f) {
-        float q = __fmaf_rn(s, -1.0f / 720.0f, 1.0f / 120.0f);
-        q = __fmaf_rn(s, q, -1.0f / 24.0f);
-        q = __fmaf_rn(s, q, 1.0f / 6.0f);
-        q = __fmaf_rn(s, q, -0.5f);
-        q = __fmaf_rn(s, q, 1.0f);
-        return s * q;
-    }
-    return -expm1f(-s);
+    float q = __fmaf_rn(s, -1.0f / 720.0f, 1.0f / 120.0f);
+    q = __fmaf_rn(s, q, -1.0f / 24.0f);
+    q = __fmaf_rn(s, q, 1.0f / 6.0f);
+    q = __fmaf_rn(s, q, -0.5f);
+    q = __fmaf_rn(s, q, 1.0f);
+    q = s * q;
+    if (!(fabsf(s) < 0.0625f)) q = -expm1f(-s);
+    return q;
 }
 
 // Trilinear density from the volume (voxel centres at i + 0.5).
@@ -263,32 +262,45 @@ __device__ inline int32_t first_inside(const Geo &g, const float org[3], const f
     return k_lo;
 }
 
-// Advance a ray through its brick (box) from sample it.k: accumulates tau and
-// I and leaves it.k at the first sample not taken. Returns the brick that owns
-// that sample, or -1 when the ray left the volume or ran out of samples.
-// kSmall: the volume has at most kSmallN^3 voxels (tri_setup_small).
-// The transmittance exp(-tau) is the hardware exponential (a base-2
+// First sample index >= k outside the box, or K. Every coordinate of p_k is
+// monotone in k, so from a sample k inside the box the inside samples are
+// [k, end): a straight-line estimate of `end`, corrected with the exact test
+// (usually by nothing), gives the index a per-sample test would stop at.
+// Per visit this costs about what three per-sample tests did (the 64-view
+// render of 128^3: 2.46 -> 2.32 ms).
+__device__ inline int32_t exit_sample(const Box &box, const float org[3], const float dir[3], float dt, int32_t k,
+                                      int32_t K)
+{
+    auto inside = [&](int32_t j) {
+        float p[3];
+        sample_pos(org, dir, dt, j, p);
+        return box.contains(p);
+    };
+    if (k >= K || !inside(k)) return k;
+    const float lo[3] = {box.lo0, box.lo1, box.lo2}, hi[3] = {box.hi0, box.hi1, box.hi2};
+    float texit = 3.0e38f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        if (dir[a] != 0.0f)
+            texit = fminf(texit, ((dir[a] > 0.0f ? hi[a] : lo[a]) - org[a]) * __builtin_amdgcn_rcpf(dir[a]));
+    const float est = ceilf(texit * __builtin_amdgcn_rcpf(dt) - 0.5f);
+    int32_t end = min(max((int32_t)fminf(fmaxf(est, 0.0f), 2147483520.0f), k + 1), K);
+    while (end < K && inside(end)) ++end;
+    while (end > k + 1 && !inside(end - 1)) --end;
+    return end;
+}
+
+// The running integral and optical depth of a visit, both sums compensated
+// (Kahan). The transmittance exp(-tau) is the hardware exponential (a base-2
 // exponential of -tau log2(e)); its relative error, about 1e-6 for the
 // optical depths of a ray, stays well inside the integrals' tolerance; the
 // emission weight 1 - exp(-sigma) keeps full relative accuracy for small
 // sigma (one_minus_exp_neg).
-template <bool kSmall>
-__device__ inline int32_t march_through_n(const float *__restrict__ vol, const Geo &g, const Box &box,
-                                          const float org[3], const float dir[3], int32_t K, float dt, float c,
-                                          Item &it)
-{
-    float tau = it.tau, I = it.I, ctau = 0.0f, cI = 0.0f;
-    int32_t k = it.k;
-    int32_t dest = -1;
-    Corners cc;
-    for (; k < K; ++k) {
-        float p[3];
-        sample_pos(org, dir, dt, k, p);
-        if (!box.contains(p)) {
-            dest = owner_of(p, g);
-            break;
-        }
-        const float rho = density_cached(vol, g.n, kSmall ? tri_setup_small(g.n, p) : tri_setup(g.n, p), cc);
+struct Sums {
+    float tau, I, ctau = 0.0f, cI = 0.0f;
+    __device__ Sums(const Item &it) : tau(it.tau), I(it.I) {}
+    __device__ void add(float rho, float c)
+    {
         const float sigma = c * rho;
         const float w = __expf(-tau) * one_minus_exp_neg(sigma);
         // compensated I += w * rho
@@ -302,18 +314,111 @@ __device__ inline int32_t march_through_n(const float *__restrict__ vol, const G
         ctau = (tt - tau) - yt;
         tau = tt;
     }
-    it.k = k;
-    it.tau = tau - ctau;
-    it.I = I - cI;
-    return dest;
+    __device__ void store(Item &it) const
+    {
+        it.tau = tau - ctau;
+        it.I = I - cI;
+    }
+};
+
+// Sample counts up to which k + 0.5 and its increments are exact in float.
+constexpr int32_t kFloatK = 1 << 22;
+
+// Samples [k, end) of a ray along z (dir[0] = dir[1] = 0): its x and y cell
+// and weights are fixed, so a voxel plane enters the interpolation as one
+// bilinear value, kept while the ray moves to the next plane, and the plane
+// after that is loaded one cell ahead. Per sample one lerp remains of seven,
+// per cell two 8-byte loads of four, with the operations and rounding of
+// interp_corners. Bound by VALU issue, about 45 instructions a sample for
+// 80: 256 scenes of axis views (7.4 G samples) 18.5 -> 10.8 ms.
+__device__ inline void march_z(const float *__restrict__ vol, int32_t n, const float org[3], float dirz, float dt,
+                               float c, int32_t k, int32_t end, Sums &s)
+{
+    const float at[3] = {org[0], org[1], 0.0f};
+    const Tri t = tri_setup_small(n, at);
+    const uint32_t row = (uint32_t)n, plane = row * row;
+    const float *col = vol + (uint32_t)(t.x + t.y * n);
+    struct Raw {
+        float a, b, c, d;
+    };
+    auto load = [&](int32_t z) {
+        const float *b = col + __umul24((uint32_t)z, plane);
+        return Raw{b[0], b[1], b[row], b[row + 1]};
+    };
+    auto blend = [&](const Raw &r) { return lerpf(lerpf(r.a, r.b, t.f0), lerpf(r.c, r.d, t.f0), t.f1); };
+    const float hi = (float)(n - 1), top = (float)(n - 2);
+    const bool up = dirz * dt > 0.0f;
+    float zc = -2.0f, y0 = 0.0f, y1 = 0.0f;  // the cell, and the values of its planes zc and zc + 1
+    Raw ahead{};                             // the plane after them in the ray's direction
+    const float kend = (float)end + 0.5f;
+    for (float kf = (float)k + 0.5f; kf < kend; kf += 1.0f) {
+        const float u = __builtin_amdgcn_fmed3f(__fmaf_rn(kf * dt, dirz, org[2]) - 0.5f, 0.0f, hi);
+        const float fl = __builtin_amdgcn_fmed3f(floorf(u), 0.0f, top);
+        if (fl != zc) {
+            const int32_t z = (int32_t)fl;
+            if (up && fl == zc + 1.0f) {
+                y0 = y1;
+                y1 = blend(ahead);
+            } else if (!up && fl == zc - 1.0f) {
+                y1 = y0;
+                y0 = blend(ahead);
+            } else {
+                const Raw r0 = load(z), r1 = load(z + 1);
+                y0 = blend(r0);
+                y1 = blend(r1);
+            }
+            ahead = load(up ? min(z + 2, n - 1) : max(z - 1, 0));
+            zc = fl;
+        }
+        s.add(lerpf(y0, y1, u - fl), c);
+    }
+}
+
+// Advance a ray through its brick (box) from sample it.k: accumulates tau and
+// I and leaves it.k at the first sample not taken. Returns the brick that owns
+// that sample, or -1 when the ray left the volume or ran out of samples.
+// kSmall: the volume has at most kSmallN^3 voxels (tri_setup_small) and the
+// ray at most kFloatK samples.
+template <bool kSmall>
+__device__ inline int32_t march_through_n(const float *__restrict__ vol, const Geo &g, const Box &box,
+                                          const float org[3], const float dir[3], int32_t K, float dt, float c,
+                                          Item &it)
+{
+    const int32_t end = exit_sample(box, org, dir, dt, it.k, K);
+    Sums s(it);
+    if (kSmall && dir[0] == 0.0f && dir[1] == 0.0f) {
+        march_z(vol, g.n, org, dir[2], dt, c, it.k, end, s);
+    } else if (kSmall) {
+        Corners cc;
+        const float kend = (float)end + 0.5f;
+        for (float kf = (float)it.k + 0.5f; kf < kend; kf += 1.0f) {
+            const float t = kf * dt;
+            const float p[3] = {__fmaf_rn(t, dir[0], org[0]), __fmaf_rn(t, dir[1], org[1]),
+                                __fmaf_rn(t, dir[2], org[2])};
+            s.add(density_cached(vol, g.n, tri_setup_small(g.n, p), cc), c);
+        }
+    } else {
+        Corners cc;
+        for (int32_t k = it.k; k < end; ++k) {
+            float p[3];
+            sample_pos(org, dir, dt, k, p);
+            s.add(density_cached(vol, g.n, tri_setup(g.n, p), cc), c);
+        }
+    }
+    s.store(it);
+    it.k = max(it.k, end);
+    if (end >= K) return -1;
+    float p[3];
+    sample_pos(org, dir, dt, end, p);
+    return owner_of(p, g);
 }
 
 __device__ inline int32_t march_through(const float *__restrict__ vol, const Geo &g, const Box &box,
                                         const float org[3], const float dir[3], int32_t K, float dt, float c,
                                         Item &it)
 {
-    return g.n <= kSmallN ? march_through_n<true>(vol, g, box, org, dir, K, dt, c, it)
-                          : march_through_n<false>(vol, g, box, org, dir, K, dt, c, it);
+    return g.n <= kSmallN && K <= kFloatK ? march_through_n<true>(vol, g, box, org, dir, K, dt, c, it)
+                                          : march_through_n<false>(vol, g, box, org, dir, K, dt, c, it);
 }
 
 // A brick's voxels plus a one-voxel rim, staged in LDS: region origin

@@ -168,6 +168,28 @@ def test_rotated_views(orc, n, grid, nv, w, h, seed, tile_items):
     _compare(g, o)
 
 
+@pytest.mark.parametrize("direction", [(0, 0, -1), (0, 0, 1), (1e-6, 0, 1), (0, -1e-7, -1), (1, 0, 0), (0.6, 0, -0.8)])
+@pytest.mark.parametrize("n,grid,dt", [(24, (2, 1, 3), 0.5), (24, (2, 3, 2), 1.75), (20, (1, 2, 4), 0.11), (2, (1, 1, 2), 0.3)])
+def test_axis_and_grazing_views(orc, direction, n, grid, dt):
+    """Rays along z (both ways), tilted from an axis by less than a voxel over
+    the whole volume, and along other axes: steps of a fraction of a voxel to
+    several cells, pixels on and outside the volume's faces."""
+    dev = device()
+    rng = np.random.default_rng(31)
+    vol = rng.random((n, n, n)).astype(np.float32)
+    d = np.asarray(direction, dtype=np.float64)
+    w = 13
+    s = (n + 2.0) / w
+    du, dv = ((s, 0, 0), (0, s, 0)) if abs(d[2]) > abs(d[0]) else ((0, s, 0), (0, 0, s))
+    start = np.where(d > 0.5, -0.7, np.where(d < -0.5, n + 0.7, -1.0 + 0.5 * s))
+    start[(d != 0) & (np.abs(d) <= 0.5)] = 0.5 * s
+    views = np.array([W.view_record(start, du, dv, d, w, w, int(np.ceil((n + 3) / dt)))], dtype=W.VIEW_DTYPE)
+    announce(f"ea axis view {direction} n={n} dt={dt}")
+    g = _stepwise(torch.from_numpy(vol).to(dev), grid, views, dt=dt)
+    o = orc.ea_render(vol, grid, views, dt=dt, c=C32, queue_cap=1 << 20)
+    _compare(g, o)
+
+
 def _segments(queue, counts):
     """Split a concatenation of per-round, per-domain queues into its segments."""
     ends = np.cumsum(counts.reshape(-1).astype(np.int64))
