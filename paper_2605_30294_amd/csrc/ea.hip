@@ -9,6 +9,7 @@
 #include "ea_device.h"
 #include "internal.h"
 #include "rafi_device.h"
+#include "split_device.h"
 
 namespace rafi {
 namespace {
@@ -148,14 +149,8 @@ march_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
             int32_t K;
             job_ray(job, it.ray, org, dir, &K);
             const Box box = ea::box_of(d, g);
-            const float lo[3] = {box.lo0, box.lo1, box.lo2}, hi[3] = {box.hi0, box.hi1, box.hi2};
-            float texit = 3.0e38f;
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                if (dir[a] != 0.0f)
-                    texit = fminf(texit, ((dir[a] > 0.0f ? hi[a] : lo[a]) - org[a]) * __builtin_amdgcn_rcpf(dir[a]));
             const float span = (float)(g.b0 + g.b1 + g.b2) * __builtin_amdgcn_rcpf(job.dt);
-            const float left = fminf(texit * __builtin_amdgcn_rcpf(job.dt) - 0.5f - (float)it.k, (float)(K - it.k));
+            const float left = fminf(ea::exit_estimate(box, org, dir, job.dt), (float)K) - (float)it.k;
             key = (uint32_t)fminf(fmaxf(left * ((float)(kBuckets - 1) / span), 0.0f), (float)(kBuckets - 2));
         }
     }
@@ -203,34 +198,95 @@ march_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
     emit_ray(view, job, slot, it, dest);
 }
 
-// LDS-staged march: one workgroup per domain-pure tile of the input queue
-// stages its brick's densities (plus a one-voxel rim) in LDS once and marches
-// all the tile's rays against it.
-constexpr int kMarchLdsThreads = 1024;
+// LDS-staged march: one workgroup per CU, each taking an equal contiguous
+// slice of the queue and working through the brick segments it spans (usually
+// one or two): it stages the brick's densities plus a one-voxel rim in LDS and
+// marches the segment's rays against them. Gathers from global memory cost
+// by the lane (about 26 address cycles per wave-wide gather, the address unit
+// 74% busy), LDS reads a few cycles each. Rays go through in batches ordered
+// by the samples they have left in the brick, longest first, and each wave
+// takes the next 64 when it is done, so lanes and waves stay busy (94% of the
+// issued lanes live, 66% with gathers). Every ray is marched as if alone and
+// written to its own output slot, so results do not depend on the lane. Bound
+// by VALU issue (62% of the slots, 63 instructions a sample) and the brick
+// loads (first launch of the 64-view render of 128^3: 243 us for 2.1 M rays).
+constexpr uint32_t kBrickThreads = 1024, kBrickBatch = 2 * kBrickThreads, kBrickKeys = 64;
 
-__global__ void __launch_bounds__(kMarchLdsThreads)
-march_lds_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
+__global__ void __launch_bounds__(kBrickThreads)
+march_brick_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
 {
-    extern __shared__ float vl[];
-    uint64_t tb, te;
-    const int32_t d = rafi_tile(view, rafi_xcd_block(blockIdx.x, gridDim.x), &tb, &te);
+    extern __shared__ float region[];  // the brick's region, then s_idx
+    __shared__ uint32_t s_cnt[kBrickKeys], s_next;
+    const uint64_t n = rafi_queue_length(view);
+    const uint32_t t = threadIdx.x, lane = t & 63;
+    const uint64_t w = rafi_xcd_block(blockIdx.x, gridDim.x);
+    uint64_t i = n * w / gridDim.x;
+    const uint64_t end = n * (w + 1) / gridDim.x;
+    const Item *__restrict__ in = static_cast<const Item *>(view.in_items);
     const Geo g = job_geo(job);
-    const Box box = ea::box_of(d, g);
-    const ea::Region reg = ea::region_of(box, g);
-    ea::load_region(vl, job.volume, g.n, reg);
-    __syncthreads();
-    for (uint64_t i = tb + threadIdx.x; i < te; i += blockDim.x) {
-        Item it = static_cast<const Item *>(view.in_items)[i];
-        if ((uint32_t)it.ray >= n_rays) {
-            emit_item(view, job, i, it, RAFI_POISON);
-            continue;
+    const float per_key = (float)kBrickKeys * job.dt / (float)(g.b0 + g.b1 + g.b2);  // keys per sample
+    while (i < end) {
+        const int32_t d = ea::find_domain(view.in_offsets, view.n_domains, i);
+        const uint64_t seg_end = min(end, view.in_offsets[d + 1]);
+        const Box box = ea::box_of(d, g);
+        const ea::LdsVol vol(region, ea::region_of(box, g));
+        ea::load_region<kBrickThreads>(region, job.volume, g.n, vol.r);
+        uint16_t *s_idx = reinterpret_cast<uint16_t *>(region + vol.r.ex * vol.r.ey * vol.r.ez);
+        for (; i < seg_end; i += kBrickBatch) {
+            const uint32_t m = (uint32_t)min((uint64_t)kBrickBatch, seg_end - i);
+            if (t < kBrickKeys) s_cnt[t] = 0;
+            if (t == 0) s_next = 0;
+            __syncthreads();  // the region and the counters
+            uint32_t key[2], rank[2];
+#pragma unroll
+            for (uint32_t j = 0; j < 2; ++j) {
+                const uint32_t q = j * kBrickThreads + t;
+                if (q >= m) continue;
+                const Item it = in[i + q];
+                float left = 0.0f;
+                if ((uint32_t)it.ray < n_rays) {
+                    float org[3], dir[3];
+                    int32_t K;
+                    job_ray(job, it.ray, org, dir, &K);
+                    left = fminf(ea::exit_estimate(box, org, dir, job.dt), (float)K) - (float)it.k;
+                }
+                key[j] = kBrickKeys - 1 - (uint32_t)fminf(fmaxf(left * per_key, 0.0f), (float)(kBrickKeys - 1));
+                rank[j] = atomicAdd(&s_cnt[key[j]], 1u);
+            }
+            __syncthreads();
+            if (t < 64) {
+                const uint32_t c = s_cnt[t];
+                s_cnt[t] = dev::wave_incl_scan(c) - c;
+            }
+            __syncthreads();
+#pragma unroll
+            for (uint32_t j = 0; j < 2; ++j)
+                if (j * kBrickThreads + t < m) s_idx[s_cnt[key[j]] + rank[j]] = (uint16_t)(j * kBrickThreads + t);
+            __syncthreads();
+            for (;;) {
+                uint32_t c = 0;
+                if (lane == 0) c = atomicAdd(&s_next, 64u);
+                c = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+                if (c >= m) break;
+                if (c + lane >= m) continue;
+                const uint64_t slot = i + s_idx[c + lane];
+                Item it = in[slot];
+                if ((uint32_t)it.ray >= n_rays) {  // never true for items this library emitted
+                    emit_item(view, job, slot, it, RAFI_POISON);
+                    continue;
+                }
+                log_visit(job, it.ray, d);
+                float org[3], dir[3];
+                int32_t K;
+                job_ray(job, it.ray, org, dir, &K);
+                const int32_t dest = K <= ea::kFloatK
+                                         ? ea::march_through_lds(vol, g, box, org, dir, K, job.dt, job.c, it)
+                                         : ea::march_through(job.volume, g, box, org, dir, K, job.dt, job.c, it);
+                emit_ray(view, job, slot, it, dest);
+            }
+            __syncthreads();  // s_idx, the counters and the region are reused
         }
-        log_visit(job, it.ray, d);
-        float org[3], dir[3];
-        int32_t K;
-        job_ray(job, it.ray, org, dir, &K);
-        const int32_t dest = ea::march_through_lds(vl, reg, g, box, org, dir, K, job.dt, job.c, it);
-        emit_ray(view, job, i, it, dest);
+        i = seg_end;
     }
 }
 
@@ -592,7 +648,44 @@ bool job_ok(const rafi_ctx *c, const rafi_ea_job *j)
     return rays <= c->cap && rays < (1ull << 31);
 }
 
+int cu_count(int *cus)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || *cus < 1)
+        return RAFI_ERR_HIP;
+    return RAFI_OK;
+}
+
 uint32_t n_rays_of(const rafi_ea_job *j) { return (uint32_t)((uint64_t)j->n_views * j->width * j->height); }
+
+// The brick kernel is taken when every CU gets at least 1536 rays: below that
+// the bricks' loads and the longest chords of a part-filled batch cost more
+// than the gathers (64-view render of 128^3: all launches brick 1.77 ms, from
+// 100 K rays 1.72, from 400 K 1.645, never 2.26).
+constexpr uint64_t kBrickRaysPerCu = 1536;
+
+// One march launch over the view's n_in queued rays (an upper bound is enough).
+int launch_march(rafi_ctx *c, const rafi_device_view &v, const rafi_ea_job *job)
+{
+    int cus = 0;
+    if (cu_count(&cus) != RAFI_OK) return RAFI_ERR_HIP;
+    const int ph = prof_domain_begin(c);
+    if (v.n_in) {
+        const size_t lds = region_bytes(job) + kBrickBatch * sizeof(uint16_t);
+        const size_t statics = sizeof(uint32_t) * (kBrickKeys + 1) + 16;
+        if (job->n <= ea::kSmallN && v.n_in >= kBrickRaysPerCu * cus && lds + statics <= max_lds_bytes()) {
+            hipLaunchKernelGGL(march_brick_kernel, dim3(cus), dim3(kBrickThreads), lds, c->stream, v, *job,
+                               n_rays_of(job));
+        } else {
+            hipLaunchKernelGGL(march_kernel, dim3((uint32_t)((v.n_in + 255) / 256)), dim3(256), 0, c->stream, v,
+                               *job, n_rays_of(job));
+        }
+    }
+    prof_domain_end(c, ph);
+    RAFI_LAUNCH_CHECK();
+    return RAFI_OK;
+}
 
 }  // namespace
 }  // namespace rafi
@@ -621,61 +714,22 @@ int rafi_ea_march(rafi_ctx *c, const rafi_ea_job *job)
     if (!job_ok(c, job)) return RAFI_ERR_ARG;
     rafi_device_view v;
     rafi_view(c, &v);
-    // The LDS-staged kernel pays one brick load per workgroup, so it is used
-    // when the tile table was built with large tiles and the brick fits.
-    const size_t lds = region_bytes(job);
-    const bool staged = v.tile_items >= 512 && lds <= max_lds_bytes();
-    const int ph = prof_domain_begin(c);
-    if (v.n_in) {
-        if (staged)
-            hipLaunchKernelGGL(march_lds_kernel, dim3(v.n_tiles), dim3(kMarchLdsThreads), lds, c->stream, v, *job,
-                               n_rays_of(job));
-        else
-            hipLaunchKernelGGL(march_kernel, dim3((uint32_t)((v.n_in + 255) / 256)), dim3(256), 0, c->stream, v,
-                               *job, n_rays_of(job));
-    }
-    prof_domain_end(c, ph);
-    RAFI_LAUNCH_CHECK();
-    return RAFI_OK;
+    return launch_march(c, v, job);
 }
 
 int rafi_ea_render(rafi_ctx *c, const rafi_ea_job *job, int32_t max_rounds, int32_t *rounds)
 {
     if (!job_ok(c, job) || max_rounds < 1) return RAFI_ERR_ARG;
-    int rc = rafi_ea_raygen(c, job);
+    const int rc = rafi_ea_raygen(c, job);
     if (rc != RAFI_OK) return rc;
-    // Tiles of 512 or more (rafi_set_tile_items) select the LDS-staged march,
-    // whose grid is the host's tile count: rounds then wait for each total.
-    if (c->tile_items >= 512 && region_bytes(job) <= max_lds_bytes()) {
-        int32_t r = 0;
-        for (;;) {
-            uint64_t total = 0;
-            rc = rafi_round(c, nullptr, &total);
-            ++r;
-            if (rc != RAFI_OK || total == 0) break;
-            if (r >= max_rounds) { rc = RAFI_ERR_MAX_ROUNDS; break; }
-            if (job->emit_mode == RAFI_SLOTS_APPEND && (rc = rafi_open(c, c->n_slots, RAFI_SLOTS_APPEND)) != RAFI_OK)
-                break;
-            if ((rc = rafi_ea_march(c, job)) != RAFI_OK) break;
-        }
-        if (rounds) *rounds = r;
-        return rc;
-    }
-    // The gather march, launched one step ahead of the host (run_rounds).
-    const uint32_t n_rays = n_rays_of(job);
+    // launched one step ahead of the host (run_rounds)
     auto launch = [&](uint64_t bound) -> int {
         const int orc = rafi_open(c, bound, job->emit_mode);
         if (orc != RAFI_OK) return orc;
         rafi_device_view v;
         rafi_view(c, &v);
         v.n_in = bound;
-        const int ph = prof_domain_begin(c);
-        if (bound)
-            hipLaunchKernelGGL(march_kernel, dim3((uint32_t)((bound + 255) / 256)), dim3(256), 0, c->stream, v,
-                               *job, n_rays);
-        prof_domain_end(c, ph);
-        RAFI_LAUNCH_CHECK();
-        return RAFI_OK;
+        return launch_march(c, v, job);
     };
     return run_rounds(c, max_rounds, rounds, nullptr, launch, [](uint64_t n) { return n; });
 }
@@ -697,10 +751,8 @@ int rafi_ea_backward(rafi_ctx *c, const rafi_ea_job *job, const float *grad_imag
     // LDS privatisation when the brick's region fits a workgroup's LDS
     const size_t lds = region_bytes(job);
     const bool use_lds = lds <= max_lds_bytes();
-    int cus = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        return RAFI_ERR_HIP;
+    int cus = 0;
+    if (cu_count(&cus) != RAFI_OK) return RAFI_ERR_HIP;
     if (use_lds && job->bwd_tile_items) {  // tile per workgroup: the host's tile count sizes the grid
         const uint32_t saved_tile = c->tile_items;
         c->tile_items = job->bwd_tile_items;

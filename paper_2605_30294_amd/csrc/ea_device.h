@@ -262,6 +262,18 @@ __device__ inline int32_t first_inside(const Geo &g, const float org[3], const f
     return k_lo;
 }
 
+// First sample index past the box along a straight line, to rounding.
+__device__ inline float exit_estimate(const Box &box, const float org[3], const float dir[3], float dt)
+{
+    const float lo[3] = {box.lo0, box.lo1, box.lo2}, hi[3] = {box.hi0, box.hi1, box.hi2};
+    float texit = 3.0e38f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        if (dir[a] != 0.0f)
+            texit = fminf(texit, ((dir[a] > 0.0f ? hi[a] : lo[a]) - org[a]) * __builtin_amdgcn_rcpf(dir[a]));
+    return ceilf(texit * __builtin_amdgcn_rcpf(dt) - 0.5f);
+}
+
 // First sample index >= k outside the box, or K. Every coordinate of p_k is
 // monotone in k, so from a sample k inside the box the inside samples are
 // [k, end): a straight-line estimate of `end`, corrected with the exact test
@@ -277,13 +289,7 @@ __device__ inline int32_t exit_sample(const Box &box, const float org[3], const 
         return box.contains(p);
     };
     if (k >= K || !inside(k)) return k;
-    const float lo[3] = {box.lo0, box.lo1, box.lo2}, hi[3] = {box.hi0, box.hi1, box.hi2};
-    float texit = 3.0e38f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        if (dir[a] != 0.0f)
-            texit = fminf(texit, ((dir[a] > 0.0f ? hi[a] : lo[a]) - org[a]) * __builtin_amdgcn_rcpf(dir[a]));
-    const float est = ceilf(texit * __builtin_amdgcn_rcpf(dt) - 0.5f);
+    const float est = exit_estimate(box, org, dir, dt);
     int32_t end = min(max((int32_t)fminf(fmaxf(est, 0.0f), 2147483520.0f), k + 1), K);
     while (end < K && inside(end)) ++end;
     while (end > k + 1 && !inside(end - 1)) --end;
@@ -324,6 +330,51 @@ struct Sums {
 // Sample counts up to which k + 0.5 and its increments are exact in float.
 constexpr int32_t kFloatK = 1 << 22;
 
+// Where a march reads densities from: the volume in global memory ...
+struct GlobalVol {
+    const float *__restrict__ vol;
+    int32_t n;
+    __device__ const float *at(float x, float y, float z) const
+    {
+        return vol + ((uint32_t)x + __umul24((uint32_t)y, (uint32_t)n) + __umul24((uint32_t)z, (uint32_t)(n * n)));
+    }
+    __device__ uint32_t row() const { return (uint32_t)n; }
+    __device__ int32_t z_first() const { return 0; }
+    __device__ int32_t z_last() const { return n - 1; }
+};
+
+// ... or a brick's voxels plus a one-voxel rim, staged in LDS: region origin
+// o = lo - 1 per axis, extent e = b + 2. Samples inside the brick only touch
+// voxels [max(lo-1, 0), min(hi, n-1)], all inside the region.
+struct Region {
+    int32_t ox, oy, oz, ex, ey, ez;
+};
+
+__device__ inline Region region_of(const Box &box, const Geo &g)
+{
+    return Region{(int32_t)box.lo0 - 1, (int32_t)box.lo1 - 1, (int32_t)box.lo2 - 1, g.b0 + 2, g.b1 + 2, g.b2 + 2};
+}
+
+struct LdsVol {
+    const float *origin;  // the LDS address voxel (0, 0, 0) would have
+    Region r;
+    __device__ LdsVol(const float *lds, const Region &reg)
+        : origin(lds - (reg.ox + reg.ex * (reg.oy + reg.ey * reg.oz))), r(reg)
+    {
+    }
+    // x, y, z: whole numbers. The index is computed in float, at full rate and
+    // exactly: at most 8192 bricks of at most 160 KiB make n < 690, and with
+    // three planes or more in a region the index stays below 2^24.
+    __device__ const float *at(float x, float y, float z) const
+    {
+        return origin + (int32_t)__fmaf_rn(__fmaf_rn(z, (float)r.ey, y), (float)r.ex, x);
+    }
+    __device__ uint32_t row() const { return (uint32_t)r.ex; }
+    __device__ uint32_t plane() const { return (uint32_t)(r.ex * r.ey); }
+    __device__ int32_t z_first() const { return r.oz; }
+    __device__ int32_t z_last() const { return r.oz + r.ez - 1; }
+};
+
 // Samples [k, end) of a ray along z (dir[0] = dir[1] = 0): its x and y cell
 // and weights are fixed, so a voxel plane enters the interpolation as one
 // bilinear value, kept while the ray moves to the next plane, and the plane
@@ -331,22 +382,24 @@ constexpr int32_t kFloatK = 1 << 22;
 // per cell two 8-byte loads of four, with the operations and rounding of
 // interp_corners. Bound by VALU issue, about 45 instructions a sample for
 // 80: 256 scenes of axis views (7.4 G samples) 18.5 -> 10.8 ms.
-__device__ inline void march_z(const float *__restrict__ vol, int32_t n, const float org[3], float dirz, float dt,
+template <typename Vol>
+__device__ inline void march_z(const Vol &vol, int32_t n, const float org[3], float dirz, float dt,
                                float c, int32_t k, int32_t end, Sums &s)
 {
     const float at[3] = {org[0], org[1], 0.0f};
     const Tri t = tri_setup_small(n, at);
-    const uint32_t row = (uint32_t)n, plane = row * row;
-    const float *col = vol + (uint32_t)(t.x + t.y * n);
+    const uint32_t row = vol.row();
     struct Raw {
         float a, b, c, d;
     };
-    auto load = [&](int32_t z) {
-        const float *b = col + __umul24((uint32_t)z, plane);
+    const float tx = (float)t.x, ty = (float)t.y;
+    auto load = [&](float z) {
+        const float *b = vol.at(tx, ty, z);
         return Raw{b[0], b[1], b[row], b[row + 1]};
     };
     auto blend = [&](const Raw &r) { return lerpf(lerpf(r.a, r.b, t.f0), lerpf(r.c, r.d, t.f0), t.f1); };
     const float hi = (float)(n - 1), top = (float)(n - 2);
+    const float z_first = (float)vol.z_first(), z_last = (float)vol.z_last();
     const bool up = dirz * dt > 0.0f;
     float zc = -2.0f, y0 = 0.0f, y1 = 0.0f;  // the cell, and the values of its planes zc and zc + 1
     Raw ahead{};                             // the plane after them in the ray's direction
@@ -355,7 +408,6 @@ __device__ inline void march_z(const float *__restrict__ vol, int32_t n, const f
         const float u = __builtin_amdgcn_fmed3f(__fmaf_rn(kf * dt, dirz, org[2]) - 0.5f, 0.0f, hi);
         const float fl = __builtin_amdgcn_fmed3f(floorf(u), 0.0f, top);
         if (fl != zc) {
-            const int32_t z = (int32_t)fl;
             if (up && fl == zc + 1.0f) {
                 y0 = y1;
                 y1 = blend(ahead);
@@ -363,11 +415,11 @@ __device__ inline void march_z(const float *__restrict__ vol, int32_t n, const f
                 y1 = y0;
                 y0 = blend(ahead);
             } else {
-                const Raw r0 = load(z), r1 = load(z + 1);
+                const Raw r0 = load(fl), r1 = load(fl + 1.0f);
                 y0 = blend(r0);
                 y1 = blend(r1);
             }
-            ahead = load(up ? min(z + 2, n - 1) : max(z - 1, 0));
+            ahead = load(up ? fminf(fl + 2.0f, z_last) : fmaxf(fl - 1.0f, z_first));
             zc = fl;
         }
         s.add(lerpf(y0, y1, u - fl), c);
@@ -387,7 +439,7 @@ __device__ inline int32_t march_through_n(const float *__restrict__ vol, const G
     const int32_t end = exit_sample(box, org, dir, dt, it.k, K);
     Sums s(it);
     if (kSmall && dir[0] == 0.0f && dir[1] == 0.0f) {
-        march_z(vol, g.n, org, dir[2], dt, c, it.k, end, s);
+        march_z(GlobalVol{vol, g.n}, g.n, org, dir[2], dt, c, it.k, end, s);
     } else if (kSmall) {
         Corners cc;
         const float kend = (float)end + 0.5f;
@@ -421,84 +473,86 @@ __device__ inline int32_t march_through(const float *__restrict__ vol, const Geo
                                           : march_through_n<false>(vol, g, box, org, dir, K, dt, c, it);
 }
 
-// A brick's voxels plus a one-voxel rim, staged in LDS: region origin
-// o = lo - 1 per axis, extent e = b + 2. Samples inside the brick only touch
-// voxels [max(lo-1, 0), min(hi, n-1)], all inside the region.
-struct Region {
-    int32_t ox, oy, oz, ex, ey, ez;
-};
-
-__device__ inline Region region_of(const Box &box, const Geo &g)
+// march_through with the brick's densities read from a staged region, for
+// volumes of at most kSmallN^3 voxels and rays of at most kFloatK samples: the
+// same values and operations. No cell is kept in registers here: eight LDS
+// reads cost less than testing for a new cell and branching.
+__device__ inline int32_t march_through_lds(const LdsVol &vol, const Geo &g, const Box &box, const float org[3],
+                                            const float dir[3], int32_t K, float dt, float c, Item &it)
 {
-    return Region{(int32_t)box.lo0 - 1, (int32_t)box.lo1 - 1, (int32_t)box.lo2 - 1, g.b0 + 2, g.b1 + 2, g.b2 + 2};
+    const int32_t end = exit_sample(box, org, dir, dt, it.k, K);
+    Sums s(it);
+    if (dir[0] == 0.0f && dir[1] == 0.0f) {
+        march_z(vol, g.n, org, dir[2], dt, c, it.k, end, s);
+    } else {
+        const uint32_t row = vol.row(), plane = vol.plane();
+        const float hi = (float)(g.n - 1), top = (float)(g.n - 2);
+        const float kend = (float)end + 0.5f;
+#pragma unroll 2
+        for (float kf = (float)it.k + 0.5f; kf < kend; kf += 1.0f) {
+            const float t = kf * dt;
+            const float p[3] = {__fmaf_rn(t, dir[0], org[0]), __fmaf_rn(t, dir[1], org[1]),
+                                __fmaf_rn(t, dir[2], org[2])};
+            float fl[3], f[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float u = __builtin_amdgcn_fmed3f(p[a] - 0.5f, 0.0f, hi);
+                fl[a] = __builtin_amdgcn_fmed3f(floorf(u), 0.0f, top);
+                f[a] = u - fl[a];
+            }
+            const float *b0 = vol.at(fl[0], fl[1], fl[2]), *b1 = b0 + row, *b2 = b0 + plane, *b3 = b1 + plane;
+            Corners cc;
+            cc.v[0] = b0[0];
+            cc.v[1] = b0[1];
+            cc.v[2] = b1[0];
+            cc.v[3] = b1[1];
+            cc.v[4] = b2[0];
+            cc.v[5] = b2[1];
+            cc.v[6] = b3[0];
+            cc.v[7] = b3[1];
+            s.add(interp_corners(cc, Tri{0, 0, 0, 0, f[0], f[1], f[2]}), c);
+        }
+    }
+    s.store(it);
+    it.k = max(it.k, end);
+    if (end >= K) return -1;
+    float p[3];
+    sample_pos(org, dir, dt, end, p);
+    return owner_of(p, g);
 }
 
-// Corner (i0, j0, k0) of a trilinear setup -> region index.
-__device__ inline int32_t region_index(const Region &r, const Tri &t)
-{
-    return (t.x - r.ox) + r.ex * ((t.y - r.oy) + r.ey * (t.z - r.oz));
-}
-
-// Load the region of `vol` into lds (voxels outside the volume are never read).
+// The staged region of `vol`, loaded by the whole workgroup of NT threads
+// (positions outside the volume take its nearest voxel and are never used).
+// Eight loads are in flight per thread; the position advances by NT with
+// carries instead of divisions.
+template <uint32_t NT>
 __device__ inline void load_region(float *lds, const float *__restrict__ vol, int32_t n, const Region &r)
 {
-    const int32_t total = r.ex * r.ey * r.ez, sxy = r.ex * r.ey;
-    for (int32_t k = threadIdx.x; k < total; k += blockDim.x) {
-        const int32_t lz = k / sxy, ly = (k - lz * sxy) / r.ex, lx = k - lz * sxy - ly * r.ex;
-        const int32_t x = r.ox + lx, y = r.oy + ly, z = r.oz + lz;
-        float v = 0.0f;
-        if (x >= 0 && x < n && y >= 0 && y < n && z >= 0 && z < n) v = vol[x + (int64_t)n * (y + (int64_t)n * z)];
-        lds[k] = v;
-    }
-}
-
-// Trilinear density from a staged region: the same values and operations as
-// density(), so the result is bit-identical.
-__device__ inline float density_lds(const float *lds, const Region &r, int32_t li, const Tri &t)
-{
-    const int32_t sy = r.ex, sz = r.ex * r.ey;
-    const float *b = lds + li;
-    const float x00 = lerpf(b[0], b[1], t.f0);
-    const float x10 = lerpf(b[sy], b[sy + 1], t.f0);
-    const float x01 = lerpf(b[sz], b[sz + 1], t.f0);
-    const float x11 = lerpf(b[sz + sy], b[sz + sy + 1], t.f0);
-    const float y0 = lerpf(x00, x10, t.f1);
-    const float y1 = lerpf(x01, x11, t.f1);
-    return lerpf(y0, y1, t.f2);
-}
-
-// march_through with the brick's densities read from a staged region.
-__device__ inline int32_t march_through_lds(const float *lds, const Region &reg, const Geo &g, const Box &box,
-                                            const float org[3], const float dir[3], int32_t K, float dt, float c,
-                                            Item &it)
-{
-    float tau = it.tau, I = it.I, ctau = 0.0f, cI = 0.0f;
-    int32_t k = it.k;
-    int32_t dest = -1;
-    for (; k < K; ++k) {
-        float p[3];
-        sample_pos(org, dir, dt, k, p);
-        if (!box.contains(p)) {
-            dest = owner_of(p, g);
-            break;
+    constexpr int kU = 8;
+    const int32_t total = r.ex * r.ey * r.ez;
+    const int32_t dz = (int32_t)NT / (r.ex * r.ey), rem = (int32_t)NT - dz * (r.ex * r.ey);
+    const int32_t dy = rem / r.ex, dx = rem - dy * r.ex;
+    int32_t k = threadIdx.x;
+    int32_t z = k / (r.ex * r.ey), y = (k - z * r.ex * r.ey) / r.ex, x = k - (z * r.ey + y) * r.ex;
+    while (k < total) {
+        float v[kU];
+        const int32_t k0 = k;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t gx = min(max(r.ox + x, 0), n - 1), gy = min(max(r.oy + y, 0), n - 1),
+                          gz = min(max(r.oz + z, 0), n - 1);
+            v[u] = vol[gx + (int64_t)n * (gy + (int64_t)n * gz)];
+            k += NT;
+            x += dx;
+            if (x >= r.ex) { x -= r.ex; ++y; }
+            y += dy;
+            if (y >= r.ey) { y -= r.ey; ++z; }
+            z += dz;
         }
-        const Tri t = tri_setup(g.n, p);
-        const float rho = density_lds(lds, reg, region_index(reg, t), t);
-        const float sigma = c * rho;
-        const float w = expf(-tau) * -expm1f(-sigma);
-        const float yI = w * rho - cI;
-        const float tI = I + yI;
-        cI = (tI - I) - yI;
-        I = tI;
-        const float yt = sigma - ctau;
-        const float tt = tau + yt;
-        ctau = (tt - tau) - yt;
-        tau = tt;
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            if (k0 + u * (int32_t)NT < total) lds[k0 + u * (int32_t)NT] = v[u];
     }
-    it.k = k;
-    it.tau = tau - ctau;
-    it.I = I - cI;
-    return dest;
 }
 
 __device__ inline int32_t find_domain(const uint64_t *__restrict__ off, int32_t D, uint64_t i)

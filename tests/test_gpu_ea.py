@@ -190,6 +190,28 @@ def test_axis_and_grazing_views(orc, direction, n, grid, dt):
     _compare(g, o)
 
 
+@pytest.mark.parametrize("n,grid,nv,w", [(48, (3, 2, 4), 7, 260), (32, (1, 1, 1), 25, 128), (40, (5, 10, 4), 9, 225),
+                                         (24, (2, 2, 2), 1, 640)])
+def test_brick_march(orc, n, grid, nv, w):
+    """Launches large enough for the LDS-staged march (1536 rays per CU and
+    more): uneven bricks, one brick, bricks thinner than a cell row's rim, many
+    bricks per workgroup slice; ragged ray counts; the rounds fall back to the
+    gather march as rays finish. The second case's views are along z."""
+    dev = device()
+    rng = np.random.default_rng(n + nv)
+    vol = rng.random((n, n, n)).astype(np.float32)
+    views = W.random_views(nv, n, w, w, seed=300 + n)
+    if nv == 25:
+        views[:] = W.plusz_view(n, w, w)[0]
+        views["org0"][1::2, 2] = n
+        views["dir"][1::2, 2] = -1.0
+    views["org0"] += 0.01
+    announce(f"ea brick march n={n} grid={grid} rays={nv * w * w}")
+    g = _stepwise(torch.from_numpy(vol).to(dev), grid, views)
+    o = orc.ea_render(vol, grid, views, c=C32, queue_cap=1 << 23)
+    _compare(g, o)
+
+
 def _segments(queue, counts):
     """Split a concatenation of per-round, per-domain queues into its segments."""
     ends = np.cumsum(counts.reshape(-1).astype(np.int64))
