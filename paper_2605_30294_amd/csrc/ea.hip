@@ -212,19 +212,63 @@ march_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
 // loads (first launch of the 64-view render of 128^3: 243 us for 2.1 M rays).
 constexpr uint32_t kBrickThreads = 1024, kBrickBatch = 2 * kBrickThreads, kBrickKeys = 64;
 
+struct BrickOrder {
+    uint32_t cnt[kBrickKeys], next;
+};
+
+// Batch order of the brick kernels: s_idx[0, m) = the batch's items by
+// descending `left(q)` (samples item q has left), 1 / per_key samples to a
+// bucket; o.next = 0. Called by the whole workgroup; m <= kBrickBatch. Ends
+// with a barrier. The order within a bucket varies from run to run.
+template <typename Left>
+__device__ inline void order_batch(BrickOrder &o, uint16_t *s_idx, uint32_t m, float per_key, Left left)
+{
+    const uint32_t t = threadIdx.x;
+    if (t < kBrickKeys) o.cnt[t] = 0;
+    if (t == 0) o.next = 0;
+    __syncthreads();
+    uint32_t key[2], rank[2];
+#pragma unroll
+    for (uint32_t j = 0; j < 2; ++j) {
+        const uint32_t q = j * kBrickThreads + t;
+        if (q >= m) continue;
+        key[j] = kBrickKeys - 1 - (uint32_t)fminf(fmaxf(left(q) * per_key, 0.0f), (float)(kBrickKeys - 1));
+        rank[j] = atomicAdd(&o.cnt[key[j]], 1u);
+    }
+    __syncthreads();
+    if (t < kBrickKeys) {  // one wave
+        const uint32_t c = o.cnt[t];
+        o.cnt[t] = dev::wave_incl_scan(c) - c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < 2; ++j)
+        if (j * kBrickThreads + t < m) s_idx[o.cnt[key[j]] + rank[j]] = (uint16_t)(j * kBrickThreads + t);
+    __syncthreads();
+}
+static_assert(kBrickKeys == 64, "one wave scans the buckets");
+
+// This wave's next 64 places of the batch (the first of them).
+__device__ inline uint32_t next_places(BrickOrder &o)
+{
+    uint32_t c = 0;
+    if ((threadIdx.x & 63) == 0) c = atomicAdd(&o.next, 64u);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+}
+
 __global__ void __launch_bounds__(kBrickThreads)
 march_brick_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
 {
     extern __shared__ float region[];  // the brick's region, then s_idx
-    __shared__ uint32_t s_cnt[kBrickKeys], s_next;
+    __shared__ BrickOrder s_order;
     const uint64_t n = rafi_queue_length(view);
-    const uint32_t t = threadIdx.x, lane = t & 63;
+    const uint32_t lane = threadIdx.x & 63;
     const uint64_t w = rafi_xcd_block(blockIdx.x, gridDim.x);
     uint64_t i = n * w / gridDim.x;
     const uint64_t end = n * (w + 1) / gridDim.x;
     const Item *__restrict__ in = static_cast<const Item *>(view.in_items);
     const Geo g = job_geo(job);
-    const float per_key = (float)kBrickKeys * job.dt / (float)(g.b0 + g.b1 + g.b2);  // keys per sample
+    const float per_key = (float)kBrickKeys * job.dt / (float)(g.b0 + g.b1 + g.b2);
     while (i < end) {
         const int32_t d = ea::find_domain(view.in_offsets, view.n_domains, i);
         const uint64_t seg_end = min(end, view.in_offsets[d + 1]);
@@ -234,40 +278,15 @@ march_brick_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
         uint16_t *s_idx = reinterpret_cast<uint16_t *>(region + vol.r.ex * vol.r.ey * vol.r.ez);
         for (; i < seg_end; i += kBrickBatch) {
             const uint32_t m = (uint32_t)min((uint64_t)kBrickBatch, seg_end - i);
-            if (t < kBrickKeys) s_cnt[t] = 0;
-            if (t == 0) s_next = 0;
-            __syncthreads();  // the region and the counters
-            uint32_t key[2], rank[2];
-#pragma unroll
-            for (uint32_t j = 0; j < 2; ++j) {
-                const uint32_t q = j * kBrickThreads + t;
-                if (q >= m) continue;
+            order_batch(s_order, s_idx, m, per_key, [&](uint32_t q) {
                 const Item it = in[i + q];
-                float left = 0.0f;
-                if ((uint32_t)it.ray < n_rays) {
-                    float org[3], dir[3];
-                    int32_t K;
-                    job_ray(job, it.ray, org, dir, &K);
-                    left = fminf(ea::exit_estimate(box, org, dir, job.dt), (float)K) - (float)it.k;
-                }
-                key[j] = kBrickKeys - 1 - (uint32_t)fminf(fmaxf(left * per_key, 0.0f), (float)(kBrickKeys - 1));
-                rank[j] = atomicAdd(&s_cnt[key[j]], 1u);
-            }
-            __syncthreads();
-            if (t < 64) {
-                const uint32_t c = s_cnt[t];
-                s_cnt[t] = dev::wave_incl_scan(c) - c;
-            }
-            __syncthreads();
-#pragma unroll
-            for (uint32_t j = 0; j < 2; ++j)
-                if (j * kBrickThreads + t < m) s_idx[s_cnt[key[j]] + rank[j]] = (uint16_t)(j * kBrickThreads + t);
-            __syncthreads();
-            for (;;) {
-                uint32_t c = 0;
-                if (lane == 0) c = atomicAdd(&s_next, 64u);
-                c = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
-                if (c >= m) break;
+                if ((uint32_t)it.ray >= n_rays) return 0.0f;
+                float org[3], dir[3];
+                int32_t K;
+                job_ray(job, it.ray, org, dir, &K);
+                return fminf(ea::exit_estimate(box, org, dir, job.dt), (float)K) - (float)it.k;
+            });
+            for (uint32_t c; (c = next_places(s_order)) < m;) {
                 if (c + lane >= m) continue;
                 const uint64_t slot = i + s_idx[c + lane];
                 Item it = in[slot];
@@ -284,7 +303,7 @@ march_brick_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
                                          : ea::march_through(job.volume, g, box, org, dir, K, job.dt, job.c, it);
                 emit_ray(view, job, slot, it, dest);
             }
-            __syncthreads();  // s_idx, the counters and the region are reused
+            __syncthreads();  // the order and the region are reused
         }
         i = seg_end;
     }
@@ -389,222 +408,281 @@ bwd_march_kernel(rafi_device_view view, rafi_ea_job job, const float *__restrict
     else rafi_done(view, i);
 }
 
-// LDS-privatised backward: one workgroup per domain-pure tile of the input
-// queue. The workgroup accumulates dL/dV for the voxels its brick's samples
-// touch -- the brick plus a one-voxel rim, (b+2)^3 floats -- in LDS, and each
-// lane first sums its ray's contributions in registers while consecutive
-// samples stay in the same trilinear cell. At the end the non-zero LDS
-// entries are added to the global gradient.
-constexpr int kBwdThreads = 1024;
+// LDS-privatised backward: the workgroup accumulates dL/dV for the voxels its
+// brick's samples touch -- the brick plus a one-voxel rim, (b+2)^3 floats -- in
+// LDS, and each lane first sums its ray's contributions in registers while
+// consecutive samples stay in the same trilinear cell. At the end the non-zero
+// LDS entries are added to the global gradient. Bound by the latency of a
+// turn's LDS round trips with the 16 waves one region leaves room for, and by
+// VALU issue (58% of the slots): 64 views of 128^3 in 64 bricks, all backward
+// launches 7.7 ms with lanes in queue order, both cells' corners swapped at
+// every move and a brick test per sample, 3.9 ms in the form below.
 
-// Add v to a float in LDS as a compare-and-swap loop on the word's bits: the
-// same single rounded float addition as an atomic add, in the same
-// unspecified order. On gfx950 the native LDS float32 add (ds_add_f32) costs
-// about 200 cycles per full wave, some 3 per active lane, while a 32-bit
+// Add v[j] to the LDS floats p[o[j]], j < 4, as compare-and-swaps of the
+// words' bits: the same single rounded float addition as an atomic add, in the
+// same unspecified order. On gfx950 the native LDS float32 add (ds_add_f32)
+// costs about 200 cycles per full wave, some 3 per active lane, while a 32-bit
 // compare-and-swap costs about 27 (measured, 64 distinct words per wave).
-__device__ inline void lds_add(float *p, float v)
+// Every word is read, then every swap issued, then one wait. Swaps that lost a
+// race (64 rays in a brick's cross-section of 1000 cells: about one a word)
+// are tried again together with the value they found; a word already done
+// takes a swap of some other value for that same value, which fails or
+// rewrites the word unchanged.
+__device__ inline void lds_add4(float *p, const int32_t o[4], const float v[4])
 {
-    uint32_t *q = reinterpret_cast<uint32_t *>(p);
-    uint32_t old = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    for (;;) {
-        uint32_t seen = old;
-        if (__hip_atomic_compare_exchange_strong(q, &seen, __float_as_uint(__uint_as_float(old) + v), __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
-            return;
-        old = seen;
+    uint32_t *w = reinterpret_cast<uint32_t *>(p);
+    // the word as read, and as the swap found it: equal when it took
+    uint32_t old[4], seen[4], miss[4];
+    auto swap = [&](int j, uint32_t want) {
+        (void)__hip_atomic_compare_exchange_strong(w + o[j], &seen[j], want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        seen[j] = old[j] = __hip_atomic_load(w + o[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) swap(j, __float_as_uint(__uint_as_float(old[j]) + v[j]));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) miss[j] = seen[j] ^ old[j];
+    while (miss[0] | miss[1] | miss[2] | miss[3]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            seen[j] = old[j] = miss[j] ? seen[j] : ~seen[j];
+            swap(j, miss[j] ? __float_as_uint(__uint_as_float(old[j]) + v[j]) : old[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) miss[j] = miss[j] ? seen[j] ^ old[j] : 0u;
     }
 }
 
-// Add acc[q] to the LDS words base[o[q]] for the corners q with fl[q]: every
-// word read, then every compare-and-swap issued, then one wait, so a cell
-// change pays two LDS round trips instead of two per corner. A corner that
-// is not flushed takes a swap of its read value's bits with one bit flipped
-// for that same value: it fails, or rewrites the word unchanged. Corners
-// whose swap lost a race to another lane are added again one by one.
-__device__ inline void lds_add_corners(float *base, const int32_t o[8], const float acc[8], const bool fl[8])
+// A ray's pending gradient at the 8 corners of its current cell. The walk is
+// monotone along each axis, so corners are numbered in the direction of
+// travel: bit a of q set = ahead along axis a. Crossing a face leaves the 4
+// corners behind it, which go to LDS, and keeps the other 4.
+struct Pending {
+    float a0, a1, a2, a3, a4, a5, a6, a7;
+    float *p;            // corner 0
+    int32_t ox, oy, oz;  // word offsets of the corner ahead, per axis
+
+    __device__ void enter(float *corner)
+    {
+        p = corner;
+        a0 = a1 = a2 = a3 = a4 = a5 = a6 = a7 = 0.0f;
+    }
+    // One cell on, along x, else along y, else along z.
+    __device__ void cross(bool x, bool y)
+    {
+        const int32_t dx = ox, dy = oy, dz = oz;
+        const float c0 = a0, c1 = a1, c2 = a2, c3 = a3, c4 = a4, c5 = a5, c6 = a6, c7 = a7;
+        const int32_t o1 = x ? dy : dx, o2 = x || y ? dz : dy;
+        const int32_t o[4] = {0, o1, o2, o1 + o2};
+        const float v[4] = {c0, x ? c2 : c1, x || y ? c4 : c2, x ? c6 : (y ? c5 : c3)};
+        lds_add4(p, o, v);
+        p += x ? dx : (y ? dy : dz);
+        a0 = x ? c1 : (y ? c2 : c4);
+        a1 = x ? 0.0f : (y ? c3 : c5);
+        a2 = x ? c3 : (y ? 0.0f : c6);
+        a3 = x || y ? 0.0f : c7;
+        a4 = x ? c5 : (y ? c6 : 0.0f);
+        a5 = y ? c7 : 0.0f;
+        a6 = x ? c7 : 0.0f;
+        a7 = 0.0f;
+    }
+    __device__ void flush()
+    {
+        const int32_t lo[4] = {0, ox, oy, ox + oy}, hi[4] = {oz, oz + ox, oz + oy, oz + ox + oy};
+        const float a[4] = {a0, a1, a2, a3}, b[4] = {a4, a5, a6, a7};
+        lds_add4(p, lo, a);
+        lds_add4(p, hi, b);
+    }
+};
+
+// One ray's walk back through brick d (box, region r with its gradient gl).
+__device__ inline void bwd_ray(const rafi_device_view &view, const rafi_ea_job &job,
+                               const float *__restrict__ grad_image, uint32_t n_rays, int32_t d, const Geo &g,
+                               const Box &box, const ea::Region &r, uint64_t slot, float *gl)
 {
-    uint32_t *w = reinterpret_cast<uint32_t *>(base);
-    uint32_t old[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) old[q] = __hip_atomic_load(w + o[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    // seen[q]: the word as each swap found it (equal to old[q] when it took)
-    uint32_t seen[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        seen[q] = fl[q] ? old[q] : old[q] ^ 1u;
-        const uint32_t want = fl[q] ? __float_as_uint(__uint_as_float(old[q]) + acc[q]) : seen[q];
-        (void)__hip_atomic_compare_exchange_strong(w + o[q], &seen[q], want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+    Item it = static_cast<const Item *>(view.in_items)[slot];
+    if ((uint32_t)it.ray >= n_rays) {
+        rafi_forward_t(view, slot, it, RAFI_POISON);
+        return;
     }
-    bool ok[8], all = true;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        ok[q] = !fl[q] || seen[q] == old[q];
-        all &= ok[q];
+    log_visit(job, it.ray, d);
+    float org[3], dir[3];
+    int32_t K;
+    job_ray(job, it.ray, org, dir, &K);
+    const float gI = grad_image[it.ray], c = job.c, dt = job.dt;
+    const int32_t first = ea::entry_sample(box, org, dir, dt, it.k);
+    float tau = it.tau, ctau = 0.0f, B = it.I;
+    int32_t k = it.k;
+    if (k >= first) {
+        // travel is toward smaller coordinates where dir dt > 0
+        const bool nx = (dir[0] > 0.0f) == (dt > 0.0f), ny = (dir[1] > 0.0f) == (dt > 0.0f),
+                   nz = (dir[2] > 0.0f) == (dt > 0.0f);
+        Pending pend;
+        pend.ox = nx ? -1 : 1;
+        pend.oy = ny ? -r.ex : r.ex;
+        pend.oz = nz ? -r.ex * r.ey : r.ex * r.ey;
+        // the first sample's cell, then the cell of every sample, in local voxels
+        auto corner = [&](int32_t x, int32_t y, int32_t z) {
+            return gl + ((x + nx - r.ox) + r.ex * ((y + ny - r.oy) + r.ey * (z + nz - r.oz)));
+        };
+        auto setup = [&](int32_t j) {
+            float p[3];
+            ea::sample_pos(org, dir, dt, j, p);
+            return ea::tri_setup_small(g.n, p);
+        };
+        Tri t = setup(k);
+        int32_t mx = 0, my = 0, mz = 0;  // cells between the pending cell and sample k's
+        pend.enter(corner(t.x, t.y, t.z));
+        ea::Corners cc;
+        ea::fetch_corners(job.volume, g.n, t, cc);
+        // Per turn a lane crosses at most one face, and takes its sample once
+        // it has reached the sample's cell: a lane that crosses two faces
+        // between samples falls a turn behind instead of holding the wave's
+        // other lanes in a second crossing.
+        while (k >= first) {
+            // A crossing flushes the corners the lane leaves, which hold only
+            // earlier samples' terms: its LDS round trips overlap the gathers
+            // issued for sample k.
+            if (mx + my + mz > 3) {
+                pend.flush();
+                pend.enter(corner(t.x, t.y, t.z));
+                mx = my = mz = 0;
+            } else if (mx + my + mz > 0) {
+                const bool x = mx > 0, y = !x && my > 0;
+                pend.cross(x, y);
+                mx -= x;
+                my -= y;
+                mz -= !x && !y;
+            }
+            if (mx + my + mz == 0) {
+                // the forward march's per-sample forms: cached corners, the
+                // hardware exponential, the series for 1 - exp(-sigma)
+                const float rho = ea::interp_corners(cc, t);
+                const float sigma = c * rho;
+                const float yt = -sigma - ctau;
+                const float tt = tau + yt;
+                ctau = (tt - tau) - yt;
+                tau = tt;
+                const float T = __expf(-tau);
+                const float a = ea::one_minus_exp_neg(sigma);
+                const float dIdrho = T * __fmaf_rn(c * (1.0f - a), rho - B, a);
+                B = __fmaf_rn(a, rho - B, B);
+                if (gI != 0.0f) {
+                    const float s = gI * dIdrho;
+                    const float gx = 1.0f - t.f0, gy = 1.0f - t.f1, gz = 1.0f - t.f2;
+                    // weights behind and ahead
+                    const float x0 = nx ? t.f0 : gx, x1 = nx ? gx : t.f0;
+                    const float y0 = ny ? t.f1 : gy, y1 = ny ? gy : t.f1;
+                    const float z0 = nz ? t.f2 : gz, z1 = nz ? gz : t.f2;
+                    const float a00 = s * z0 * y0, a01 = s * z0 * y1, a10 = s * z1 * y0, a11 = s * z1 * y1;
+                    pend.a0 += a00 * x0;
+                    pend.a1 += a00 * x1;
+                    pend.a2 += a01 * x0;
+                    pend.a3 += a01 * x1;
+                    pend.a4 += a10 * x0;
+                    pend.a5 += a10 * x1;
+                    pend.a6 += a11 * x0;
+                    pend.a7 += a11 * x1;
+                }
+                --k;
+                const Tri u = setup(max(k, first));
+                if (gI != 0.0f) {
+                    mx = abs(u.x - t.x);
+                    my = abs(u.y - t.y);
+                    mz = abs(u.z - t.z);
+                }
+                t = u;
+                ea::fetch_corners(job.volume, g.n, t, cc);
+            }
+            // one latch: every lane ends its turn here (without it the
+            // compiler makes two nested loops of the two kinds of turns)
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (gI != 0.0f) pend.flush();
     }
-    if (!all) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (!ok[q]) lds_add(base + o[q], acc[q]);
+    it.k = k;
+    it.tau = tau - ctau;
+    it.I = B;
+    int32_t dest = RAFI_DONE;
+    if (k >= 0) {
+        float p[3];
+        ea::sample_pos(org, dir, dt, k, p);
+        dest = ea::owner_of(p, g);
     }
+    if (dest >= 0) rafi_forward_t(view, slot, it, dest);
+    else rafi_done(view, slot);
 }
 
 // The backward of the queue items [first, last), all in domain d, by the whole
-// workgroup: zero the brick's gradient region in LDS, march every ray back
+// workgroup: zero the brick's gradient region in LDS, walk every ray back
 // through the brick accumulating into it, then add its non-zero entries to
-// the global gradient. kSmall: the volume has at most kSmallN^3 voxels.
-template <bool kSmall>
+// the global gradient. Rays go through in batches of kBrickBatch ordered by
+// the samples they have left in the brick; ordered = 0: in queue order, where
+// the LDS has no room for the order.
 __device__ inline void bwd_segment(const rafi_device_view &view, const rafi_ea_job &job,
                                    const float *__restrict__ grad_image, float *__restrict__ grad, uint32_t n_rays,
-                                   int32_t d, uint64_t first, uint64_t last, float *gl)
+                                   int32_t d, uint64_t first, uint64_t last, int ordered, float *gl, BrickOrder &order)
 {
     const Geo g = job_geo(job);
     const Box box = ea::box_of(d, g);
-    const int32_t ox = (int32_t)box.lo0 - 1, oy = (int32_t)box.lo1 - 1, oz = (int32_t)box.lo2 - 1;
-    const int32_t ex = g.b0 + 2, ey = g.b1 + 2, ez = g.b2 + 2;
-    const int32_t nl = ex * ey * ez, sxy = ex * ey;
-    for (int32_t k = threadIdx.x; k < nl; k += blockDim.x) gl[k] = 0.0f;
-    __syncthreads();
-
-    const float c = job.c;
-    for (uint64_t i = first + threadIdx.x; i < last; i += blockDim.x) {
-        Item it = static_cast<const Item *>(view.in_items)[i];
-        if ((uint32_t)it.ray >= n_rays) {
-            rafi_forward_t(view, i, it, RAFI_POISON);
-            continue;
+    const ea::Region r = ea::region_of(box, g);
+    const int32_t nl = r.ex * r.ey * r.ez;
+    const uint32_t lane = threadIdx.x & 63;
+    for (int32_t k = threadIdx.x; k < nl; k += kBrickThreads) gl[k] = 0.0f;
+    uint16_t *s_idx = reinterpret_cast<uint16_t *>(gl + nl);
+    const float per_key = (float)kBrickKeys * job.dt / (float)(g.b0 + g.b1 + g.b2);
+    for (uint64_t i = first; i < last; i += kBrickBatch) {
+        const uint32_t m = (uint32_t)min((uint64_t)kBrickBatch, last - i);
+        if (ordered) {
+            order_batch(order, s_idx, m, per_key, [&](uint32_t q) {
+                const Item it = static_cast<const Item *>(view.in_items)[i + q];
+                if ((uint32_t)it.ray >= n_rays) return 0.0f;
+                float org[3], dir[3];
+                int32_t K;
+                job_ray(job, it.ray, org, dir, &K);
+                return (float)it.k - fmaxf(ea::entry_estimate(box, org, dir, job.dt), 0.0f);
+            });
+        } else {
+            if (threadIdx.x == 0) order.next = 0;
+            __syncthreads();
         }
-        log_visit(job, it.ray, d);
-        float org[3], dir[3];
-        int32_t K;
-        job_ray(job, it.ray, org, dir, &K);
-        const float gI = grad_image[it.ray];
-        float tau = it.tau, ctau = 0.0f, B = it.I;
-        int32_t k = it.k;
-        int32_t dest = RAFI_DONE;
-        // acc[q]: this lane's pending gradient for corner q = (q&1, q>>1&1, q>>2)
-        // of the cell whose corner (0,0,0) is local voxel (cx, cy, cz)
-        int32_t cell = -1, cx = 0, cy = 0, cz = 0;
-        ea::Corners cc;
-        float acc[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
-        const int32_t o[8] = {0, 1, ex, ex + 1, sxy, sxy + 1, sxy + ex, sxy + ex + 1};
-        auto flush = [&]() {
-            if (cell < 0) return;
-            bool fl[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) fl[q] = acc[q] != 0.0f;
-            lds_add_corners(gl + cell, o, acc, fl);
-        };
-        // Move to the cell with corner (tx, ty, tz). Across one face the 4
-        // shared corners stay in registers (renumbered); only the other 4 are
-        // added to LDS. Any other move adds all 8.
-        auto move_to = [&](int32_t tx, int32_t ty, int32_t tz) {
-            const int32_t mx = tx - cx, my = ty - cy, mz = tz - cz;
-            const bool face = cell >= 0 && abs(mx) + abs(my) + abs(mz) == 1;
-            const int bit = mx ? 1 : (my ? 2 : 4);
-            const bool up = mx + my + mz > 0;
-            float keep[8];
-            bool fl[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                // a corner on the far side of the crossed face survives as corner q ^ bit
-                const bool kept = face && (((q & bit) != 0) == up);
-                fl[q] = !kept && acc[q] != 0.0f;
-                keep[q] = kept ? acc[q] : 0.0f;
-            }
-            if (cell >= 0) lds_add_corners(gl + cell, o, acc, fl);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const float from = bit == 1 ? keep[q ^ 1] : (bit == 2 ? keep[q ^ 2] : keep[q ^ 4]);
-                acc[q] = face ? from : 0.0f;
-            }
-            cx = tx;
-            cy = ty;
-            cz = tz;
-            cell = tx + ex * (ty + ey * tz);
-        };
-        for (; k >= 0; --k) {
-            float p[3];
-            ea::sample_pos(org, dir, job.dt, k, p);
-            if (!box.contains(p)) {
-                dest = ea::owner_of(p, g);
-                break;
-            }
-            // the forward march's per-sample forms: cached corners, the
-            // hardware exponential, the series for 1 - exp(-sigma)
-            const Tri t = kSmall ? ea::tri_setup_small(g.n, p) : ea::tri_setup(g.n, p);
-            ea::fetch_corners(job.volume, g.n, t, cc);
-            // local corner (i0, j0, k0) of the sample's cell. A move flushes
-            // the corners the lane leaves, which hold only earlier samples'
-            // terms: its LDS round trips overlap the gathers just issued.
-            const int32_t tx = t.x - ox, ty = t.y - oy, tz = t.z - oz;
-            if (gI != 0.0f && (cell < 0 || tx != cx || ty != cy || tz != cz)) move_to(tx, ty, tz);
-            const float rho = ea::interp_corners(cc, t);
-            const float sigma = c * rho;
-            const float yt = -sigma - ctau;
-            const float tt = tau + yt;
-            ctau = (tt - tau) - yt;
-            tau = tt;
-            const float T = __expf(-tau);
-            const float a = ea::one_minus_exp_neg(sigma);
-            const float dIdrho = T * __fmaf_rn(c * (1.0f - a), rho - B, a);
-            B = __fmaf_rn(a, rho - B, B);
-            if (gI == 0.0f) continue;
-            const float s = gI * dIdrho;
-            const float gx0 = 1.0f - t.f0, gy0 = 1.0f - t.f1, gz0 = 1.0f - t.f2;
-            const float a00 = s * gz0 * gy0, a01 = s * gz0 * t.f1, a10 = s * t.f2 * gy0, a11 = s * t.f2 * t.f1;
-            acc[0] += a00 * gx0;
-            acc[1] += a00 * t.f0;
-            acc[2] += a01 * gx0;
-            acc[3] += a01 * t.f0;
-            acc[4] += a10 * gx0;
-            acc[5] += a10 * t.f0;
-            acc[6] += a11 * gx0;
-            acc[7] += a11 * t.f0;
-        }
-        flush();
-        it.k = k;
-        it.tau = tau - ctau;
-        it.I = B;
-        if (k >= 0 && dest >= 0) rafi_forward_t(view, i, it, dest);
-        else rafi_done(view, i);
+        for (uint32_t c; (c = next_places(order)) < m;)
+            if (c + lane < m)
+                bwd_ray(view, job, grad_image, n_rays, d, g, box, r, i + (ordered ? s_idx[c + lane] : c + lane), gl);
+        __syncthreads();  // the order is reused, and after the last batch the region is complete
     }
-    __syncthreads();
-    for (int32_t k = threadIdx.x; k < nl; k += blockDim.x) {
-        const float v = gl[k];
-        if (v != 0.0f) {
-            const int32_t lz = k / sxy, ly = (k - lz * sxy) / ex, lx = k - lz * sxy - ly * ex;
-            const int64_t idx = (ox + lx) + (int64_t)g.n * ((oy + ly) + (int64_t)g.n * (oz + lz));
-            unsafeAtomicAdd(&grad[idx], v);
-        }
+    for (ea::RegionWalk<kBrickThreads> at(r); at.k < nl; at.step(r)) {
+        const float v = gl[at.k];
+        if (v != 0.0f)
+            unsafeAtomicAdd(&grad[(r.ox + at.x) + (int64_t)g.n * ((r.oy + at.y) + (int64_t)g.n * (r.oz + at.z))], v);
     }
     __syncthreads();  // the region is reused by the next segment
 }
 
 // One workgroup per domain-pure tile of the input queue.
-__global__ void __launch_bounds__(kBwdThreads)
+__global__ void __launch_bounds__(kBrickThreads)
 bwd_march_lds_kernel(rafi_device_view view, rafi_ea_job job, const float *__restrict__ grad_image,
-                     float *__restrict__ grad, uint32_t n_rays)
+                     float *__restrict__ grad, uint32_t n_rays, int ordered)
 {
     extern __shared__ float gl[];
+    __shared__ BrickOrder order;
     uint64_t tb, te;
     const int32_t d = rafi_tile(view, rafi_xcd_block(blockIdx.x, gridDim.x), &tb, &te);
-    if (job.n <= ea::kSmallN)
-        bwd_segment<true>(view, job, grad_image, grad, n_rays, d, tb, te, gl);
-    else
-        bwd_segment<false>(view, job, grad_image, grad, n_rays, d, tb, te, gl);
+    bwd_segment(view, job, grad_image, grad, n_rays, d, tb, te, ordered, gl, order);
 }
 
 // One workgroup per CU, each taking an equal contiguous slice of the queue
 // and working through the brick segments it spans (usually one or two), so
 // every CU is busy for the whole launch and the gradient region is flushed
 // about once per workgroup.
-__global__ void __launch_bounds__(kBwdThreads)
+__global__ void __launch_bounds__(kBrickThreads)
 bwd_march_range_kernel(rafi_device_view view, rafi_ea_job job, const float *__restrict__ grad_image,
-                       float *__restrict__ grad, uint32_t n_rays)
+                       float *__restrict__ grad, uint32_t n_rays, int ordered)
 {
     extern __shared__ float gl[];
+    __shared__ BrickOrder order;
     const uint64_t w = rafi_xcd_block(blockIdx.x, gridDim.x);
     const uint64_t n = rafi_queue_length(view);
     uint64_t i = n * w / gridDim.x;
@@ -612,10 +690,7 @@ bwd_march_range_kernel(rafi_device_view view, rafi_ea_job job, const float *__re
     while (i < end) {
         const int32_t d = ea::find_domain(view.in_offsets, view.n_domains, i);
         const uint64_t seg_end = min(end, view.in_offsets[d + 1]);
-        if (job.n <= ea::kSmallN)
-            bwd_segment<true>(view, job, grad_image, grad, n_rays, d, i, seg_end, gl);
-        else
-            bwd_segment<false>(view, job, grad_image, grad, n_rays, d, i, seg_end, gl);
+        bwd_segment(view, job, grad_image, grad, n_rays, d, i, seg_end, ordered, gl, order);
         i = seg_end;
     }
 }
@@ -625,6 +700,10 @@ size_t region_bytes(const rafi_ea_job *j)
 {
     return sizeof(float) * (size_t)(j->n / j->grid[0] + 2) * (j->n / j->grid[1] + 2) * (j->n / j->grid[2] + 2);
 }
+
+// The brick kernels' batch order and their static LDS (rounded up).
+constexpr size_t kOrderBytes = kBrickBatch * sizeof(uint16_t);
+constexpr size_t kBrickStatic = (sizeof(BrickOrder) + 63) / 64 * 64;
 
 size_t max_lds_bytes()
 {
@@ -672,9 +751,8 @@ int launch_march(rafi_ctx *c, const rafi_device_view &v, const rafi_ea_job *job)
     if (cu_count(&cus) != RAFI_OK) return RAFI_ERR_HIP;
     const int ph = prof_domain_begin(c);
     if (v.n_in) {
-        const size_t lds = region_bytes(job) + kBrickBatch * sizeof(uint16_t);
-        const size_t statics = sizeof(uint32_t) * (kBrickKeys + 1) + 16;
-        if (job->n <= ea::kSmallN && v.n_in >= kBrickRaysPerCu * cus && lds + statics <= max_lds_bytes()) {
+        const size_t lds = region_bytes(job) + kOrderBytes;
+        if (job->n <= ea::kSmallN && v.n_in >= kBrickRaysPerCu * cus && lds + kBrickStatic <= max_lds_bytes()) {
             hipLaunchKernelGGL(march_brick_kernel, dim3(cus), dim3(kBrickThreads), lds, c->stream, v, *job,
                                n_rays_of(job));
         } else {
@@ -749,8 +827,11 @@ int rafi_ea_backward(rafi_ctx *c, const rafi_ea_job *job, const float *grad_imag
                            *job, rays);
     RAFI_LAUNCH_CHECK();
     // LDS privatisation when the brick's region fits a workgroup's LDS
-    const size_t lds = region_bytes(job);
-    const bool use_lds = lds <= max_lds_bytes();
+    const size_t room = max_lds_bytes(), need = region_bytes(job) + kBrickStatic;
+    // (a brick that fits, of at most 8192, makes n < 690: the 32-bit cell index)
+    const bool use_lds = need <= room && job->n <= ea::kSmallN;
+    const int ordered = need + kOrderBytes <= room;
+    const size_t lds = region_bytes(job) + (ordered ? kOrderBytes : 0);
     int cus = 0;
     if (cu_count(&cus) != RAFI_OK) return RAFI_ERR_HIP;
     if (use_lds && job->bwd_tile_items) {  // tile per workgroup: the host's tile count sizes the grid
@@ -765,8 +846,8 @@ int rafi_ea_backward(rafi_ctx *c, const rafi_ea_job *job, const float *grad_imag
             if (r >= max_rounds) { rc = RAFI_ERR_MAX_ROUNDS; break; }
             rafi_view(c, &v);
             const int ph = prof_domain_begin(c);
-            hipLaunchKernelGGL(bwd_march_lds_kernel, dim3(v.n_tiles), dim3(kBwdThreads), lds, c->stream, v, *job,
-                               grad_image, grad_volume, (uint32_t)rays);
+            hipLaunchKernelGGL(bwd_march_lds_kernel, dim3(v.n_tiles), dim3(kBrickThreads), lds, c->stream, v, *job,
+                               grad_image, grad_volume, (uint32_t)rays, ordered);
             prof_domain_end(c, ph);
             rc = hipGetLastError() == hipSuccess ? RAFI_OK : RAFI_ERR_HIP;
             if (rc != RAFI_OK) break;
@@ -785,10 +866,13 @@ int rafi_ea_backward(rafi_ctx *c, const rafi_ea_job *job, const float *grad_imag
         lv.n_in = bound;
         const int ph = prof_domain_begin(c);
         if (bound && use_lds) {
-            const uint64_t want = (bound + kBwdThreads - 1) / kBwdThreads;
+            // at least 256 rays a workgroup: a small launch spreads over the CUs,
+            // where its few waves take turns four times as fast (128^3, 64 views:
+            // the 100 K rays of round 9 241 us in 100 workgroups, 229 in 256)
+            const uint64_t want = (bound + 255) / 256;
             const uint32_t blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, cus));
-            hipLaunchKernelGGL(bwd_march_range_kernel, dim3(blocks), dim3(kBwdThreads), lds, c->stream, lv, *job,
-                               grad_image, grad_volume, (uint32_t)rays);
+            hipLaunchKernelGGL(bwd_march_range_kernel, dim3(blocks), dim3(kBrickThreads), lds, c->stream, lv, *job,
+                               grad_image, grad_volume, (uint32_t)rays, ordered);
         } else if (bound) {
             hipLaunchKernelGGL(bwd_march_kernel, dim3((uint32_t)((bound + 255) / 256)), dim3(256), 0, c->stream,
                                lv, *job, grad_image, grad_volume, (uint32_t)rays);

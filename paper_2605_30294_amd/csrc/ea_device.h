@@ -296,6 +296,35 @@ __device__ inline int32_t exit_sample(const Box &box, const float org[3], const 
     return end;
 }
 
+// First sample index of the run of inside samples that ends at k: the walk of
+// the adjoint stops below it (k + 1 when k itself is outside). As exit_sample,
+// in the other direction.
+__device__ inline float entry_estimate(const Box &box, const float org[3], const float dir[3], float dt)
+{
+    const float lo[3] = {box.lo0, box.lo1, box.lo2}, hi[3] = {box.hi0, box.hi1, box.hi2};
+    float tin = -3.0e38f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        if (dir[a] != 0.0f)
+            tin = fmaxf(tin, ((dir[a] > 0.0f ? lo[a] : hi[a]) - org[a]) * __builtin_amdgcn_rcpf(dir[a]));
+    return ceilf(tin * __builtin_amdgcn_rcpf(dt) - 0.5f);
+}
+
+__device__ inline int32_t entry_sample(const Box &box, const float org[3], const float dir[3], float dt, int32_t k)
+{
+    auto inside = [&](int32_t j) {
+        float p[3];
+        sample_pos(org, dir, dt, j, p);
+        return box.contains(p);
+    };
+    if (k < 0 || !inside(k)) return k + 1;
+    const float est = entry_estimate(box, org, dir, dt);
+    int32_t first = min((int32_t)fminf(fmaxf(est, 0.0f), 2147483520.0f), k);
+    while (first > 0 && inside(first - 1)) --first;
+    while (first < k && !inside(first)) ++first;
+    return first;
+}
+
 // The running integral and optical depth of a visit, both sums compensated
 // (Kahan). The transmittance exp(-tau) is the hardware exponential (a base-2
 // exponential of -tau log2(e)); its relative error, about 1e-6 for the
@@ -521,33 +550,50 @@ __device__ inline int32_t march_through_lds(const LdsVol &vol, const Geo &g, con
     return owner_of(p, g);
 }
 
-// The staged region of `vol`, loaded by the whole workgroup of NT threads
-// (positions outside the volume take its nearest voxel and are never used).
-// Eight loads are in flight per thread; the position advances by NT with
+// Position k of a region, as thread t of NT threads steps through it by NT:
 // carries instead of divisions.
+template <uint32_t NT>
+struct RegionWalk {
+    int32_t k, x, y, z, dx, dy, dz;
+    __device__ RegionWalk(const Region &r)
+    {
+        const int32_t sxy = r.ex * r.ey;
+        dz = (int32_t)NT / sxy;
+        dy = ((int32_t)NT - dz * sxy) / r.ex;
+        dx = (int32_t)NT - dz * sxy - dy * r.ex;
+        k = (int32_t)threadIdx.x;
+        z = k / sxy;
+        y = (k - z * sxy) / r.ex;
+        x = k - z * sxy - y * r.ex;
+    }
+    __device__ void step(const Region &r)
+    {
+        k += NT;
+        x += dx;
+        if (x >= r.ex) { x -= r.ex; ++y; }
+        y += dy;
+        if (y >= r.ey) { y -= r.ey; ++z; }
+        z += dz;
+    }
+};
+
+// The staged region of `vol`, loaded by the whole workgroup of NT threads
+// (positions outside the volume take its nearest voxel and are never used),
+// eight loads in flight per thread.
 template <uint32_t NT>
 __device__ inline void load_region(float *lds, const float *__restrict__ vol, int32_t n, const Region &r)
 {
     constexpr int kU = 8;
     const int32_t total = r.ex * r.ey * r.ez;
-    const int32_t dz = (int32_t)NT / (r.ex * r.ey), rem = (int32_t)NT - dz * (r.ex * r.ey);
-    const int32_t dy = rem / r.ex, dx = rem - dy * r.ex;
-    int32_t k = threadIdx.x;
-    int32_t z = k / (r.ex * r.ey), y = (k - z * r.ex * r.ey) / r.ex, x = k - (z * r.ey + y) * r.ex;
-    while (k < total) {
+    for (RegionWalk<NT> at(r); at.k < total;) {
         float v[kU];
-        const int32_t k0 = k;
+        const int32_t k0 = at.k;
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const int32_t gx = min(max(r.ox + x, 0), n - 1), gy = min(max(r.oy + y, 0), n - 1),
-                          gz = min(max(r.oz + z, 0), n - 1);
+            const int32_t gx = min(max(r.ox + at.x, 0), n - 1), gy = min(max(r.oy + at.y, 0), n - 1),
+                          gz = min(max(r.oz + at.z, 0), n - 1);
             v[u] = vol[gx + (int64_t)n * (gy + (int64_t)n * gz)];
-            k += NT;
-            x += dx;
-            if (x >= r.ex) { x -= r.ex; ++y; }
-            y += dy;
-            if (y >= r.ey) { y -= r.ey; ++z; }
-            z += dz;
+            at.step(r);
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u)

@@ -85,6 +85,43 @@ def test_gradient_matches_float64_oracle(orc, n, grid, nv, w, bwd_tile):
         assert abs(gv - fd) <= 1e-3 * abs(fd) + 1e-6 * np.abs(g).max(), (v, gv, fd)
 
 
+@pytest.mark.parametrize("n,grid,dt", [
+    (24, (1, 12, 24), 0.5),    # bricks one and two voxels thick
+    (64, (1, 2, 4), 0.5),      # a region that leaves no room in LDS for the batch order
+    (24, (2, 1, 3), 0.07),     # many samples per cell
+    (24, (2, 1, 1), 1.4),      # steps over two and three faces
+    (30, (1, 2, 1), 6.0),      # steps over whole cells
+])
+def test_gradient_cell_walk(orc, n, grid, dt):
+    """The walk from cell to cell: one, several or no faces between samples,
+    every direction sign and axis-parallel rays, rays of zero gradient between
+    the others. Float32 terms (about 1e-6 relative) and sums keep the gradient
+    within 1e-5 (relative L2) of the float64 oracle's."""
+    dev = device()
+    rng = np.random.default_rng(n)
+    vol = rng.random((n, n, n)).astype(np.float32)
+    w = 40
+    views = W.random_views(6, n, w, w, seed=65, dt=dt)
+    for i, d in enumerate(([0, 0, -1], [0, 1, 0], [-1, 0, 0])):
+        s, a = n / w, int(np.argmax(np.abs(d)))
+        org = np.full(3, 0.5 * s)
+        org[a] = n + 0.1 if d[a] < 0 else -0.1
+        others = [b for b in range(3) if b != a]
+        du, dv = np.zeros(3), np.zeros(3)
+        du[others[0]], dv[others[1]] = s, s
+        views[i] = W.view_record(org, du, dv, d, w, w, int(views[i]["n_samples"]))
+    announce(f"adjoint cell walk n={n} grid={grid} dt={dt}")
+    v = torch.from_numpy(vol).to(dev).requires_grad_(True)
+    img = rafi.ea_render_differentiable(v, grid, views, dt=dt, c=C32)
+    target = np.zeros(img.numel(), dtype=np.float32)
+    target[::3] = img.detach().cpu().numpy()[::3]          # these rays have no gradient
+    ((img - torch.from_numpy(target).to(dev)) ** 2).sum().backward()
+    g = v.grad.cpu().numpy().astype(np.float64)
+    ids = np.flatnonzero(np.arange(img.numel()) % 3)
+    _, g64, _ = orc.ea_loss_grad(vol, grid, views, target, dt=dt, c=C32, ray_ids=ids)
+    assert _rel_l2(g, g64) <= 1e-5, _rel_l2(g, g64)
+
+
 def test_backward_replays_reversed_visits():
     dev = device()
     n, grid = 64, (4, 4, 4)
