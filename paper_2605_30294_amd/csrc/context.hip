@@ -1,10 +1,11 @@
 // Host context: queue ownership, the device view and the forward step
 // (Sec. 3.4 of the paper: create a context, size its queues, hand kernels a
 // device interface, call forwardRays() between kernel launches).
-#include <cstdlib>
+#include <chrono>
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <thread>
 
 #include "internal.h"
 
@@ -168,7 +169,7 @@ void prof_domain_end(rafi_ctx *c, int h)
     (void)hipEventRecord(c->pending[h].e[1], c->stream);
 }
 
-int round_enqueue(rafi_ctx *c)
+int round_enqueue(rafi_ctx *c, bool want_counts)
 {
     const SplitPlan p = split_plan(c->n_slots, c->D, c->S);
     if (p.bytes > c->ws_bytes) return RAFI_ERR_STATE;
@@ -188,20 +189,42 @@ int round_enqueue(rafi_ctx *c)
         }
     }
     // the split also moves the dropped-emit count into summary[4] and resets it
-    int rc = split_run(p, c->buf[1], c->dest, c->buf[0], c->offsets, c->summary, c->tile_offsets,
-                       c->tile_items, c->ws, c->stream, evp, c->dropped, true);
-    if (rc != RAFI_OK) return rc;
-    RAFI_HIP_CHECK(hipMemcpyAsync(c->host_summary, c->summary, sizeof(uint64_t) * 5, hipMemcpyDeviceToHost,
-                                  c->stream));
-    if (!c->summary_ready) RAFI_HIP_CHECK(hipEventCreateWithFlags(&c->summary_ready, hipEventDisableTiming));
-    RAFI_HIP_CHECK(hipEventRecord(c->summary_ready, c->stream));
-    return RAFI_OK;
+    const HostOut host{c->host_summary_dev, want_counts ? c->host_summary_dev + 8 : nullptr, ++c->round_seq};
+    return split_run(p, c->buf[1], c->dest, c->buf[0], c->offsets, c->summary, c->tile_offsets, c->tile_items, c->ws,
+                     c->stream, evp, c->dropped, true, host);
 }
 
-int round_finish(rafi_ctx *c, uint64_t *total)
+namespace {
+// Waits until the scan of the last enqueued round has written its results.
+// The word is polled (a copy and an event cost each round a launch, 10 us);
+// after a second the stream is synchronised instead, which also reports a
+// failed launch.
+int wait_summary(rafi_ctx *c)
 {
-    RAFI_HIP_CHECK(hipEventSynchronize(c->summary_ready));
+    const uint64_t *word = c->host_summary + 7;
+    auto arrived = [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == c->round_seq; };
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint32_t i = 1; !arrived(); ++i) {
+        __builtin_ia32_pause();
+        if (i % 256 != 0) continue;
+        const auto waited = std::chrono::steady_clock::now() - t0;
+        if (waited > std::chrono::seconds(1)) {
+            RAFI_HIP_CHECK(hipStreamSynchronize(c->stream));
+            return arrived() ? RAFI_OK : RAFI_ERR_HIP;
+        }
+        if (waited > std::chrono::microseconds(200)) std::this_thread::yield();
+    }
+    return RAFI_OK;
+}
+}  // namespace
+
+int round_finish(rafi_ctx *c, uint64_t *total, uint64_t *counts)
+{
+    const int wrc = wait_summary(c);
+    if (wrc != RAFI_OK) return wrc;
     const uint64_t *h = c->host_summary;
+    if (counts)
+        for (int32_t d = 0; d < c->D; ++d) counts[d] = h[8 + d + 1] - h[8 + d];
     if (c->n_pending) {
         int rc = prof_resolve(c, false);
         if (rc != RAFI_OK) return rc;
@@ -220,6 +243,15 @@ int round_finish(rafi_ctx *c, uint64_t *total)
     if (h[2]) return RAFI_ERR_BAD_DEST;
     if (h[4]) return RAFI_ERR_OVERFLOW;
     return RAFI_OK;
+}
+
+int round_run(rafi_ctx *c, uint64_t *counts, uint64_t *total)
+{
+    int rc = round_enqueue(c, counts != nullptr);
+    if (rc != RAFI_OK) return rc;
+    rc = round_finish(c, total, counts);
+    const int fill = ctx_fill_poison(c, c->n_slots);
+    return rc != RAFI_OK ? rc : fill;
 }
 
 }  // namespace rafi
@@ -299,8 +331,11 @@ int rafi_create(int32_t n_domains, uint32_t item_bytes, uint64_t capacity, rafi_
          hipMemset(c->work, 0, 2 * sizeof(unsigned long long)) != hipSuccess ||
          hipMalloc(reinterpret_cast<void **>(&c->append), sizeof(unsigned long long)) != hipSuccess ||
          hipMemset(c->append, 0, sizeof(unsigned long long)) != hipSuccess ||
-         hipHostMalloc(reinterpret_cast<void **>(&c->host_summary), sizeof(uint64_t) * 8, hipHostMallocDefault) != hipSuccess))
+         hipHostMalloc(reinterpret_cast<void **>(&c->host_summary), sizeof(uint64_t) * (8 + n_domains + 1),
+                       hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+         hipHostGetDevicePointer(reinterpret_cast<void **>(&c->host_summary_dev), c->host_summary, 0) != hipSuccess))
         rc = RAFI_ERR_OOM;
+    if (rc == RAFI_OK) c->host_summary[7] = 0;
     if (rc == RAFI_OK) rc = empty_queue(c);
     if (rc == RAFI_OK && hipStreamSynchronize(c->stream) != hipSuccess) rc = RAFI_ERR_HIP;
     if (rc != RAFI_OK) {
@@ -324,7 +359,6 @@ void rafi_destroy(rafi_ctx *c)
     if (c->work) (void)hipFree(c->work);
     if (c->append) (void)hipFree(c->append);
     if (c->host_summary) (void)hipHostFree(c->host_summary);
-    if (c->summary_ready) (void)hipEventDestroy(c->summary_ready);
     for (int i = 0; i < c->n_pending; ++i)
         for (int k = 0; k < (c->pending[i].kind == 0 ? 3 : 2); ++k)
             if (c->pending[i].e[k]) (void)hipEventDestroy(c->pending[i].e[k]);
@@ -417,22 +451,10 @@ int rafi_emit_bulk(rafi_ctx *c, const void *items, const int32_t *dest, uint64_t
 int rafi_round(rafi_ctx *c, uint64_t *counts, uint64_t *total)
 {
     if (!c) return RAFI_ERR_ARG;
-    int rc = round_enqueue(c);
-    if (rc != RAFI_OK) return rc;
-    if (counts) {
-        uint64_t *tmp = static_cast<uint64_t *>(std::malloc(sizeof(uint64_t) * (c->D + 1)));
-        if (!tmp) return RAFI_ERR_OOM;
-        hipError_t e = hipMemcpyAsync(tmp, c->offsets, sizeof(uint64_t) * (c->D + 1), hipMemcpyDeviceToHost,
-                                      c->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (e == hipSuccess)
-            for (int32_t d = 0; d < c->D; ++d) counts[d] = tmp[d + 1] - tmp[d];
-        std::free(tmp);
-        RAFI_HIP_CHECK(e);
-    }
-    rc = round_finish(c, total);
-    const int fill = ctx_fill_poison(c, c->n_slots);
-    return rc != RAFI_OK ? rc : fill;
+    const int rc = round_run(c, counts, total);
+    if (rc != RAFI_OK && rc != RAFI_ERR_BAD_DEST && rc != RAFI_ERR_OVERFLOW) return rc;
+    RAFI_HIP_CHECK(hipStreamSynchronize(c->stream));
+    return rc;
 }
 
 int rafi_copy_queue(const rafi_ctx *c, void *items_dst, uint64_t *offsets_dst)

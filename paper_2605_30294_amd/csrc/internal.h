@@ -40,7 +40,7 @@ struct SplitPlan {
     uint32_t tile = 0;       // slots per tile
     uint32_t n_tiles = 0;
     uint64_t rows = 0;       // D + 2 (domains, done, bad)
-    uint64_t M = 0;          // rows * n_tiles table entries
+    uint64_t M = 0;          // rows * n_cols table entries
     uint32_t scan_blocks = 0;
     uint64_t off_table = 0, off_part = 0, off_dummy = 0, off_done = 0, bytes = 0;  // workspace layout
     // off_dummy: 16 bytes any scatter lane may overwrite; off_done: the finished-tile
@@ -52,6 +52,12 @@ struct SplitPlan {
     uint32_t lock = 0;
     uint32_t n_chunks = 0;
     uint64_t off_pre = 0;
+    // Grouped histogram (few destinations, the context rounds' sizes): the
+    // table has one column per 2^group_bits tiles, and the workspace at off_pre
+    // holds, per tile and destination, the items bound there in the earlier
+    // tiles of its column (u16). 0: a column per tile.
+    uint32_t group_bits = 0;
+    uint32_t n_cols = 0;  // table columns
 };
 
 // allow_lock: the plan may use the lockstep scatter (its workspace grows by
@@ -61,6 +67,15 @@ SplitPlan split_plan(uint64_t n, int32_t D, uint32_t S, bool allow_lock = true);
 int split_set_variant(int v);
 // A plan whose workspace covers every n <= cap.
 SplitPlan split_plan_bound(uint64_t cap, int32_t D, uint32_t S);
+
+// Where a split's scan leaves its results for the host (pinned memory), before
+// the scatter runs: the five summary words, then `seq` (nonzero) at words[7]
+// once they and, with offsets set, the D + 1 offsets are written.
+struct HostOut {
+    uint64_t *words = nullptr;
+    uint64_t *offsets = nullptr;
+    uint64_t seq = 0;
+};
 
 // Optional events recorded around the split's passes (on the split stream).
 struct SplitEvents {
@@ -72,11 +87,12 @@ struct SplitEvents {
 // (optional): device u32 [D+1] built for tiles of tile_items. dropped
 // (optional): device counter read into summary[4] and reset. fused: allow the
 // one-launch histogram + scan + finalize for small tables (the workspace's
-// first 4 bytes must be zero, as the context keeps them).
+// first 4 bytes must be zero, as the context keeps them). host (optional):
+// the results for the host.
 int split_run(const SplitPlan &p, const void *items, const int32_t *dest, void *out,
               uint64_t *offsets, uint64_t *summary, uint32_t *tile_offsets, uint32_t tile_items,
               void *workspace, hipStream_t stream, const SplitEvents *ev = nullptr,
-              unsigned long long *dropped = nullptr, bool fused = false);
+              unsigned long long *dropped = nullptr, bool fused = false, const HostOut &host = HostOut());
 
 }  // namespace rafi
 
@@ -98,8 +114,9 @@ struct rafi_ctx {
     // that have exited. Zero between launches: the last wave to exit resets both.
     unsigned long long *work = nullptr;
     unsigned long long *append = nullptr;  // slots taken by rafi_emit since the last rafi_open
-    uint64_t *host_summary = nullptr;   // pinned [8]
-    hipEvent_t summary_ready = nullptr; // recorded after each round's summary copy
+    uint64_t *host_summary = nullptr;   // pinned [8 + D + 1]: summary words, sequence number, offsets
+    uint64_t *host_summary_dev = nullptr;  // its device address
+    uint64_t round_seq = 0;             // sequence number of the last enqueued round
     void *ws = nullptr;
     uint64_t ws_bytes = 0;
     uint64_t n_in = 0, n_slots = 0;
@@ -131,12 +148,17 @@ void prof_domain_end(rafi_ctx *ctx, int h);
 // Resolve pending event pairs: all of them after synchronising the context
 // stream (wait), or only those already complete, in order.
 int prof_resolve(rafi_ctx *ctx, bool wait);
-// The two halves of rafi_round: enqueue the split of the current output slots
-// and the copy of its summary to the host (no wait); then wait for that copy
-// only and take the results (queue length, statistics). Work enqueued between
-// the two keeps running. round_finish does not touch the output slots.
-int round_enqueue(rafi_ctx *ctx);
-int round_finish(rafi_ctx *ctx, uint64_t *total);
+// The two halves of rafi_round: enqueue the split of the current output slots,
+// whose scan writes its results to pinned memory (want_counts: the offsets
+// too); then wait for them and take them (queue length, statistics; counts,
+// optional: items per domain). The wait ends before the scatter does: what is
+// enqueued next on the stream follows it. round_finish does not touch the
+// output slots.
+int round_enqueue(rafi_ctx *ctx, bool want_counts = false);
+int round_finish(rafi_ctx *ctx, uint64_t *total, uint64_t *counts = nullptr);
+// Both halves and the refill of the slots in debug mode: rafi_round without
+// its synchronisation of the stream.
+int round_run(rafi_ctx *ctx, uint64_t *counts, uint64_t *total);
 
 // The round loop with the host one step ahead of the device. After a forward
 // step is enqueued, the next domain launch is enqueued at once as

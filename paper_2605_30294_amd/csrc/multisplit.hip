@@ -267,12 +267,16 @@ template <int NT>
 __device__ inline void finalize_body(const uint32_t *__restrict__ table, uint32_t n_tiles, int32_t D, uint64_t n,
                                      uint64_t *__restrict__ offsets, uint64_t *__restrict__ summary,
                                      uint32_t *__restrict__ tile_offsets, uint32_t tile_items,
-                                     unsigned long long *__restrict__ dropped, uint32_t *lds)
+                                     unsigned long long *__restrict__ dropped, const HostOut &host, uint32_t *lds)
 {
     auto row_start = [&](int32_t e) -> uint64_t {
         return n_tiles ? (uint64_t)table[(uint64_t)e * n_tiles] : 0ull;
     };
-    for (int32_t e = threadIdx.x; e <= D; e += NT) offsets[e] = row_start(e);
+    for (int32_t e = threadIdx.x; e <= D; e += NT) {
+        const uint64_t o = row_start(e);
+        offsets[e] = o;
+        if (host.offsets) host.offsets[e] = o;
+    }
     const uint64_t total = row_start(D);
     const uint64_t done_end = n_tiles ? row_start(D + 1) : 0ull;
     // per-domain tile counts, scanned (each thread owns a contiguous run)
@@ -293,14 +297,28 @@ __device__ inline void finalize_body(const uint32_t *__restrict__ table, uint32_
         }
         if (threadIdx.x == 0) tile_offsets[D] = tot;
     }
+    if (host.offsets) {
+        __threadfence_system();
+        __syncthreads();  // the offsets before the sequence number
+    }
     if (threadIdx.x == 0) {
+        const uint64_t lost = dropped ? *dropped : 0ull;
         summary[0] = total;
         summary[1] = done_end - total;
         summary[2] = n - done_end;
         summary[3] = tot;
         if (dropped) {
-            summary[4] = *dropped;
+            summary[4] = lost;
             *dropped = 0;
+        }
+        if (host.words) {
+            host.words[0] = total;
+            host.words[1] = done_end - total;
+            host.words[2] = n - done_end;
+            host.words[3] = tot;
+            host.words[4] = lost;
+            __threadfence_system();
+            __hip_atomic_store(host.words + 7, host.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
 }
@@ -308,10 +326,50 @@ __device__ inline void finalize_body(const uint32_t *__restrict__ table, uint32_
 __global__ void __launch_bounds__(1024)
 finalize_kernel(const uint32_t *__restrict__ table, uint32_t n_tiles, int32_t D, uint64_t n,
                 uint64_t *__restrict__ offsets, uint64_t *__restrict__ summary,
-                uint32_t *__restrict__ tile_offsets, uint32_t tile_items, unsigned long long *__restrict__ dropped)
+                uint32_t *__restrict__ tile_offsets, uint32_t tile_items, unsigned long long *__restrict__ dropped,
+                HostOut host)
 {
     __shared__ uint32_t lds[1024 / 64 + 1];
-    finalize_body<1024>(table, n_tiles, D, n, offsets, summary, tile_offsets, tile_items, dropped, lds);
+    finalize_body<1024>(table, n_tiles, D, n, offsets, summary, tile_offsets, tile_items, dropped, host, lds);
+}
+
+// Exclusive scan of table[0, M) in place by one workgroup of 1024 threads,
+// 16384 entries a step, the next step's loads in flight (about 5 us for one
+// step, 4 for each further one).
+__device__ inline void scan_steps(uint32_t *table, uint64_t M, uint32_t *lds)
+{
+    constexpr uint64_t kStep = 1024ull * kScanPer;
+    const uint64_t mine = (uint64_t)threadIdx.x * kScanPer;
+    uint32_t v[kScanPer], next[kScanPer], carry = 0;
+    load16(table, M, mine, v);
+    for (uint64_t base = 0; base < M; base += kStep) {
+        load16(table, M, base + kStep + mine, next);
+        uint32_t s = 0;
+#pragma unroll
+        for (int k = 0; k < kScanPer; ++k) s += v[k];
+        uint32_t tot;
+        const uint32_t run = block_excl_scan<1024>(s, lds, &tot) + carry;
+        store16_excl(table, M, base + mine, v, run);
+        carry += tot;
+#pragma unroll
+        for (int k = 0; k < kScanPer; ++k) v[k] = next[k];
+    }
+    __syncthreads();
+}
+
+// The scan and finalize in one launch, for tables of at most two steps: 5 and
+// 9 us (three steps 13), where the three launches take 13.8 at any of these
+// sizes.
+constexpr uint64_t kOneScanMax = 1ull << 15;
+
+__global__ void __launch_bounds__(1024)
+scan_one_kernel(uint32_t *__restrict__ table, uint64_t M, uint32_t n_cols, int32_t D, uint64_t n,
+                uint64_t *__restrict__ offsets, uint64_t *__restrict__ summary, uint32_t *__restrict__ tile_offsets,
+                uint32_t tile_items, unsigned long long *__restrict__ dropped, HostOut host)
+{
+    __shared__ uint32_t lds[1024 / 64 + 1];
+    scan_steps(table, M, lds);
+    finalize_body<1024>(table, n_cols, D, n, offsets, summary, tile_offsets, tile_items, dropped, host, lds);
 }
 
 // True in exactly one workgroup of the launch: the last to get here. Each
@@ -363,17 +421,81 @@ __global__ void __launch_bounds__(256)
 hist_scan_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint32_t T, uint32_t n_tiles,
                  uint32_t *__restrict__ table, uint64_t M, uint32_t *__restrict__ counter,
                  uint64_t *__restrict__ offsets, uint64_t *__restrict__ summary,
-                 uint32_t *__restrict__ tile_offsets, uint32_t tile_items, unsigned long long *__restrict__ dropped)
+                 uint32_t *__restrict__ tile_offsets, uint32_t tile_items, unsigned long long *__restrict__ dropped,
+                 HostOut host)
 {
     extern __shared__ uint32_t h[];  // D + 2
     __shared__ uint32_t lds[256 / 64 + 1];
     hist_tile(dest, n, D, T, n_tiles, table, h);
     if (!last_workgroup(counter, n_tiles)) return;
     block_scan_inplace<256>(table, M, lds);
-    finalize_body<256>(table, n_tiles, D, n, offsets, summary, tile_offsets, tile_items, dropped, lds);
+    finalize_body<256>(table, n_tiles, D, n, offsets, summary, tile_offsets, tile_items, dropped, host, lds);
+}
+
+// ------------------------------------------------------ grouped pass 1 ---
+// Grouped plans: one workgroup per table column of 4 tiles, a wave per tile
+// with a histogram of its own. The tiles' running sums go to pre, the sum of
+// all to the table, which is 4 times smaller than with a column per tile: for
+// 64 destinations up to 2M slots then fit scan_one_kernel (a round of 1M slots:
+// histogram and scan 10 us for 18 in four launches). Wider groups are slower:
+// queues hold long runs of one destination, whose LDS adds are serial, and 16
+// tiles in one workgroup took 20 to 50 us.
+constexpr uint32_t kGroupBits = 2, kGroupTiles = 1u << kGroupBits;
+
+__global__ void __launch_bounds__(64 * kGroupTiles)
+hist_group_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint32_t T, uint32_t n_tiles,
+                  uint32_t n_cols, uint32_t *__restrict__ table, uint16_t *__restrict__ pre)
+{
+    extern __shared__ uint32_t h[];  // [kGroupTiles][D + 2]
+    const uint32_t rows = (uint32_t)D + 2u, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (uint32_t e = threadIdx.x; e < kGroupTiles * rows; e += blockDim.x) h[e] = 0;
+    __syncthreads();
+    const uint32_t first = blockIdx.x * kGroupTiles;
+    uint32_t *mine = h + w * rows;
+    const uint64_t start = min((uint64_t)(first + w) * T, n), end = min(start + T, n);
+    // T is a multiple of 1024 and dest is 16-byte aligned: whole int4 groups,
+    // four loads in flight
+    uint64_t i = start + 4 * lane;
+    for (; i + 768 + 4 <= end; i += 1024) {
+        uint4 d4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) d4[u] = load_nt4(dest + i + 256 * u);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            atomicAdd(&mine[bucket_of((int32_t)d4[u].x, D)], 1u);
+            atomicAdd(&mine[bucket_of((int32_t)d4[u].y, D)], 1u);
+            atomicAdd(&mine[bucket_of((int32_t)d4[u].z, D)], 1u);
+            atomicAdd(&mine[bucket_of((int32_t)d4[u].w, D)], 1u);
+        }
+    }
+    for (; i < end; i += 256)
+        for (uint64_t j = i; j < min(i + 4, end); ++j) atomicAdd(&mine[bucket_of(dest[j], D)], 1u);
+    __syncthreads();
+    for (uint32_t e = threadIdx.x; e < rows; e += blockDim.x) {
+        uint32_t run = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < kGroupTiles; ++q) {
+            if (e < (uint32_t)D && first + q < n_tiles) pre[(uint64_t)(first + q) * (uint32_t)D + e] = (uint16_t)run;
+            run += h[q * rows + e];
+        }
+        table[(uint64_t)e * n_cols + blockIdx.x] = run;
+    }
 }
 
 // ---------------------------------------------------------------- pass 3 ---
+// Output slot of a tile's first item bound for e, from the scanned table and,
+// where a column stands for several tiles, the tile's prefix inside it.
+struct RunBases {
+    const uint32_t *__restrict__ table;
+    const uint16_t *__restrict__ pre;
+    uint32_t n_cols, group_bits;
+    __device__ uint32_t at(uint32_t tile, int32_t e, int32_t D) const
+    {
+        const uint32_t base = table[(uint64_t)e * n_cols + (tile >> group_bits)];
+        return group_bits ? base + pre[(uint64_t)tile * (uint32_t)D + (uint32_t)e] : base;
+    }
+};
+
 template <int NW>
 __device__ inline void copy_item(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst)
 {
@@ -396,8 +518,7 @@ __device__ inline void copy_item(const uint32_t *__restrict__ src, uint32_t *__r
 template <int NW>
 __global__ void __launch_bounds__(256)
 scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest, uint64_t n,
-               int32_t D, int nbits, uint32_t T, uint32_t n_tiles, const uint32_t *__restrict__ table,
-               uint32_t *__restrict__ out, uint32_t nw_runtime)
+               int32_t D, int nbits, uint32_t T, RunBases bases, uint32_t *__restrict__ out, uint32_t nw_runtime)
 {
     extern __shared__ uint32_t cnt[];  // [4][D]
     const uint32_t nw = NW > 0 ? (uint32_t)NW : nw_runtime;
@@ -416,7 +537,7 @@ scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ d
     }
     __syncthreads();
     for (int32_t e = tid; e < D; e += 256) {
-        uint32_t run = table[(uint64_t)e * n_tiles + blockIdx.x];
+        uint32_t run = bases.at(blockIdx.x, e, D);
 #pragma unroll
         for (int ww = 0; ww < 4; ++ww) {
             const uint32_t c = cnt[ww * D + e];
@@ -454,22 +575,20 @@ scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ d
 template <int NW, int R, int W, int OCC, bool DB>
 __global__ void __launch_bounds__(64 * W, OCC)
 scatter_staged_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest, uint64_t n,
-                      int32_t D, int nbits, uint32_t T, uint32_t n_tiles, const uint32_t *__restrict__ table,
-                      uint32_t *__restrict__ out)
+                      int32_t D, int nbits, uint32_t T, RunBases bases, uint32_t *__restrict__ out)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const uint64_t tstart = (uint64_t)blockIdx.x * T;
     const uint64_t tend = min(tstart + T, n);
     const uint32_t tile = blockIdx.x;
     dev::staged_scatter_tile<NW, R, W, DB>(
-        items, dest, tstart, tend, D, 0, nbits,
-        [&](int32_t e) { return table[(uint64_t)e * n_tiles + tile]; }, out, n, lds);
+        items, dest, tstart, tend, D, 0, nbits, [&](int32_t e) { return bases.at(tile, e, D); }, out, n, lds);
 }
 
 // One (rounds, waves, workgroups per CU) shape of the staged scatter; it is
 // launched only if its LDS fits that many workgroups per CU.
 template <int NW, int R, int W, int BPC, bool DB = false>
-bool try_staged(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const uint32_t *table,
+bool try_staged(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const RunBases &bases,
                 uint32_t *out, hipStream_t s)
 {
     const size_t lds = dev::staged_lds_bytes<NW, R, W>(p.D) + 64;
@@ -478,7 +597,7 @@ bool try_staged(const SplitPlan &p, const uint32_t *items, const int32_t *dest, 
     while ((1 << nbits) < p.D) ++nbits;
     constexpr int OCC = (W * BPC + 3) / 4;  // waves per SIMD
     hipLaunchKernelGGL((scatter_staged_kernel<NW, R, W, OCC, DB>), dim3(p.n_tiles), dim3(64 * W), lds, s, items, dest,
-                       p.n, p.D, nbits, p.tile, p.n_tiles, table, out);
+                       p.n, p.D, nbits, p.tile, bases, out);
     return true;
 }
 
@@ -563,20 +682,20 @@ scatter_line_kernel(const uint32_t *__restrict__ items, const int32_t *__restric
 template <int NW, int R, int W>
 __global__ void __launch_bounds__(64 * W, (W + 3) / 4)
 scatter_wide_raw_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest, uint64_t n,
-                        uint64_t words, int32_t D, int nbits, uint32_t T, uint32_t n_tiles,
-                        const uint32_t *__restrict__ table, uint32_t *__restrict__ out, uint32_t *__restrict__ dummy)
+                        uint64_t words, int32_t D, int nbits, uint32_t T, RunBases bases,
+                        uint32_t *__restrict__ out, uint32_t *__restrict__ dummy)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const uint64_t tstart = (uint64_t)blockIdx.x * T;
     const uint64_t tend = min(tstart + T, n);
     const uint32_t tile = blockIdx.x;
     dev::wide_raw_scatter_tile<NW, R, W>(
-        items, dest, tstart, tend, words, D, nbits,
-        [&](int32_t e) { return table[(uint64_t)e * n_tiles + tile]; }, out, n, dummy, lds);
+        items, dest, tstart, tend, words, D, nbits, [&](int32_t e) { return bases.at(tile, e, D); }, out, n, dummy,
+        lds);
 }
 
 template <int NW, int R, int W>
-bool try_wide_raw(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const uint32_t *table,
+bool try_wide_raw(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const RunBases &bases,
                   uint32_t *out, uint32_t *dummy, hipStream_t s)
 {
     const size_t lds = dev::wide_raw_lds_bytes_c<NW, R, W>(p.D) + 64;
@@ -586,7 +705,7 @@ bool try_wide_raw(const SplitPlan &p, const uint32_t *items, const int32_t *dest
     int nbits = 1;
     while ((1 << nbits) < p.D) ++nbits;
     hipLaunchKernelGGL((scatter_wide_raw_kernel<NW, R, W>), dim3(p.n_tiles), dim3(64 * W), lds, s, items, dest, p.n,
-                       words, p.D, nbits, p.tile, p.n_tiles, table, out, dummy);
+                       words, p.D, nbits, p.tile, bases, out, dummy);
     return true;
 }
 
@@ -674,10 +793,13 @@ bool try_line(const SplitPlan &p, const uint32_t *items, const int32_t *dest, co
 int g_split_variant = 0;
 
 template <int NW>
-bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const uint32_t *table,
-                   const uint16_t *pre, uint32_t *out, uint32_t *dummy, hipStream_t s)
+bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const RunBases &bases,
+                   uint32_t *out, uint32_t *dummy, hipStream_t s)
 {
-    int v = g_split_variant;
+    const uint32_t *table = bases.table;
+    // a grouped plan (made for the automatic choice) takes only shapes that
+    // read their run bases through `bases`
+    int v = p.group_bits ? 0 : g_split_variant;
     if constexpr (NW >= 11) {
         // automatic: items of 44 bytes and more, few destinations and at most
         // 64 MiB: the plain per-thread scatter (each wave's run of a
@@ -687,7 +809,7 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
     }
     if constexpr (NW % 4 != 0 && NW >= 3 && NW <= 15) {
         // large splits: the lockstep schedule (its plan has the chunk prefixes)
-        if ((v == 0 || v == 17) && p.lock && try_lock_raw<NW>(p, items, dest, table, pre, out, dummy, s))
+        if ((v == 0 || v == 17) && p.lock && try_lock_raw<NW>(p, items, dest, table, bases.pre, out, dummy, s))
             return true;
     }
     if (v == 17) v = 0;  // no lockstep plan for this split: automatic
@@ -695,7 +817,7 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
         // item sizes that are not a multiple of 16 bytes: raw staging, one
         // workgroup per CU (automatic when a tile fills a 2048-slot chunk)
         if ((v == 16 || (v == 0 && p.tile >= 8 * 64 * 4)) &&
-            try_wide_raw<NW, 4, 8>(p, items, dest, table, out, dummy, s))
+            try_wide_raw<NW, 4, 8>(p, items, dest, bases, out, dummy, s))
             return true;
     }
     if (v == 16) v = 0;  // shape 16 does not take this item size: automatic
@@ -730,9 +852,9 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
         // when a tile fills at least one of its chunks
         if (p.D <= 128 && p.n * (uint64_t)p.S <= (1ull << 28)) {
             if constexpr (NW == 8) {
-                if (try_staged<8, 4, 4, 3>(p, items, dest, table, out, s)) return true;
+                if (try_staged<8, 4, 4, 3>(p, items, dest, bases, out, s)) return true;
             } else if constexpr (NW == 4) {
-                if (try_staged<4, 4, 4, 4>(p, items, dest, table, out, s)) return true;
+                if (try_staged<4, 4, 4, 4>(p, items, dest, bases, out, s)) return true;
             }
         }
         if (line_spans_tiles(p)) {
@@ -750,15 +872,15 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
     }
     if (v >= 8) {  // shapes 1-4 with double-buffered chunk loads
         if constexpr (NW == 8) {
-            if (v == 8) return try_staged<8, 7, 4, 2, true>(p, items, dest, table, out, s);
-            if (v == 9) return try_staged<8, 4, 4, 3, true>(p, items, dest, table, out, s);
-            if (v == 10) return try_staged<8, 3, 8, 2, true>(p, items, dest, table, out, s);
-            if (v == 11) return try_staged<8, 2, 4, 4, true>(p, items, dest, table, out, s);
+            if (v == 8) return try_staged<8, 7, 4, 2, true>(p, items, dest, bases, out, s);
+            if (v == 9) return try_staged<8, 4, 4, 3, true>(p, items, dest, bases, out, s);
+            if (v == 10) return try_staged<8, 3, 8, 2, true>(p, items, dest, bases, out, s);
+            if (v == 11) return try_staged<8, 2, 4, 4, true>(p, items, dest, bases, out, s);
         } else if constexpr (NW == 4) {
-            if (v == 8) return try_staged<4, 12, 4, 2, true>(p, items, dest, table, out, s);
-            if (v == 9) return try_staged<4, 8, 4, 3, true>(p, items, dest, table, out, s);
-            if (v == 10) return try_staged<4, 5, 8, 2, true>(p, items, dest, table, out, s);
-            if (v == 11) return try_staged<4, 4, 4, 4, true>(p, items, dest, table, out, s);
+            if (v == 8) return try_staged<4, 12, 4, 2, true>(p, items, dest, bases, out, s);
+            if (v == 9) return try_staged<4, 8, 4, 3, true>(p, items, dest, bases, out, s);
+            if (v == 10) return try_staged<4, 5, 8, 2, true>(p, items, dest, bases, out, s);
+            if (v == 11) return try_staged<4, 4, 4, 4, true>(p, items, dest, bases, out, s);
         }
         return false;
     }
@@ -769,38 +891,38 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
         return false;
     }
     if constexpr (NW == 8) {
-        if ((v == 0 || v == 1) && try_staged<8, 7, 4, 2>(p, items, dest, table, out, s)) return true;
-        if ((v == 0 || v == 2) && try_staged<8, 4, 4, 3>(p, items, dest, table, out, s)) return true;
-        if ((v == 0 || v == 3) && try_staged<8, 3, 8, 2>(p, items, dest, table, out, s)) return true;
-        if ((v == 0 || v == 4) && try_staged<8, 2, 4, 4>(p, items, dest, table, out, s)) return true;
+        if ((v == 0 || v == 1) && try_staged<8, 7, 4, 2>(p, items, dest, bases, out, s)) return true;
+        if ((v == 0 || v == 2) && try_staged<8, 4, 4, 3>(p, items, dest, bases, out, s)) return true;
+        if ((v == 0 || v == 3) && try_staged<8, 3, 8, 2>(p, items, dest, bases, out, s)) return true;
+        if ((v == 0 || v == 4) && try_staged<8, 2, 4, 4>(p, items, dest, bases, out, s)) return true;
         return false;
     } else if constexpr (NW == 4) {
-        if ((v == 0 || v == 1) && try_staged<4, 12, 4, 2>(p, items, dest, table, out, s)) return true;
-        if ((v == 0 || v == 2) && try_staged<4, 8, 4, 3>(p, items, dest, table, out, s)) return true;
-        if ((v == 0 || v == 3) && try_staged<4, 5, 8, 2>(p, items, dest, table, out, s)) return true;
-        if ((v == 0 || v == 4) && try_staged<4, 4, 4, 4>(p, items, dest, table, out, s)) return true;
+        if ((v == 0 || v == 1) && try_staged<4, 12, 4, 2>(p, items, dest, bases, out, s)) return true;
+        if ((v == 0 || v == 2) && try_staged<4, 8, 4, 3>(p, items, dest, bases, out, s)) return true;
+        if ((v == 0 || v == 3) && try_staged<4, 5, 8, 2>(p, items, dest, bases, out, s)) return true;
+        if ((v == 0 || v == 4) && try_staged<4, 4, 4, 4>(p, items, dest, bases, out, s)) return true;
         return false;
     } else if constexpr (NW <= 3) {
-        return try_staged<NW, 16, 4, 2>(p, items, dest, table, out, s);
+        return try_staged<NW, 16, 4, 2>(p, items, dest, bases, out, s);
     } else if constexpr (56 / NW > 0) {
-        return try_staged<NW, 56 / NW, 4, 2>(p, items, dest, table, out, s);
+        return try_staged<NW, 56 / NW, 4, 2>(p, items, dest, bases, out, s);
     } else {
         return false;
     }
 }
 
 template <int NW>
-void launch_scatter(const SplitPlan &p, const uint32_t *items, const int32_t *dest,
-                    const uint32_t *table, const uint16_t *pre, uint32_t *out, uint32_t *dummy, hipStream_t s)
+void launch_scatter(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const RunBases &bases,
+                    uint32_t *out, uint32_t *dummy, hipStream_t s)
 {
     if constexpr (NW > 0) {
-        if (launch_staged<NW>(p, items, dest, table, pre, out, dummy, s)) return;
+        if (launch_staged<NW>(p, items, dest, bases, out, dummy, s)) return;
     }
     int nbits = 1;
     while ((1 << nbits) < p.D) ++nbits;
     const size_t lds = sizeof(uint32_t) * 4 * (size_t)p.D;
     hipLaunchKernelGGL(scatter_kernel<NW>, dim3(p.n_tiles), dim3(256), lds, s, items, dest, p.n,
-                       p.D, nbits, p.tile, p.n_tiles, table, out, p.S / 4);
+                       p.D, nbits, p.tile, bases, out, p.S / 4);
 }
 
 }  // namespace
@@ -818,7 +940,8 @@ uint64_t min_tile(int32_t D)
 void finish_plan(SplitPlan &p)
 {
     p.rows = (uint64_t)p.D + 2;
-    p.M = p.rows * p.n_tiles;
+    p.n_cols = (p.n_tiles + (1u << p.group_bits) - 1) >> p.group_bits;
+    p.M = p.rows * p.n_cols;
     p.scan_blocks = (uint32_t)((p.M + kScanChunk - 1) / kScanChunk);
     // fixed head: the fused scan's finished-tile counter, then the dummy slot
     p.off_done = 0;
@@ -828,6 +951,19 @@ void finish_plan(SplitPlan &p)
     p.bytes = p.off_part + ((uint64_t)std::max<uint32_t>(p.scan_blocks, 1) * 4 + 255) / 256 * 256;
     p.off_pre = p.bytes;
     if (p.lock) p.bytes += ((uint64_t)p.n_chunks * (uint64_t)p.D * 2 + 255) / 256 * 256;
+    if (p.group_bits) p.bytes += ((uint64_t)p.n_tiles * (uint64_t)p.D * 2 + 255) / 256 * 256;
+}
+
+// The grouped histogram: where the automatic scatter shape is one of the
+// small staged ones or the plain one (at most 128 destinations and 256 MiB of
+// items: every context round of the workloads here), a tile's prefix fits 16
+// bits, and the ungrouped table is too large for the scans of one launch.
+// Other shapes read the table by tile. The workspace is smaller than without:
+// 3 (D + 2) bytes of table per tile saved, 2 D for the prefixes.
+bool group_eligible(const SplitPlan &p)
+{
+    return g_split_variant == 0 && p.D <= 128 && p.n * (uint64_t)p.S <= (1ull << 28) &&
+           ((uint64_t)p.D + 2) * p.n_tiles > kOneScanMax && (uint64_t)p.tile * (kGroupTiles - 1) < 65536;
 }
 
 // The lockstep scatter takes items that are not whole 16-byte pieces (the
@@ -878,6 +1014,7 @@ SplitPlan split_plan(uint64_t n, int32_t D, uint32_t S, bool allow_lock)
     t = (t + 1023) / 1024 * 1024;
     p.tile = (uint32_t)t;
     p.n_tiles = (uint32_t)((n + t - 1) / t);
+    if (group_eligible(p)) p.group_bits = kGroupBits;
     finish_plan(p);
     return p;
 }
@@ -900,7 +1037,8 @@ SplitPlan split_plan_bound(uint64_t cap, int32_t D, uint32_t S)
 
 int split_run(const SplitPlan &p, const void *items, const int32_t *dest, void *out,
               uint64_t *offsets, uint64_t *summary, uint32_t *tile_offsets, uint32_t tile_items,
-              void *workspace, hipStream_t s, const SplitEvents *ev, unsigned long long *dropped, bool fused)
+              void *workspace, hipStream_t s, const SplitEvents *ev, unsigned long long *dropped, bool fused,
+              const HostOut &host)
 {
     if (p.scan_blocks > (uint32_t)kPartMax) return RAFI_ERR_ARG;
     if (ev) RAFI_HIP_CHECK(hipEventRecord(ev->begin, s));
@@ -912,36 +1050,48 @@ int split_run(const SplitPlan &p, const void *items, const int32_t *dest, void *
     const uint32_t ti = tile_items ? tile_items : 1u;
     // The fused launch costs one device-scope fence (an L2 write-back on this
     // multi-XCD part) per workgroup: worth it only for small tables.
-    if (p.n_tiles > 0 && fused && !p.lock && p.M <= kFusedMaxM && p.n_tiles <= kFusedMaxTiles) {
+    if (p.n_tiles > 0 && fused && !p.lock && !p.group_bits && p.M <= kFusedMaxM && p.n_tiles <= kFusedMaxTiles) {
         hipLaunchKernelGGL(hist_scan_kernel, dim3(p.n_tiles), dim3(256), sizeof(uint32_t) * p.rows, s, dest, p.n,
                            p.D, p.tile, p.n_tiles, table, p.M, counters, offsets, summary, tile_offsets, ti,
-                           dropped);
+                           dropped, host);
         RAFI_LAUNCH_CHECK();
     } else {
         if (p.n_tiles > 0) {
             if (p.lock)
                 hipLaunchKernelGGL(hist_lock_kernel, dim3(p.n_tiles), dim3(256), sizeof(uint32_t) * p.rows, s,
                                    dest, p.n, p.D, p.n_tiles, p.n_chunks, table, pre);
+            else if (p.group_bits)
+                hipLaunchKernelGGL(hist_group_kernel, dim3(p.n_cols), dim3(64 * kGroupTiles),
+                                   sizeof(uint32_t) * kGroupTiles * p.rows, s, dest, p.n, p.D, p.tile, p.n_tiles,
+                                   p.n_cols, table, pre);
             else
                 hipLaunchKernelGGL(hist_kernel, dim3(p.n_tiles), dim3(256), sizeof(uint32_t) * p.rows, s,
                                    dest, p.n, p.D, p.tile, p.n_tiles, table);
             RAFI_LAUNCH_CHECK();
-            hipLaunchKernelGGL(scan_reduce_kernel, dim3(p.scan_blocks), dim3(kScanThreads), 0, s, table,
-                               p.M, part);
-            if (p.scan_blocks <= kDirectMaxBlocks) {
-                hipLaunchKernelGGL(scan_apply_direct_kernel, dim3(p.scan_blocks), dim3(kScanThreads), 0, s,
-                                   table, p.M, part);
-            } else {
-                hipLaunchKernelGGL(scan_partials_kernel, dim3(1), dim3(kPartThreads), 0, s, part,
-                                   p.scan_blocks);
-                hipLaunchKernelGGL(scan_apply_kernel, dim3(p.scan_blocks), dim3(kScanThreads), 0, s, table,
-                                   p.M, part);
+        }
+        if (p.n_tiles > 0 && p.M <= kOneScanMax) {
+            hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(1024), 0, s, table, p.M, p.n_cols, p.D, p.n, offsets,
+                               summary, tile_offsets, ti, dropped, host);
+            RAFI_LAUNCH_CHECK();
+        } else {
+            if (p.n_tiles > 0) {
+                hipLaunchKernelGGL(scan_reduce_kernel, dim3(p.scan_blocks), dim3(kScanThreads), 0, s, table, p.M,
+                                   part);
+                if (p.scan_blocks <= kDirectMaxBlocks) {
+                    hipLaunchKernelGGL(scan_apply_direct_kernel, dim3(p.scan_blocks), dim3(kScanThreads), 0, s,
+                                       table, p.M, part);
+                } else {
+                    hipLaunchKernelGGL(scan_partials_kernel, dim3(1), dim3(kPartThreads), 0, s, part,
+                                       p.scan_blocks);
+                    hipLaunchKernelGGL(scan_apply_kernel, dim3(p.scan_blocks), dim3(kScanThreads), 0, s, table,
+                                       p.M, part);
+                }
+                RAFI_LAUNCH_CHECK();
             }
+            hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, s, table, p.n_cols, p.D, p.n, offsets,
+                               summary, tile_offsets, ti, dropped, host);
             RAFI_LAUNCH_CHECK();
         }
-        hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, s, table, p.n_tiles, p.D, p.n,
-                           offsets, summary, tile_offsets, ti, dropped);
-        RAFI_LAUNCH_CHECK();
     }
     if (ev) RAFI_HIP_CHECK(hipEventRecord(ev->before_scatter, s));
     if (p.n_tiles == 0) {
@@ -950,18 +1100,19 @@ int split_run(const SplitPlan &p, const void *items, const int32_t *dest, void *
     }
     const uint32_t *it = static_cast<const uint32_t *>(items);
     uint32_t *o = static_cast<uint32_t *>(out);
+    const RunBases bases{table, pre, p.n_cols, p.group_bits};
     switch (p.S / 4) {
-    case 1: launch_scatter<1>(p, it, dest, table, pre, o, dummy, s); break;
-    case 2: launch_scatter<2>(p, it, dest, table, pre, o, dummy, s); break;
-    case 3: launch_scatter<3>(p, it, dest, table, pre, o, dummy, s); break;
-    case 4: launch_scatter<4>(p, it, dest, table, pre, o, dummy, s); break;
-    case 6: launch_scatter<6>(p, it, dest, table, pre, o, dummy, s); break;
-    case 8: launch_scatter<8>(p, it, dest, table, pre, o, dummy, s); break;
-    case 10: launch_scatter<10>(p, it, dest, table, pre, o, dummy, s); break;
-    case 11: launch_scatter<11>(p, it, dest, table, pre, o, dummy, s); break;
-    case 12: launch_scatter<12>(p, it, dest, table, pre, o, dummy, s); break;
-    case 16: launch_scatter<16>(p, it, dest, table, pre, o, dummy, s); break;
-    default: launch_scatter<0>(p, it, dest, table, pre, o, dummy, s); break;
+    case 1: launch_scatter<1>(p, it, dest, bases, o, dummy, s); break;
+    case 2: launch_scatter<2>(p, it, dest, bases, o, dummy, s); break;
+    case 3: launch_scatter<3>(p, it, dest, bases, o, dummy, s); break;
+    case 4: launch_scatter<4>(p, it, dest, bases, o, dummy, s); break;
+    case 6: launch_scatter<6>(p, it, dest, bases, o, dummy, s); break;
+    case 8: launch_scatter<8>(p, it, dest, bases, o, dummy, s); break;
+    case 10: launch_scatter<10>(p, it, dest, bases, o, dummy, s); break;
+    case 11: launch_scatter<11>(p, it, dest, bases, o, dummy, s); break;
+    case 12: launch_scatter<12>(p, it, dest, bases, o, dummy, s); break;
+    case 16: launch_scatter<16>(p, it, dest, bases, o, dummy, s); break;
+    default: launch_scatter<0>(p, it, dest, bases, o, dummy, s); break;
     }
     RAFI_LAUNCH_CHECK();
     if (ev) RAFI_HIP_CHECK(hipEventRecord(ev->end, s));

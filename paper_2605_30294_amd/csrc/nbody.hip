@@ -781,7 +781,7 @@ int rafi_nb_seed(rafi_ctx *P, const rafi_nb_job *job, const void *particles, uin
                            static_cast<const NBParticle *>(particles), n);
     RAFI_LAUNCH_CHECK();
     uint64_t total = 0;
-    return rafi_round(P, nullptr, &total);
+    return round_run(P, nullptr, &total);
 }
 
 int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job, uint64_t *round_counts,
@@ -814,7 +814,7 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
         hipLaunchKernelGGL(nb_drift_kernel, dim3(blocks_for(n)), dim3(kNBThreads), 0, s, pv, job->splitters, dt, hdt);
     RAFI_LAUNCH_CHECK();
     uint64_t total = 0;
-    rc = rafi_round(P, counts_at(0), &total);
+    rc = round_run(P, counts_at(0), &total);
     if (rc != RAFI_OK) return rc;
     if (total != n) return RAFI_ERR_BAD_DEST;  // every particle has an owner
     rafi_view(P, &pv);
@@ -878,7 +878,7 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
         hipLaunchKernelGGL(nb_roots_kernel, dim3(blocks_for(n1_slots)), dim3(kNBThreads), 0, s, vv, roots, boxes, D);
     RAFI_LAUNCH_CHECK();
     uint64_t n1 = 0;
-    rc = rafi_round(V, counts_at(1), &n1);
+    rc = round_run(V, counts_at(1), &n1);
     if (rc != RAFI_OK) return rc;
     rafi_view(V, &vv);
     if (job->log_vp1 && n1)
@@ -895,7 +895,7 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
         hipLaunchKernelGGL(nb_accept_kernel, dim3(blocks_for(n1)), dim3(kNBThreads), 0, s, vv, rv, boxes, theta, acc);
     RAFI_LAUNCH_CHECK();
     uint64_t nr = 0;
-    rc = rafi_round(Rq, counts_at(2), &nr);
+    rc = round_run(Rq, counts_at(2), &nr);
     if (rc != RAFI_OK) return rc;
     rafi_view(Rq, &rv);
 
@@ -922,7 +922,7 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
                            dcell, boxes, theta, csize, aoff, n1);
     RAFI_LAUNCH_CHECK();
     uint64_t n2 = 0;
-    rc = rafi_round(V, counts_at(3), &n2);
+    rc = round_run(V, counts_at(3), &n2);
     if (rc != RAFI_OK) return rc;
     rafi_view(V, &vv);
 

@@ -177,6 +177,53 @@ def test_split_raw_shapes_ragged_end(orc, n, D, words):
 
 
 @pytest.mark.parametrize("n,D,words", [
+    (507_904, 64, 4), (507_905, 64, 4),            # 64 destinations: a column per tile, per 4 tiles
+    (258_048, 128, 8), (258_049, 128, 8), (262_143, 129, 8),
+    (5_000_003, 5, 1), (700_001, 100, 12), (1_200_000, 128, 6), (3_000_001, 64, 11)])
+def test_split_grouped_histogram(orc, n, D, words):
+    """Few destinations and a table too large for the one-launch scan: the
+    histogram with a table column per 4 tiles and 16-bit prefixes of the tiles
+    inside it; both sides of its bounds, tiles of 1024 to 2048 slots, ragged
+    last columns, with the destinations mixed and in long runs; the stateless
+    split, and a context's round whose results come through pinned memory."""
+    _run_split(orc, n, D, words, seed=n + 21, dist="mixed")
+    _run_ctx_split(orc, n, D, words, seed=n + 22, dist="zipf")
+    dev = device()
+    rng = np.random.default_rng(n)
+    dest = np.repeat(rng.integers(-1, D, n // 3000 + 1).astype(np.int32), 3000)[:n]
+    items = rng.integers(0, 2**31, (n, words)).astype(np.int32)
+    out, offsets, summary = rafi.multisplit(torch.from_numpy(items).to(dev), torch.from_numpy(dest).to(dev), D)
+    torch.cuda.synchronize()
+    e_out, _, e_off, e_done, _ = orc.multisplit(items, dest, D)
+    total = int(e_off[-1])
+    assert np.array_equal(offsets.cpu().numpy().astype(np.uint64), e_off) and int(summary[1]) == e_done
+    assert np.array_equal(out[:total].cpu().numpy(), e_out)
+
+
+def test_round_counts_through_pinned_memory(orc):
+    """Per-domain counts and totals of consecutive rounds for the most domains
+    a context takes: every round's results are its own, also when a round
+    moves nothing and when the counts are not asked for."""
+    dev = device()
+    D, n = 8192, 100_000
+    rng = np.random.default_rng(5)
+    ctx = rafi.Context(D, 8, n)
+    try:
+        for k in range(6):
+            m = [n, 1, 0, 77_777, n, 8192][k]
+            dest = rng.integers(-1, D, m).astype(np.int32)
+            items = rng.integers(0, 2**31, (max(m, 1), 2)).astype(np.int32)[:m]
+            ctx.begin(m)
+            ctx.emit_bulk(torch.from_numpy(items).to(dev), torch.from_numpy(dest).to(dev))
+            counts, total, _ = ctx.round(counts=k != 4)
+            expect = np.bincount(dest[dest >= 0], minlength=D).astype(np.uint64)
+            assert total == int(expect.sum())
+            assert counts is None if k == 4 else np.array_equal(counts, expect)
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("n,D,words", [
     (16_777_216, 64, 4), (16_777_220, 64, 4),      # 16-byte items: shape 4 up to 2^28 bytes
     (8_388_608, 128, 8), (8_388_612, 128, 8),      # 32-byte items: shape 2 up to 2^28 bytes
     (1_525_201, 64, 11), (1_525_204, 64, 11),      # 44-byte items: plain scatter up to 2^26 bytes
