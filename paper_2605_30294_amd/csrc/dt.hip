@@ -88,10 +88,29 @@ __device__ inline float dt_logf(float x)
     return __fmaf_rn(fe, 0.693145751953125f, __fmaf_rn(fe, 1.42860677e-06f, lnm));
 }
 
+// a / smax, correctly rounded as the IEEE division is, with the majorant's
+// reciprocal at hand: two corrections of the quotient through its exact
+// residual (Markstein 1990), 5 instructions for about 13. That needs a
+// majorant far from the ends of the exponent range (the same test in every
+// lane) and quotients that are zero, normal or, where only 1 - q is used, too
+// small to count.
+struct Majorant {
+    float smax, inv;
+    bool plain;
+    __device__ explicit Majorant(float s) : smax(s), inv(1.0f / s), plain(!(s >= 0x1p-40f && s <= 0x1p40f)) {}
+    __device__ float divide(float a) const
+    {
+        if (plain) return a / smax;
+        const float q0 = a * inv;
+        const float q1 = __fmaf_rn(__fmaf_rn(-smax, q0, a), inv, q0);
+        return __fmaf_rn(__fmaf_rn(-smax, q1, a), inv, q1);
+    }
+};
+
 // Next tentative point: p += s d, s = -ln(1 - u) / smax.
-__device__ inline void fly(const rafi_dt_job &job, DTItem &it)
+__device__ inline void fly(const rafi_dt_job &job, const Majorant &mj, DTItem &it)
 {
-    const float s = -dt_logf(1.0f - draw(job, it)) / job.smax;
+    const float s = mj.divide(-dt_logf(1.0f - draw(job, it)));
     it.px = __fmaf_rn(s, it.dx, it.px);
     it.py = __fmaf_rn(s, it.dy, it.py);
     it.pz = __fmaf_rn(s, it.dz, it.pz);
@@ -127,7 +146,8 @@ __device__ inline int32_t owner(const DTItem &it, const ea::Geo &g)
 __device__ inline float sigma_at(const rafi_dt_job &job, const DTItem &it)
 {
     const float p[3] = {it.px, it.py, it.pz};
-    return job.kappa * ea::density(job.volume, job.n, ea::tri_setup(job.n, p));
+    return job.kappa * ea::density(job.volume, job.n,
+                                   job.n <= ea::kSmallN ? ea::tri_setup_small(job.n, p) : ea::tri_setup(job.n, p));
 }
 
 __device__ inline void put_contrib(const rafi_dt_job &job, const DTItem &it)
@@ -173,7 +193,7 @@ dt_raygen_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
         it.px = __fmaf_rn(t0, d[0], o[0]);
         it.py = __fmaf_rn(t0, d[1], o[1]);
         it.pz = __fmaf_rn(t0, d[2], o[2]);
-        fly(job, it);
+        fly(job, Majorant(job.smax), it);
         e = owner(it, g);
     }
     if (e >= 0) rafi_forward_t(view, r, it, e);
@@ -249,61 +269,66 @@ dt_trace_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
         if ((uint64_t)(uint32_t)it.path >= n_paths || it.bounce < 0 || it.bounce >= job.max_bounce) {
             dest0 = RAFI_POISON;  // never true for items this library emitted
         } else {
-            for (;;) {
-                if (points == kMaxPoints) {  // bounded visit: continue next round in this brick
-                    out0 = it;
-                    dest0 = d;
-                    break;
-                }
+            // The walk ends at a real collision, outside the brick, or after
+            // kMaxPoints points. What follows each end comes after the loop,
+            // once for all lanes it happened to: inside, a collision's four
+            // or more draws held the wave's other lanes each time one lane
+            // collided (1M paths through 128^3: all launches 2.45 -> 1.57 ms).
+            const Majorant mj(job.smax);
+            bool hit = false, inside = true;
+            do {
                 ++points;
                 const float sigma = sigma_at(job, it);
                 if (it.kind == kPath) {
-                    const float u = draw(job, it);
-                    if (u * job.smax < sigma) {
-                        // real collision: shadow ray into slot 2i, bounced path into 2i + 1
-                        ++hits;
-                        const float w = it.w * job.albedo;
-                        DTItem sh = it;
-                        sh.kind = kShadow;
-                        sh.stream = 2u * (uint32_t)it.bounce + 1u;
-                        sh.count = 0;
-                        sh.w = w * job.radiance * 0.0795774715f;  // 1 / (4 pi)
-                        sh.dx = job.light[0];
-                        sh.dy = job.light[1];
-                        sh.dz = job.light[2];
-                        fly(job, sh);
-                        const int32_t es = owner(sh, g);
-                        if (es >= 0) {
-                            out0 = sh;
-                            dest0 = es;
-                        } else {
-                            put_contrib(job, sh);
-                        }
-                        if (it.bounce + 1 < job.max_bounce) {
-                            it.bounce += 1;
-                            it.stream = 2u * (uint32_t)it.bounce;
-                            it.count = 0;
-                            it.w = w;
-                            isotropic(job, it);
-                            fly(job, it);
-                            dest1 = owner(it, g);
-                        }
-                        break;
-                    }
+                    hit = draw(job, it) * job.smax < sigma;
                 } else {
-                    it.w = it.w * (1.0f - sigma / job.smax);
+                    it.w = it.w * (1.0f - mj.divide(sigma));
                 }
-                fly(job, it);
-                const float p[3] = {it.px, it.py, it.pz};
-                if (box.contains(p)) continue;
-                const int32_t e = ea::owner_of(p, g);
+                if (!hit) {
+                    fly(job, mj, it);
+                    const float p[3] = {it.px, it.py, it.pz};
+                    inside = box.contains(p);
+                }
+            } while (!hit && inside && points < kMaxPoints);
+            __builtin_amdgcn_wave_barrier();
+            if (hit) {
+                // shadow ray into slot 2i, bounced path into 2i + 1
+                hits = 1;
+                const float w = it.w * job.albedo;
+                DTItem sh = it;
+                sh.kind = kShadow;
+                sh.stream = 2u * (uint32_t)it.bounce + 1u;
+                sh.count = 0;
+                sh.w = w * job.radiance * 0.0795774715f;  // 1 / (4 pi)
+                sh.dx = job.light[0];
+                sh.dy = job.light[1];
+                sh.dz = job.light[2];
+                fly(job, mj, sh);
+                const int32_t es = owner(sh, g);
+                if (es >= 0) {
+                    out0 = sh;
+                    dest0 = es;
+                } else {
+                    put_contrib(job, sh);
+                }
+                if (it.bounce + 1 < job.max_bounce) {
+                    it.bounce += 1;
+                    it.stream = 2u * (uint32_t)it.bounce;
+                    it.count = 0;
+                    it.w = w;
+                    isotropic(job, it);
+                    fly(job, mj, it);
+                    dest1 = owner(it, g);
+                }
+            } else {
+                // out of the brick, or bounded: it goes on next round
+                const int32_t e = inside ? d : owner(it, g);
                 if (e >= 0) {
                     out0 = it;
                     dest0 = e;
                 } else if (it.kind == kShadow) {
                     put_contrib(job, it);
                 }
-                break;
             }
         }
         if (dest0 == RAFI_DONE) rafi_done(view, 2 * i);

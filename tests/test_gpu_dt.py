@@ -88,6 +88,25 @@ def test_matches_oracle(orc, case):
     assert g["counters"][0] >= g["counts"].sum() and g["counters"][1] <= g["counters"][0]
 
 
+@pytest.mark.parametrize("n,grid,nv,w,B,scale", [
+    (32, (2, 2, 2), 1, 640, 3, 1.0),          # large launches (more than 2^18 slots)
+    (24, (3, 1, 2), 2, 370, 2, 1.0),
+    (24, (2, 1, 1), 1, 40, 2, 1e-13),         # a majorant outside the corrected division's range
+    (64, (1, 1, 1), 1, 33, 2, 1.0),           # one brick: visits of up to several hundred points
+])
+def test_launch_sizes_and_majorants(orc, n, grid, nv, w, B, scale):
+    """Both sides of the sizes the launches choose by, one to several hundred
+    points per visit, and a majorant too small for the corrected division."""
+    vol = W.blob_volume(n, 60 + n, n_blobs=12)
+    views = W.random_views(nv, n, w, w, seed=61)
+    kappa = 0.3 * scale
+    smax = float(np.float32(kappa * float(vol.max()) * (4.0 if n == 64 else 1.1)))
+    announce(f"dt n={n} grid={grid} paths={nv * w * w} smax={smax}")
+    g = _stepwise(vol, grid, views, kappa, smax, 0.7, (0.6, 0.0, 0.8), 1.0, B, 9)
+    o = orc.dt_render(vol, grid, views, kappa, smax, 0.7, (0.6, 0.0, 0.8), 1.0, B, 9, queue_cap=1 << 24)
+    _compare(g, o)
+
+
 def test_render_entry_point_deterministic(orc):
     dev = device()
     n, grid = 64, (4, 4, 4)
