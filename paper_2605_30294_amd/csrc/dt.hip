@@ -201,7 +201,71 @@ dt_raygen_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
 }
 
 // -------------------------------------------------------------- trace ----
-// Outcome of one visit: what goes into slots 2i and 2i + 1 (dest -1 = DONE).
+// Never true for items this library emitted.
+__device__ inline bool foreign(const rafi_dt_job &job, const DTItem &it, uint64_t n_paths)
+{
+    return (uint64_t)(uint32_t)it.path >= n_paths || it.bounce < 0 || it.bounce >= job.max_bounce;
+}
+
+__device__ inline void poison_visit(const rafi_device_view &view, const DTItem &it, uint64_t i)
+{
+    rafi_forward_t(view, 2 * i, it, RAFI_POISON);
+    rafi_done(view, 2 * i + 1);
+}
+
+// The end of a visit to brick d: what goes into slots 2i and 2i + 1. hit: a
+// real collision at the item's position; else inside: the visit was bounded
+// and goes on next round; else the position is the next tentative point,
+// outside the brick.
+__device__ inline void finish_visit(const rafi_device_view &view, const rafi_dt_job &job, const Majorant &mj,
+                                    const ea::Geo &g, DTItem it, uint64_t i, int32_t d, bool hit, bool inside)
+{
+    DTItem out0 = it;
+    int32_t dest0 = RAFI_DONE, dest1 = RAFI_DONE;
+    if (hit) {
+        // shadow ray into slot 2i, bounced path into 2i + 1
+        const float w = it.w * job.albedo;
+        DTItem sh = it;
+        sh.kind = kShadow;
+        sh.stream = 2u * (uint32_t)it.bounce + 1u;
+        sh.count = 0;
+        sh.w = w * job.radiance * 0.0795774715f;  // 1 / (4 pi)
+        sh.dx = job.light[0];
+        sh.dy = job.light[1];
+        sh.dz = job.light[2];
+        fly(job, mj, sh);
+        const int32_t es = owner(sh, g);
+        if (es >= 0) {
+            out0 = sh;
+            dest0 = es;
+        } else {
+            put_contrib(job, sh);
+        }
+        if (it.bounce + 1 < job.max_bounce) {
+            it.bounce += 1;
+            it.stream = 2u * (uint32_t)it.bounce;
+            it.count = 0;
+            it.w = w;
+            isotropic(job, it);
+            fly(job, mj, it);
+            dest1 = owner(it, g);
+        }
+    } else {
+        const int32_t e = inside ? d : owner(it, g);
+        if (e >= 0) {
+            out0 = it;
+            dest0 = e;
+        } else if (it.kind == kShadow) {
+            put_contrib(job, it);
+        }
+    }
+    if (dest0 == RAFI_DONE) rafi_done(view, 2 * i);
+    else rafi_forward_t(view, 2 * i, out0, dest0);
+    if (dest1 >= 0) rafi_forward_t(view, 2 * i + 1, it, dest1);
+    else rafi_done(view, 2 * i + 1);
+}
+
+// One lane per item.
 __global__ void __launch_bounds__(256)
 dt_trace_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
 {
@@ -264,10 +328,8 @@ dt_trace_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
         d = s_d[t];
         const ea::Box box = ea::box_of(d, g);
         DTItem it = static_cast<const DTItem *>(view.in_items)[i];
-        DTItem out0 = it;
-        int32_t dest0 = RAFI_DONE, dest1 = RAFI_DONE;
-        if ((uint64_t)(uint32_t)it.path >= n_paths || it.bounce < 0 || it.bounce >= job.max_bounce) {
-            dest0 = RAFI_POISON;  // never true for items this library emitted
+        if (foreign(job, it, n_paths)) {
+            poison_visit(view, it, i);
         } else {
             // The walk ends at a real collision, outside the brick, or after
             // kMaxPoints points. What follows each end comes after the loop,
@@ -291,50 +353,9 @@ dt_trace_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
                 }
             } while (!hit && inside && points < kMaxPoints);
             __builtin_amdgcn_wave_barrier();
-            if (hit) {
-                // shadow ray into slot 2i, bounced path into 2i + 1
-                hits = 1;
-                const float w = it.w * job.albedo;
-                DTItem sh = it;
-                sh.kind = kShadow;
-                sh.stream = 2u * (uint32_t)it.bounce + 1u;
-                sh.count = 0;
-                sh.w = w * job.radiance * 0.0795774715f;  // 1 / (4 pi)
-                sh.dx = job.light[0];
-                sh.dy = job.light[1];
-                sh.dz = job.light[2];
-                fly(job, mj, sh);
-                const int32_t es = owner(sh, g);
-                if (es >= 0) {
-                    out0 = sh;
-                    dest0 = es;
-                } else {
-                    put_contrib(job, sh);
-                }
-                if (it.bounce + 1 < job.max_bounce) {
-                    it.bounce += 1;
-                    it.stream = 2u * (uint32_t)it.bounce;
-                    it.count = 0;
-                    it.w = w;
-                    isotropic(job, it);
-                    fly(job, mj, it);
-                    dest1 = owner(it, g);
-                }
-            } else {
-                // out of the brick, or bounded: it goes on next round
-                const int32_t e = inside ? d : owner(it, g);
-                if (e >= 0) {
-                    out0 = it;
-                    dest0 = e;
-                } else if (it.kind == kShadow) {
-                    put_contrib(job, it);
-                }
-            }
+            finish_visit(view, job, mj, g, it, i, d, hit, inside);
+            hits = hit ? 1 : 0;
         }
-        if (dest0 == RAFI_DONE) rafi_done(view, 2 * i);
-        else rafi_forward_t(view, 2 * i, out0, dest0);
-        if (dest1 >= 0) rafi_forward_t(view, 2 * i + 1, it, dest1);
-        else rafi_done(view, 2 * i + 1);
     }
     if (job.counters) {  // the whole wave is here: one atomic pair per wave
 #pragma unroll
@@ -349,6 +370,112 @@ dt_trace_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
     }
 }
 
+// -------------------------------------------- 32 lanes per item -----------
+// Launches over few items are bound by the latency of the longest visit, a
+// chain of some 250 to 350 instructions and a gather per point (a round of a
+// few thousand items took 50 us). The random numbers are counter based, so
+// here half a wave carries one item and lane l prepares point l of the next
+// 32: its draws, its free flight, then, after the positions are chained
+// through the half (one fused multiply-add per coordinate and point, the only
+// serial part), its density and decision. The first lane whose point ends the
+// visit decides; what later lanes prepared is dropped. Every operation and
+// its order is the one-lane kernel's, so the results are bit-identical.
+
+// Lane Q of this half's value (Q constant).
+template <int Q>
+__device__ inline float half_read(float v)
+{
+    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), Q << 5));
+}
+
+// p after the flights of lanes 0 .. l - 1, for this half's lane l.
+template <int Q = 0>
+__device__ inline void chain_flights(float s, uint32_t l, const DTItem &it, float &x, float &y, float &z)
+{
+    if constexpr (Q < 31) {
+        const float sq = half_read<Q>(s);
+        if (l > (uint32_t)Q) {
+            x = __fmaf_rn(sq, it.dx, x);
+            y = __fmaf_rn(sq, it.dy, y);
+            z = __fmaf_rn(sq, it.dz, z);
+        }
+        chain_flights<Q + 1>(s, l, it, x, y, z);
+    }
+}
+
+// w times the factors of lanes 0 .. last, in order.
+template <int Q = 0>
+__device__ inline float chain_weights(float f, uint32_t last, float w)
+{
+    if constexpr (Q < 32) {
+        const float fq = half_read<Q>(f);
+        return chain_weights<Q + 1>(f, last, (uint32_t)Q <= last ? w * fq : w);
+    } else {
+        return w;
+    }
+}
+
+constexpr uint32_t kHalfItems = 8;  // items per workgroup of 256 threads
+
+__global__ void __launch_bounds__(32 * kHalfItems)
+dt_trace_half_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
+{
+    const uint64_t n_in = rafi_queue_length(view);
+    const uint32_t nb = (uint32_t)((n_in + kHalfItems - 1) / kHalfItems);
+    if (blockIdx.x >= nb) return;
+    const uint32_t l = threadIdx.x & 31, upper = threadIdx.x & 32;
+    const uint64_t i = rafi_xcd_block(blockIdx.x, nb) * (uint64_t)kHalfItems + (threadIdx.x >> 5);
+    if (i >= n_in) return;  // whole halves: the cross-lane reads below stay inside one
+    const ea::Geo g = ea::make_geo(job.n, job.grid);
+    const int32_t d = ea::find_domain(view.in_offsets, view.n_domains, i);
+    const ea::Box box = ea::box_of(d, g);
+    DTItem it = static_cast<const DTItem *>(view.in_items)[i];
+    if (foreign(job, it, n_paths)) {
+        if (l == 0) poison_visit(view, it, i);
+        return;
+    }
+    const Majorant mj(job.smax);
+    const bool path = it.kind == kPath;
+    uint32_t points = 0;
+    bool hit = false, inside = true;
+    do {
+        // point l's draws: a path's collision test, then the flight
+        DTItem mine = it;
+        mine.count = it.count + (path ? 2 * l : l);
+        const float u = path ? draw(job, mine) : 0.0f;
+        const float s = mj.divide(-dt_logf(1.0f - draw(job, mine)));
+        // point l, and the one its flight leads to
+        float p[3] = {it.px, it.py, it.pz};
+        chain_flights(s, l, it, p[0], p[1], p[2]);
+        const float q[3] = {__fmaf_rn(s, it.dx, p[0]), __fmaf_rn(s, it.dy, p[1]), __fmaf_rn(s, it.dz, p[2])};
+        mine.px = p[0];
+        mine.py = p[1];
+        mine.pz = p[2];
+        // (lanes past the visit's end have points outside the brick, which the
+        // sampler clamps into the volume)
+        const float sigma = sigma_at(job, mine);
+        const bool collides = path && u * job.smax < sigma;
+        const bool stays = box.contains(q);
+        const uint32_t ends = (uint32_t)(__ballot(collides || !stays) >> upper);
+        const uint32_t last = ends ? (uint32_t)__ffs((int)ends) - 1 : 31;
+        if (!path) it.w = chain_weights(1.0f - mj.divide(sigma), last, it.w);
+        hit = __shfl((int)collides, (int)last, 32) != 0;
+        inside = hit || ends == 0;
+        it.px = __shfl(hit ? p[0] : q[0], (int)last, 32);
+        it.py = __shfl(hit ? p[1] : q[1], (int)last, 32);
+        it.pz = __shfl(hit ? p[2] : q[2], (int)last, 32);
+        it.count += path ? 2 * last + (hit ? 1 : 2) : last + 1;
+        points += last + 1;
+    } while (!hit && inside && points < kMaxPoints);
+    if (l != 0) return;
+    finish_visit(view, job, mj, g, it, i, d, hit, inside);
+    if (job.counters) {
+        atomicAdd(&job.counters[0], (unsigned long long)points);
+        if (hit) atomicAdd(&job.counters[1], 1ull);
+    }
+}
+static_assert(kMaxPoints % 32 == 0, "a bounded visit ends with a whole turn of the half");
+
 // image[path] = sum over scattering events, in event order
 __global__ void dt_resolve_kernel(rafi_dt_job job, uint64_t n_paths)
 {
@@ -357,6 +484,24 @@ __global__ void dt_resolve_kernel(rafi_dt_job job, uint64_t n_paths)
     float s = 0.0f;
     for (int32_t b = 0; b < job.max_bounce; ++b) s += job.contrib[r * job.max_bounce + b];
     job.image[r] = s;
+}
+
+// Launches of at most this many queued items (an upper bound is enough, in
+// rounds after the first about 3 times the items there are) take 32 lanes per
+// item: it needs twice the instructions, and wins while the one-lane launch
+// lasts as long as its longest visit. 1M paths through 128^3, whole render:
+// never 2.27-2.37 ms, up to 50 K 1.93, 100 K 1.88, 160 K 1.86, 262 K 1.87,
+// 524 K 2.05, always 3.74. A round of 10 K items: 50 -> 9 us.
+constexpr uint64_t kHalfMax = 160 * 1024;
+
+void launch_trace(const rafi_device_view &v, const rafi_dt_job &job, uint64_t n_paths, hipStream_t s)
+{
+    if (v.n_in == 0) return;
+    if (v.n_in <= kHalfMax)
+        hipLaunchKernelGGL(dt_trace_half_kernel, dim3((uint32_t)((v.n_in + kHalfItems - 1) / kHalfItems)),
+                           dim3(32 * kHalfItems), 0, s, v, job, n_paths);
+    else
+        hipLaunchKernelGGL(dt_trace_kernel, dim3((uint32_t)((v.n_in + 255) / 256)), dim3(256), 0, s, v, job, n_paths);
 }
 
 uint64_t n_paths_of(const rafi_dt_job *j) { return (uint64_t)j->n_views * j->width * j->height; }
@@ -411,9 +556,7 @@ int rafi_dt_trace(rafi_ctx *c, const rafi_dt_job *job)
     rafi_device_view v;
     rafi_view(c, &v);
     const int ph = prof_domain_begin(c);
-    if (v.n_in)
-        hipLaunchKernelGGL(dt_trace_kernel, dim3((uint32_t)((v.n_in + 255) / 256)), dim3(256), 0, c->stream, v,
-                           *job, n_paths_of(job));
+    launch_trace(v, *job, n_paths_of(job), c->stream);
     prof_domain_end(c, ph);
     RAFI_LAUNCH_CHECK();
     return RAFI_OK;
@@ -438,9 +581,7 @@ int rafi_dt_render(rafi_ctx *c, const rafi_dt_job *job, int32_t max_rounds, int3
         rafi_view(c, &v);
         v.n_in = bound;
         const int ph = prof_domain_begin(c);
-        if (bound)
-            hipLaunchKernelGGL(dt_trace_kernel, dim3((uint32_t)((bound + 255) / 256)), dim3(256), 0, c->stream, v,
-                               *job, paths);
+        launch_trace(v, *job, paths, c->stream);
         prof_domain_end(c, ph);
         RAFI_LAUNCH_CHECK();
         return RAFI_OK;

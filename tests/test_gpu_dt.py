@@ -89,7 +89,7 @@ def test_matches_oracle(orc, case):
 
 
 @pytest.mark.parametrize("n,grid,nv,w,B,scale", [
-    (32, (2, 2, 2), 1, 640, 3, 1.0),          # large launches (more than 2^18 slots)
+    (32, (2, 2, 2), 1, 640, 3, 1.0),          # launches over 160 K items, one lane each, and under
     (24, (3, 1, 2), 2, 370, 2, 1.0),
     (24, (2, 1, 1), 1, 40, 2, 1e-13),         # a majorant outside the corrected division's range
     (64, (1, 1, 1), 1, 33, 2, 1.0),           # one brick: visits of up to several hundred points
