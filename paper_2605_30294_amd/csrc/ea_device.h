@@ -216,11 +216,20 @@ __device__ inline float density_cached(const float *__restrict__ vol, int32_t n,
     return interp_corners(cc, t);
 }
 
-// First k in [0, K] for which pred(k) flips from `from` to !from (K if never).
+// First k in [0, K] for which pred(k) flips from `from` to !from (K if never):
+// the estimate or a neighbour of it, or else a binary search of what is left.
 template <typename Pred>
-__device__ inline int32_t first_flip(int32_t K, bool from, Pred pred)
+__device__ inline int32_t first_flip(int32_t K, bool from, float estimate, Pred pred)
 {
     int32_t lo = 0, hi = K;
+    const int32_t k = min((int32_t)fminf(fmaxf(estimate, 0.0f), 2147483520.0f), K);
+    if (k < K && pred(k) == from) {
+        lo = k + 1;
+        if (lo < K && pred(lo) != from) hi = lo;
+    } else {
+        hi = k;
+        if (k > 0 && pred(k - 1) == from) lo = k;
+    }
     while (lo < hi) {
         const int32_t mid = (lo + hi) >> 1;
         if (pred(mid) != from) hi = mid; else lo = mid + 1;
@@ -231,11 +240,12 @@ __device__ inline int32_t first_flip(int32_t K, bool from, Pred pred)
 // Ray generation: the first sample index inside [0, n)^3, or -1 if none.
 // Every coordinate of p_k is monotone in k (the product and the fma are
 // correctly rounded, hence monotone), so the inside samples form one interval
-// of k, found by a binary search per face; *owner is the brick of that sample.
+// of k: per face, the straight line's crossing estimates its end and the exact
+// test settles it. *owner is the brick of the first sample.
 __device__ inline int32_t first_inside(const Geo &g, const float org[3], const float dir[3], int32_t K, float dt,
                                        int32_t *owner)
 {
-    const float fn = (float)g.n;
+    const float fn = (float)g.n, rdt = __builtin_amdgcn_rcpf(dt);
     int32_t k_lo = 0, k_hi = K;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -245,12 +255,14 @@ __device__ inline int32_t first_inside(const Geo &g, const float org[3], const f
         };
         auto ge0 = [&](int32_t k) { return coord(k) >= 0.0f; };
         auto ltn = [&](int32_t k) { return coord(k) < fn; };
+        const float r = __builtin_amdgcn_rcpf(dir[a]) * rdt;
+        const float k0 = ceilf(-org[a] * r - 0.5f), kn = ceilf((fn - org[a]) * r - 0.5f);
         if (dir[a] > 0.0f) {
-            k_lo = max(k_lo, first_flip(K, false, ge0));   // becomes true
-            k_hi = min(k_hi, first_flip(K, true, ltn));    // becomes false
+            k_lo = max(k_lo, first_flip(K, false, k0, ge0));   // becomes true
+            k_hi = min(k_hi, first_flip(K, true, kn, ltn));    // becomes false
         } else if (dir[a] < 0.0f) {
-            k_lo = max(k_lo, first_flip(K, false, ltn));
-            k_hi = min(k_hi, first_flip(K, true, ge0));
+            k_lo = max(k_lo, first_flip(K, false, kn, ltn));
+            k_hi = min(k_hi, first_flip(K, true, k0, ge0));
         } else if (!(org[a] >= 0.0f && org[a] < fn)) {
             k_hi = 0;
         }
