@@ -389,7 +389,7 @@ typedef struct rafi_batch rafi_batch;
 typedef struct rafi_batch_tuning {
     uint32_t split_tile;      /* slots per split tile, multiple of 256, >= 1024 (default 4096) */
     uint32_t march_block;     /* threads per march workgroup: 64, 128, 256 or 512 (default 256) */
-    uint32_t march_grid;      /* persistent march workgroups (default 2048) */
+    uint32_t march_grid;      /* march workgroups at most (default 32768) */
     int32_t use_graph;        /* 1: rounds replayed from a captured hipGraph (default 1) */
     int32_t rounds_per_sync;  /* rounds launched between host checks of the total (default 4) */
 } rafi_batch_tuning;

@@ -14,7 +14,7 @@ import torch
 DEFAULT_SPACE = {
     "split_tile": [2048, 4096, 8192],
     "march_block": [128, 256],
-    "march_grid": [1024, 2048, 4096],
+    "march_grid": [2048, 8192, 32768],
     "use_graph": [1],
     "rounds_per_sync": [8],
 }

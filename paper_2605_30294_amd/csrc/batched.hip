@@ -13,7 +13,7 @@
 //   scan      exclusive scan of the table = output slot of each (tile, dest)
 //   finalize  exclusive scan of the per-domain totals -> new queue offsets
 //   scatter   per tile: the staged stable scatter of split_device.h
-//   march     persistent kernel over all items of all scenes
+//   march     all items of all scenes, a wavefront at a time
 #include <algorithm>
 #include <cstring>
 #include <new>
@@ -35,7 +35,8 @@ constexpr int kScanChunk = 4096;  // 256 threads x 16
 constexpr int kPartMax = 16384;
 
 // summary words (u64)
-enum { S_TOTAL = 0, S_DONE, S_BAD, S_TILES, S_TABLE, S_SLOTS, S_ROUNDS, S_COUNT };
+// S_ALIVE: the last march left something for another round.
+enum { S_TOTAL = 0, S_DONE, S_BAD, S_TILES, S_TABLE, S_SLOTS, S_ROUNDS, S_ALIVE, S_COUNT };
 
 struct BatchDev {
     const rafi_ea_scene *scenes;   // [S]
@@ -60,6 +61,25 @@ struct BatchDev {
 };
 
 // ------------------------------------------------------------- raygen ---
+// The last index with a[index] <= x in [0, n), a[0] <= x, for an x that is the
+// same in every lane of the wavefront: 64 probes at a time, so two dependent
+// loads up to 4096 entries instead of a dozen. All 64 lanes must be active.
+template <typename T>
+__device__ inline int32_t wave_last_le(const T *__restrict__ a, int32_t n, T x)
+{
+    const int32_t lane = (int32_t)(threadIdx.x & 63u);
+    int32_t lo = 0;
+    while (n > 1) {
+        const int32_t step = (n + 63) / 64;
+        const int32_t at = lane * step;
+        const bool le = at < n && a[lo + at] <= x;
+        const int32_t hit = (int32_t)__popcll(__ballot(le)) - 1;
+        lo += hit * step;
+        n = min(step, n - hit * step);
+    }
+    return lo;
+}
+
 __device__ inline int32_t scene_of_ray(const uint32_t *scene_ray, int32_t S, uint32_t r)
 {
     int32_t lo = 0, hi = S;  // last s with scene_ray[s] <= r
@@ -73,9 +93,12 @@ __device__ inline int32_t scene_of_ray(const uint32_t *scene_ray, int32_t S, uin
 __global__ void __launch_bounds__(256)
 batch_raygen_kernel(BatchDev b, const float *__restrict__ volumes, float *__restrict__ image, uint32_t n_rays)
 {
-    const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
+    // A wavefront's 64 rays mostly belong to one scene: its first ray's.
+    const uint32_t r0 = blockIdx.x * blockDim.x + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+    int32_t s = wave_last_le(b.scene_ray, b.S, r0);
+    const uint32_t r = r0 + (threadIdx.x & 63u);
     if (r >= n_rays) return;
-    const int32_t s = scene_of_ray(b.scene_ray, b.S, r);
+    if (r >= b.scene_ray[s + 1]) s = scene_of_ray(b.scene_ray, b.S, r);
     const rafi_ea_scene &sc = b.scenes[s];
     const Geo g = ea::make_geo(sc.n, sc.grid);
     float org[3], dir[3];
@@ -144,6 +167,7 @@ batch_plan_kernel(BatchDev b)
         b.summary[S_SLOTS] = b.offsets[b.Dt];
         b.summary[S_DONE] = 0;
         b.summary[S_BAD] = 0;
+        b.summary[S_ALIVE] = 0;
     }
 }
 
@@ -156,11 +180,7 @@ struct TileRef {
 
 __device__ inline TileRef tile_ref(const BatchDev &b, uint32_t t)
 {
-    int32_t lo = 0, hi = b.S;  // last s with seg_tiles[s] <= t
-    while (hi - lo > 1) {
-        const int32_t mid = (lo + hi) >> 1;
-        if (b.seg_tiles[mid] <= t) lo = mid; else hi = mid;
-    }
+    const int32_t lo = wave_last_le(b.seg_tiles, b.S, t);
     TileRef r;
     r.s = lo;
     r.local = t - b.seg_tiles[lo];
@@ -182,12 +202,32 @@ batch_hist_kernel(BatchDev b)
     const int32_t D = b.scene_dom[tr.s + 1] - dbase;
     for (int32_t e = threadIdx.x; e < D + 2; e += blockDim.x) h[e] = 0;
     __syncthreads();
-    for (uint64_t i = tr.begin + threadIdx.x; i < tr.end; i += blockDim.x) {
-        const int32_t d = b.dest[i];
-        uint32_t bucket = (uint32_t)D + 1u;  // invalid
-        if (d == RAFI_DONE) bucket = (uint32_t)D;
-        else if (d >= dbase && d < dbase + D) bucket = (uint32_t)(d - dbase);
-        atomicAdd(&h[bucket], 1u);
+    // Eight destinations in flight per lane. Slots next to each other mostly go
+    // to the same domain, and 64 additions to one LDS word take 64 turns: the
+    // first lane's bucket and the next one left are each added as a count
+    // (32.5 M slots of 256 scenes, 7.9 K tiles: 113 -> 43 us).
+    constexpr int kU = 8;
+    const int32_t lane = (int32_t)(threadIdx.x & 63u);
+    for (uint64_t i0 = tr.begin; i0 < tr.end; i0 += kU * 256u) {
+        const uint64_t i = i0 + threadIdx.x;
+        int32_t d[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) d[u] = i + u * 256u < tr.end ? b.dest[i + u * 256u] : RAFI_DONE;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            uint32_t bucket = (uint32_t)D + 1u;  // invalid
+            if (d[u] == RAFI_DONE) bucket = (uint32_t)D;
+            else if (d[u] >= dbase && d[u] < dbase + D) bucket = (uint32_t)(d[u] - dbase);
+            uint64_t left = __ballot(i + u * 256u < tr.end);
+#pragma unroll
+            for (int turn = 0; turn < 2 && left; ++turn) {
+                const int32_t first = __ffsll((unsigned long long)left) - 1;
+                const uint64_t same = left & __ballot(bucket == (uint32_t)__builtin_amdgcn_readlane((int)bucket, first));
+                if (lane == first) atomicAdd(&h[bucket], (uint32_t)__popcll(same));
+                left &= ~same;
+            }
+            if (left >> lane & 1u) atomicAdd(&h[bucket], 1u);
+        }
     }
     __syncthreads();
     const uint64_t tb = b.seg_table[tr.s];
@@ -321,36 +361,55 @@ batch_scatter_kernel(BatchDev b, uint64_t cap)
 }
 
 // -------------------------------------------------------------- march ---
+// Item in[i] of domain d through its brick; true if it needs another round.
+__device__ inline bool march_slot(const BatchDev &b, const float *__restrict__ volumes, float *__restrict__ image,
+                                  uint32_t n_rays, int32_t d, uint64_t i)
+{
+    const rafi_ea_scene &sc = b.scenes[b.dom_scene[d]];
+    Item it = static_cast<const Item *>(b.items_in)[i];
+    if ((uint32_t)it.ray >= n_rays || (uint32_t)it.ray < sc.ray_base) {  // never for emitted items
+        b.dest[i] = RAFI_POISON;
+        return true;
+    }
+    const Geo g = ea::make_geo(sc.n, sc.grid);
+    float org[3], dir[3];
+    int32_t K;
+    ea::ray_setup(sc.view, (int32_t)(it.ray - sc.ray_base), org, dir, &K);
+    const int32_t local = ea::march_through(volumes + sc.volume_offset, g, ea::box_of(d - sc.dom_base, g), org, dir,
+                                            K, b.dt, b.c, it);
+    if (local >= 0) {
+        static_cast<Item *>(b.items_out)[i] = it;
+        b.dest[i] = sc.dom_base + local;
+        return true;
+    }
+    image[it.ray] = it.I;
+    b.dest[i] = RAFI_DONE;
+    return false;
+}
+
+// March workgroups unless the caller sets another number; never more than the
+// rays fill. Visits differ in length up to eight times between scenes, and of
+// 2048 workgroups only 1280 fit on the card at once (95 VGPRs): a grid this
+// size leaves the balance to the hardware's dispatch. 256 scenes, 32.5 M rays:
+// 9.5 ms a render at 2048, 8.2 at 8192, 7.9 at 32768 and beyond.
+constexpr uint32_t kMarchGrid = 32768;
+
 __global__ void batch_march_kernel(BatchDev b, const float *__restrict__ volumes, float *__restrict__ image,
                                    uint32_t n_rays)
 {
     const uint64_t n_in = b.summary[S_TOTAL];
-    const Item *in = static_cast<const Item *>(b.items_in);
-    Item *out = static_cast<Item *>(b.items_out);
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n_in;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        const int32_t d = ea::find_domain(b.offsets, b.Dt, i);
-        const int32_t s = b.dom_scene[d];
-        const rafi_ea_scene &sc = b.scenes[s];
-        Item it = in[i];
-        if ((uint32_t)it.ray >= n_rays || (uint32_t)it.ray < sc.ray_base) {  // never for emitted items
-            b.dest[i] = RAFI_POISON;
-            continue;
-        }
-        const Geo g = ea::make_geo(sc.n, sc.grid);
-        float org[3], dir[3];
-        int32_t K;
-        ea::ray_setup(sc.view, (int32_t)(it.ray - sc.ray_base), org, dir, &K);
-        const int32_t local = ea::march_through(volumes + sc.volume_offset, g, ea::box_of(d - sc.dom_base, g),
-                                                org, dir, K, b.dt, b.c, it);
-        if (local >= 0) {
-            out[i] = it;
-            b.dest[i] = sc.dom_base + local;
-        } else {
-            image[it.ray] = it.I;
-            b.dest[i] = RAFI_DONE;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+    bool alive = false;
+    for (uint64_t i0 = blockIdx.x * (uint64_t)blockDim.x + wave; i0 < n_in; i0 += (uint64_t)gridDim.x * blockDim.x) {
+        // A wavefront's 64 slots mostly lie in one domain: its first slot's.
+        int32_t d = wave_last_le(b.offsets, b.Dt, i0);
+        const uint64_t i = i0 + (threadIdx.x & 63u);
+        if (i < n_in) {
+            if (i >= b.offsets[d + 1]) d = ea::find_domain(b.offsets, b.Dt, i);
+            alive |= march_slot(b, volumes, image, n_rays, d, i);
         }
     }
+    if (alive) b.summary[S_ALIVE] = 1;
 }
 
 }  // namespace
@@ -364,7 +423,7 @@ struct rafi_batch {
     float dt = 0.5f, c = 0.025f;
     std::vector<rafi_ea_scene> scenes;
     std::vector<uint32_t> rays_per_scene;
-    rafi_batch_tuning tune{4096, 256, 2048, 1, 4};
+    rafi_batch_tuning tune{4096, 256, rafi::kMarchGrid, 1, 4};
     // device
     rafi_ea_scene *d_scenes = nullptr;
     int32_t *d_dom_scene = nullptr, *d_scene_dom = nullptr;
@@ -469,7 +528,9 @@ int launch_round(rafi_batch *b, const float *volumes, float *image, hipStream_t 
     hipLaunchKernelGGL(batch_finalize_kernel, dim3(1), dim3(1024), 0, st, d);
     const size_t lds = dev::staged_lds_bytes<kNW, kR, kW>(kMaxSceneDomains);
     hipLaunchKernelGGL(batch_scatter_kernel, dim3(tiles), dim3(64 * kW), lds, st, d, (uint64_t)b->n_rays);
-    hipLaunchKernelGGL(batch_march_kernel, dim3(b->tune.march_grid), dim3(b->tune.march_block), 0, st, d, volumes,
+    const uint64_t march = (b->n_rays + b->tune.march_block - 1) / b->tune.march_block;  // a round has no more items
+    const uint32_t grid = (uint32_t)std::min<uint64_t>(b->tune.march_grid, std::max<uint64_t>(march, 1));
+    hipLaunchKernelGGL(batch_march_kernel, dim3(grid), dim3(b->tune.march_block), 0, st, d, volumes,
                        image, (uint32_t)b->n_rays);
     RAFI_LAUNCH_CHECK();
     return RAFI_OK;
@@ -676,6 +737,7 @@ int rafi_batch_render(rafi_batch *b, const float *volumes, float *image, int32_t
             if (rounds) *rounds = (int32_t)b->h_summary[S_ROUNDS] + 1;
             return RAFI_ERR_MAX_ROUNDS;
         }
+        if (b->h_summary[S_ALIVE] == 0) break;  // another round would find nothing
     }
     if (rounds) *rounds = (int32_t)b->h_summary[S_ROUNDS] + 1;
     return b->h_summary[S_BAD] ? RAFI_ERR_BAD_DEST : RAFI_OK;

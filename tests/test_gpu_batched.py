@@ -118,3 +118,49 @@ def test_batched_256_scenes(orc, tmp_path, monkeypatch):
         ok, i, r = rel_close(img[base + ids], o["image"], RTOL, ATOL)
         assert ok, (s, i, r)
     b.close()
+
+
+@pytest.mark.parametrize("n_scenes", [1, 63, 65, 4097])
+def test_batched_scene_search(n_scenes):
+    """Scene and domain counts around the steps of the 64-probe search, scenes
+    smaller than a wavefront, rays that all miss: the plain renders' bits."""
+    dev = device()
+    specs, vols, scenes = _small_batch(dev)
+    tiny = []
+    for i, (n, grid, view, off) in enumerate(scenes):
+        view = view.copy()
+        view["width"], view["height"] = 1 + i % 5, 1 + i // 3   # 1 to 20 rays
+        if i == 7:
+            view["n_samples"] = 0
+        tiny.append((n, grid, view, off))
+    plain, plain_rounds = _plain_images(vols, tiny)
+    sizes = [int(v["width"]) * int(v["height"]) for _, _, v, _ in tiny]
+    whole, rest = divmod(n_scenes, len(tiny))
+    want = torch.cat([plain] * whole + [plain[:sum(sizes[:rest])]])
+    announce(f"batched scene search {n_scenes}")
+    b = rafi.Batch([tiny[i % len(tiny)] for i in range(n_scenes)], c=C32)
+    image = torch.full((b.n_rays,), -7.0, dtype=torch.float32, device=dev)
+    for _ in range(2):
+        rounds = b.render(vols, image)
+        torch.cuda.synchronize()
+        assert torch.equal(image, want)
+        assert rounds == plain_rounds or n_scenes < len(tiny)
+    b.close()
+
+
+def test_batched_round_limit():
+    """The limit counts the round that finds nothing left, as before: one round
+    too few is refused, and the render after it is whole."""
+    dev = device()
+    _, vols, scenes = _small_batch(dev)
+    b = rafi.Batch(scenes, c=C32)
+    image = torch.empty(b.n_rays, dtype=torch.float32, device=dev)
+    rounds = b.render(vols, image)
+    want = image.clone()
+    with pytest.raises(Exception):
+        b.render(vols, image, max_rounds=rounds - 1)
+    image.fill_(-7.0)
+    b.render(vols, image, max_rounds=rounds)
+    torch.cuda.synchronize()
+    assert torch.equal(image, want)
+    b.close()
