@@ -58,6 +58,10 @@ struct SplitPlan {
     // tiles of its column (u16). 0: a column per tile.
     uint32_t group_bits = 0;
     uint32_t n_cols = 0;  // table columns
+    // The scatter finds its run bases and the results itself, without a scan:
+    // from the unscanned table, or from the destinations without a histogram.
+    // 0: off.
+    uint32_t self = 0;
 };
 
 // allow_lock: the plan may use the lockstep scatter (its workspace grows by
@@ -68,7 +72,7 @@ int split_set_variant(int v);
 // A plan whose workspace covers every n <= cap.
 SplitPlan split_plan_bound(uint64_t cap, int32_t D, uint32_t S);
 
-// Where a split's scan leaves its results for the host (pinned memory), before
+// Where a split leaves its results for the host (pinned memory), before or while
 // the scatter runs: the five summary words, then `seq` (nonzero) at words[7]
 // once they and, with offsets set, the D + 1 offsets are written.
 struct HostOut {
@@ -149,7 +153,7 @@ void prof_domain_end(rafi_ctx *ctx, int h);
 // stream (wait), or only those already complete, in order.
 int prof_resolve(rafi_ctx *ctx, bool wait);
 // The two halves of rafi_round: enqueue the split of the current output slots,
-// whose scan writes its results to pinned memory (want_counts: the offsets
+// which writes its results to pinned memory (want_counts: the offsets
 // too); then wait for them and take them (queue length, statistics; counts,
 // optional: items per domain). The wait ends before the scatter does: what is
 // enqueued next on the stream follows it. round_finish does not touch the

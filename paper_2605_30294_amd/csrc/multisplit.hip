@@ -7,7 +7,7 @@
 // with RAFI_DONE leave, slots with any other out-of-range value are dropped;
 // both are counted. The paper reaches the same placement with a radix sort of
 // (dest << 32 | i) keys, a gather and a begin/end tally; here it is three
-// HBM-streaming passes:
+// HBM-streaming passes (the second, for few destinations, inside the third):
 //
 //   1. hist    per tile of T slots, a destination histogram (LDS atomics),
 //              written destination-major: table[e * n_tiles + tile].
@@ -43,9 +43,17 @@ using dev::load_nt4;
 using dev::match_peers;
 
 // ---------------------------------------------------------------- pass 1 ---
+// Where the count of destination e in column c of a table is: at
+// e * row + c * col, destination-major for the scans (col = 1), or column by
+// column for the scatter that sums the columns itself (row = 1).
+struct TableLayout {
+    uint32_t row, col;
+    __device__ uint64_t at(uint32_t e, uint32_t c) const { return (uint64_t)e * row + (uint64_t)c * col; }
+};
+
 // Destination histogram of tile blockIdx.x into column blockIdx.x of table.
 __device__ inline void hist_tile(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint32_t T,
-                                 uint32_t n_tiles, uint32_t *__restrict__ table, uint32_t *h)
+                                 TableLayout layout, uint32_t *__restrict__ table, uint32_t *h)
 {
     const uint32_t rows = (uint32_t)D + 2u;
     for (uint32_t e = threadIdx.x; e < rows; e += blockDim.x) h[e] = 0;
@@ -79,16 +87,15 @@ __device__ inline void hist_tile(const int32_t *__restrict__ dest, uint64_t n, i
     }
     for (uint64_t j = vend + threadIdx.x; j < end; j += blockDim.x) atomicAdd(&h[bucket_of(dest[j], D)], 1u);
     __syncthreads();
-    for (uint32_t e = threadIdx.x; e < rows; e += blockDim.x)
-        table[(uint64_t)e * n_tiles + blockIdx.x] = h[e];
+    for (uint32_t e = threadIdx.x; e < rows; e += blockDim.x) table[layout.at(e, blockIdx.x)] = h[e];
 }
 
 __global__ void __launch_bounds__(256)
-hist_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint32_t T, uint32_t n_tiles,
+hist_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint32_t T, TableLayout layout,
             uint32_t *__restrict__ table)
 {
     extern __shared__ uint32_t h[];  // D + 2
-    hist_tile(dest, n, D, T, n_tiles, table, h);
+    hist_tile(dest, n, D, T, layout, table, h);
 }
 
 // Lockstep plans: tiles of kLockTile chunks of kLockChunk slots. Besides the
@@ -263,22 +270,29 @@ scan_apply_direct_kernel(uint32_t *__restrict__ a, uint64_t M, const uint32_t *_
 // Offsets, summary and the tile table for domain-pure launches, from the
 // scanned table; with `dropped`, its count goes to summary[4] and is reset
 // (the domain kernels that add to it have completed).
-template <int NT>
-__device__ inline void finalize_body(const uint32_t *__restrict__ table, uint32_t n_tiles, int32_t D, uint64_t n,
-                                     uint64_t *__restrict__ offsets, uint64_t *__restrict__ summary,
-                                     uint32_t *__restrict__ tile_offsets, uint32_t tile_items,
-                                     unsigned long long *__restrict__ dropped, const HostOut &host, uint32_t *lds)
+struct Results {
+    uint64_t *offsets, *summary;
+    uint32_t *tile_offsets;
+    uint32_t tile_items;
+    unsigned long long *dropped;
+    HostOut host;
+};
+
+template <int NT, typename RowStart>
+__device__ inline void finalize_body(RowStart row_start, int32_t D, uint64_t n, const Results &to, uint32_t *lds)
 {
-    auto row_start = [&](int32_t e) -> uint64_t {
-        return n_tiles ? (uint64_t)table[(uint64_t)e * n_tiles] : 0ull;
-    };
+    uint64_t *__restrict__ offsets = to.offsets, *__restrict__ summary = to.summary;
+    uint32_t *__restrict__ tile_offsets = to.tile_offsets;
+    const uint32_t tile_items = to.tile_items;
+    unsigned long long *__restrict__ dropped = to.dropped;
+    const HostOut &host = to.host;
     for (int32_t e = threadIdx.x; e <= D; e += NT) {
         const uint64_t o = row_start(e);
         offsets[e] = o;
         if (host.offsets) host.offsets[e] = o;
     }
     const uint64_t total = row_start(D);
-    const uint64_t done_end = n_tiles ? row_start(D + 1) : 0ull;
+    const uint64_t done_end = row_start(D + 1);
     // per-domain tile counts, scanned (each thread owns a contiguous run)
     const int32_t per = (D + NT - 1) / NT;
     const int32_t e0 = threadIdx.x * per;
@@ -324,13 +338,11 @@ __device__ inline void finalize_body(const uint32_t *__restrict__ table, uint32_
 }
 
 __global__ void __launch_bounds__(1024)
-finalize_kernel(const uint32_t *__restrict__ table, uint32_t n_tiles, int32_t D, uint64_t n,
-                uint64_t *__restrict__ offsets, uint64_t *__restrict__ summary,
-                uint32_t *__restrict__ tile_offsets, uint32_t tile_items, unsigned long long *__restrict__ dropped,
-                HostOut host)
+finalize_kernel(const uint32_t *__restrict__ table, uint32_t n_cols, int32_t D, uint64_t n, Results to)
 {
     __shared__ uint32_t lds[1024 / 64 + 1];
-    finalize_body<1024>(table, n_tiles, D, n, offsets, summary, tile_offsets, tile_items, dropped, host, lds);
+    finalize_body<1024>(
+        [&](int32_t e) { return n_cols ? (uint64_t)table[(uint64_t)e * n_cols] : 0ull; }, D, n, to, lds);
 }
 
 // Exclusive scan of table[0, M) in place by one workgroup of 1024 threads,
@@ -363,13 +375,11 @@ __device__ inline void scan_steps(uint32_t *table, uint64_t M, uint32_t *lds)
 constexpr uint64_t kOneScanMax = 1ull << 15;
 
 __global__ void __launch_bounds__(1024)
-scan_one_kernel(uint32_t *__restrict__ table, uint64_t M, uint32_t n_cols, int32_t D, uint64_t n,
-                uint64_t *__restrict__ offsets, uint64_t *__restrict__ summary, uint32_t *__restrict__ tile_offsets,
-                uint32_t tile_items, unsigned long long *__restrict__ dropped, HostOut host)
+scan_one_kernel(uint32_t *__restrict__ table, uint64_t M, uint32_t n_cols, int32_t D, uint64_t n, Results to)
 {
     __shared__ uint32_t lds[1024 / 64 + 1];
     scan_steps(table, M, lds);
-    finalize_body<1024>(table, n_cols, D, n, offsets, summary, tile_offsets, tile_items, dropped, host, lds);
+    finalize_body<1024>([&](int32_t e) { return (uint64_t)table[(uint64_t)e * n_cols]; }, D, n, to, lds);
 }
 
 // True in exactly one workgroup of the launch: the last to get here. Each
@@ -419,17 +429,14 @@ constexpr uint32_t kFusedMaxTiles = 512;  // workgroups, each with its own fence
 
 __global__ void __launch_bounds__(256)
 hist_scan_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint32_t T, uint32_t n_tiles,
-                 uint32_t *__restrict__ table, uint64_t M, uint32_t *__restrict__ counter,
-                 uint64_t *__restrict__ offsets, uint64_t *__restrict__ summary,
-                 uint32_t *__restrict__ tile_offsets, uint32_t tile_items, unsigned long long *__restrict__ dropped,
-                 HostOut host)
+                 uint32_t *__restrict__ table, uint64_t M, uint32_t *__restrict__ counter, Results to)
 {
     extern __shared__ uint32_t h[];  // D + 2
     __shared__ uint32_t lds[256 / 64 + 1];
-    hist_tile(dest, n, D, T, n_tiles, table, h);
+    hist_tile(dest, n, D, T, TableLayout{n_tiles, 1}, table, h);
     if (!last_workgroup(counter, n_tiles)) return;
     block_scan_inplace<256>(table, M, lds);
-    finalize_body<256>(table, n_tiles, D, n, offsets, summary, tile_offsets, tile_items, dropped, host, lds);
+    finalize_body<256>([&](int32_t e) { return (uint64_t)table[(uint64_t)e * n_tiles]; }, D, n, to, lds);
 }
 
 // ------------------------------------------------------ grouped pass 1 ---
@@ -444,7 +451,7 @@ constexpr uint32_t kGroupBits = 2, kGroupTiles = 1u << kGroupBits;
 
 __global__ void __launch_bounds__(64 * kGroupTiles)
 hist_group_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint32_t T, uint32_t n_tiles,
-                  uint32_t n_cols, uint32_t *__restrict__ table, uint16_t *__restrict__ pre)
+                  TableLayout layout, uint32_t *__restrict__ table, uint16_t *__restrict__ pre)
 {
     extern __shared__ uint32_t h[];  // [kGroupTiles][D + 2]
     const uint32_t rows = (uint32_t)D + 2u, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -478,23 +485,152 @@ hist_group_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint3
             if (e < (uint32_t)D && first + q < n_tiles) pre[(uint64_t)(first + q) * (uint32_t)D + e] = (uint16_t)run;
             run += h[q * rows + e];
         }
-        table[(uint64_t)e * n_cols + blockIdx.x] = run;
+        table[layout.at(e, blockIdx.x)] = run;
     }
 }
 
 // ---------------------------------------------------------------- pass 3 ---
 // Output slot of a tile's first item bound for e, from the scanned table and,
-// where a column stands for several tiles, the tile's prefix inside it.
+// where a column stands for several tiles, the tile's prefix inside it. With
+// self set, the scatter's workgroups find it themselves (self_base), from the
+// unscanned table, column by column (kSumTable), or from the destinations
+// (kCountSlots); workgroup 0 then has no tile and writes the results
+// (self_results).
 struct RunBases {
     const uint32_t *__restrict__ table;
     const uint16_t *__restrict__ pre;
-    uint32_t n_cols, group_bits;
+    uint32_t n_cols, group_bits, self;
+    __device__ uint32_t in_group(uint32_t tile, int32_t e, int32_t D) const
+    {
+        return group_bits ? pre[(uint64_t)tile * (uint32_t)D + (uint32_t)e] : 0u;
+    }
     __device__ uint32_t at(uint32_t tile, int32_t e, int32_t D) const
     {
-        const uint32_t base = table[(uint64_t)e * n_cols + (tile >> group_bits)];
-        return group_bits ? base + pre[(uint64_t)tile * (uint32_t)D + (uint32_t)e] : base;
+        return table[(uint64_t)e * n_cols + (tile >> group_bits)] + in_group(tile, e, D);
     }
 };
+
+// Sums of the first `rows` counts over all columns and over those before col,
+// for row threadIdx.x, by a workgroup of NT threads: up to 16 threads share a
+// row, 16 loads in flight each. scratch: 2 NT words.
+constexpr int kSelfD = 128;                                  // destinations at most
+constexpr size_t kSelfLds = (2 * 256 + kSelfD + 2 + 8) * 4;  // bytes of LDS for 256 threads
+
+template <int NT>
+__device__ inline void sum_columns(const RunBases &b, uint32_t col, uint32_t rows, uint32_t stride, uint32_t *scratch,
+                                   uint32_t &all, uint32_t &before)
+{
+    uint32_t lg = 0;
+    while ((1u << lg) < rows) ++lg;
+    const uint32_t parts = min((uint32_t)NT >> lg, 16u), e = threadIdx.x & ((1u << lg) - 1), part = threadIdx.x >> lg;
+    all = before = 0;
+    if (e < rows && part < parts) {
+        for (uint32_t c0 = part; c0 < b.n_cols; c0 += 16 * parts) {
+            uint32_t v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const uint32_t c = c0 + u * parts;
+                v[u] = c < b.n_cols ? b.table[(uint64_t)c * stride + e] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                all += v[u];
+                before += c0 + u * parts < col ? v[u] : 0u;
+            }
+        }
+    }
+    scratch[threadIdx.x] = all;
+    scratch[NT + threadIdx.x] = before;
+    __syncthreads();
+    if (threadIdx.x < rows)
+        for (uint32_t q = 1; q < parts; ++q) {
+            all += scratch[(q << lg) + threadIdx.x];
+            before += scratch[NT + (q << lg) + threadIdx.x];
+        }
+    __syncthreads();
+}
+
+// The same from the destinations of all n slots, of which those before `mid` (a
+// multiple of 4) count as before. Runs of four equal destinations are added
+// at once.
+template <int NT>
+__device__ inline void count_slots(const int32_t *__restrict__ dest, uint64_t n, uint64_t mid, int32_t D,
+                                   uint32_t *scratch, uint32_t &all, uint32_t &before)
+{
+    const uint32_t rows = (uint32_t)D + 2u;
+    uint32_t *h0 = scratch, *h1 = scratch + rows;
+    for (uint32_t e = threadIdx.x; e < 2 * rows; e += NT) scratch[e] = 0;
+    __syncthreads();
+    constexpr int kU = 4;
+    for (uint64_t i0 = 4ull * threadIdx.x; i0 < n; i0 += kU * 4ull * NT) {
+        uint4 d[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint64_t i = i0 + u * 4ull * NT;
+            d[u] = i + 4 <= n ? *reinterpret_cast<const uint4 *>(dest + i) : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint64_t i = i0 + u * 4ull * NT;
+            uint32_t *h = i < mid ? h0 : h1;
+            if (i + 4 <= n) {
+                const uint32_t x = bucket_of((int32_t)d[u].x, D), y = bucket_of((int32_t)d[u].y, D),
+                               z = bucket_of((int32_t)d[u].z, D), w = bucket_of((int32_t)d[u].w, D);
+                if (x == y && x == z && x == w) {
+                    atomicAdd(&h[x], 4u);
+                } else {
+                    atomicAdd(&h[x], 1u);
+                    atomicAdd(&h[y], 1u);
+                    atomicAdd(&h[z], 1u);
+                    atomicAdd(&h[w], 1u);
+                }
+            } else {
+                for (uint64_t j = i; j < n; ++j) atomicAdd(&h[bucket_of(dest[j], D)], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    before = threadIdx.x < rows ? h0[threadIdx.x] : 0u;
+    all = threadIdx.x < rows ? before + h1[threadIdx.x] : 0u;
+    __syncthreads();
+}
+
+enum : uint32_t { kSumTable = 1, kCountSlots = 2 };
+
+// RunBases::at(tile, e) of destination e = threadIdx.x, for tiles of T slots.
+// scratch is free again on return.
+template <int NT>
+__device__ inline uint32_t self_base(const RunBases &b, const int32_t *__restrict__ dest, uint64_t n, uint32_t tile,
+                                     uint32_t T, int32_t D, uint32_t *scratch)
+{
+    static_assert(NT >= kSelfD + 2, "a thread per row");
+    uint32_t all, before, total;
+    if (b.self == kCountSlots)
+        count_slots<NT>(dest, n, (uint64_t)tile * T, D, scratch, all, before);
+    else
+        sum_columns<NT>(b, tile >> b.group_bits, (uint32_t)D, (uint32_t)D + 2u, scratch, all, before);
+    const bool own = (int32_t)threadIdx.x < D;
+    const uint32_t start = block_excl_scan<NT>(own ? all : 0u, scratch, &total);  // ends with a barrier
+    return own ? start + before + b.in_group(tile, (int32_t)threadIdx.x, D) : 0u;
+}
+
+// Offsets and summary.
+template <int NT>
+__device__ inline void self_results(const RunBases &b, const int32_t *__restrict__ dest, int32_t D, uint64_t n,
+                                    const Results &to, uint32_t *scratch)
+{
+    const uint32_t rows = (uint32_t)D + 2u;
+    uint32_t all, before, total;
+    if (b.self == kCountSlots)
+        count_slots<NT>(dest, n, 0, D, scratch, all, before);
+    else
+        sum_columns<NT>(b, 0, rows, rows, scratch, all, before);
+    uint32_t *starts = scratch + 2 * NT;
+    const uint32_t start = block_excl_scan<NT>(threadIdx.x < rows ? all : 0u, scratch, &total);
+    if (threadIdx.x < rows) starts[threadIdx.x] = start;
+    __syncthreads();
+    finalize_body<NT>([&](int32_t e) { return (uint64_t)starts[e]; }, D, n, to, scratch);
+}
 
 template <int NW>
 __device__ inline void copy_item(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst)
@@ -518,12 +654,22 @@ __device__ inline void copy_item(const uint32_t *__restrict__ src, uint32_t *__r
 template <int NW>
 __global__ void __launch_bounds__(256)
 scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest, uint64_t n,
-               int32_t D, int nbits, uint32_t T, RunBases bases, uint32_t *__restrict__ out, uint32_t nw_runtime)
+               int32_t D, int nbits, uint32_t T, RunBases bases, uint32_t *__restrict__ out, uint32_t nw_runtime,
+               Results results)
 {
     extern __shared__ uint32_t cnt[];  // [4][D]
     const uint32_t nw = NW > 0 ? (uint32_t)NW : nw_runtime;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    const uint64_t start = (uint64_t)blockIdx.x * T;
+    uint32_t tile = blockIdx.x, own_base = 0;
+    if (bases.self) {
+        if (tile == 0) {
+            self_results<256>(bases, dest, D, n, results, cnt);
+            return;
+        }
+        --tile;
+        own_base = self_base<256>(bases, dest, n, tile, T, D, cnt);
+    }
+    const uint64_t start = (uint64_t)tile * T;
     const uint64_t end = min(start + T, n);
     const uint64_t q = T / 4;
     const uint64_t wstart = min(start + w * q, end), wend = min(wstart + q, end);
@@ -537,7 +683,7 @@ scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ d
     }
     __syncthreads();
     for (int32_t e = tid; e < D; e += 256) {
-        uint32_t run = bases.at(blockIdx.x, e, D);
+        uint32_t run = bases.self ? own_base : bases.at(tile, e, D);  // self: D <= 128, so e is tid
 #pragma unroll
         for (int ww = 0; ww < 4; ++ww) {
             const uint32_t c = cnt[ww * D + e];
@@ -575,29 +721,41 @@ scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ d
 template <int NW, int R, int W, int OCC, bool DB>
 __global__ void __launch_bounds__(64 * W, OCC)
 scatter_staged_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest, uint64_t n,
-                      int32_t D, int nbits, uint32_t T, RunBases bases, uint32_t *__restrict__ out)
+                      int32_t D, int nbits, uint32_t T, RunBases bases, uint32_t *__restrict__ out, Results results)
 {
     extern __shared__ __align__(16) uint32_t lds[];
-    const uint64_t tstart = (uint64_t)blockIdx.x * T;
+    uint32_t tile = blockIdx.x, own_base = 0;
+    if constexpr (W == 4) {
+        if (bases.self) {
+            if (tile == 0) {
+                self_results<256>(bases, dest, D, n, results, lds);
+                return;
+            }
+            --tile;
+            own_base = self_base<256>(bases, dest, n, tile, T, D, lds);
+        }
+    }
+    const uint64_t tstart = (uint64_t)tile * T;
     const uint64_t tend = min(tstart + T, n);
-    const uint32_t tile = blockIdx.x;
     dev::staged_scatter_tile<NW, R, W, DB>(
-        items, dest, tstart, tend, D, 0, nbits, [&](int32_t e) { return bases.at(tile, e, D); }, out, n, lds);
+        items, dest, tstart, tend, D, 0, nbits,
+        [&](int32_t e) { return W == 4 && bases.self ? own_base : bases.at(tile, e, D); }, out, n, lds);
 }
 
 // One (rounds, waves, workgroups per CU) shape of the staged scatter; it is
 // launched only if its LDS fits that many workgroups per CU.
 template <int NW, int R, int W, int BPC, bool DB = false>
 bool try_staged(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const RunBases &bases,
-                uint32_t *out, hipStream_t s)
+                uint32_t *out, hipStream_t s, const Results &results)
 {
     const size_t lds = dev::staged_lds_bytes<NW, R, W>(p.D) + 64;
     if (p.D > dev::kStagedMaxD || lds * BPC > dev::kStagedLdsPerCu) return false;
+    if (p.self && (W != 4 || lds < kSelfLds)) return false;
     int nbits = 1;
     while ((1 << nbits) < p.D) ++nbits;
     constexpr int OCC = (W * BPC + 3) / 4;  // waves per SIMD
-    hipLaunchKernelGGL((scatter_staged_kernel<NW, R, W, OCC, DB>), dim3(p.n_tiles), dim3(64 * W), lds, s, items, dest,
-                       p.n, p.D, nbits, p.tile, bases, out);
+    hipLaunchKernelGGL((scatter_staged_kernel<NW, R, W, OCC, DB>), dim3(p.n_tiles + (p.self ? 1 : 0)), dim3(64 * W), lds, s,
+                       items, dest, p.n, p.D, nbits, p.tile, bases, out, results);
     return true;
 }
 
@@ -794,12 +952,12 @@ int g_split_variant = 0;
 
 template <int NW>
 bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const RunBases &bases,
-                   uint32_t *out, uint32_t *dummy, hipStream_t s)
+                   uint32_t *out, uint32_t *dummy, hipStream_t s, const Results &results)
 {
     const uint32_t *table = bases.table;
-    // a grouped plan (made for the automatic choice) takes only shapes that
-    // read their run bases through `bases`
-    int v = p.group_bits ? 0 : g_split_variant;
+    // a plan with grouped tiles or an unscanned table (made for the automatic
+    // choice) takes only shapes that read their run bases through `bases`
+    int v = p.group_bits || p.self ? 0 : g_split_variant;
     if constexpr (NW >= 11) {
         // automatic: items of 44 bytes and more, few destinations and at most
         // 64 MiB: the plain per-thread scatter (each wave's run of a
@@ -816,7 +974,7 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
     if constexpr (NW % 4 != 0 && NW >= 3 && NW <= 15) {
         // item sizes that are not a multiple of 16 bytes: raw staging, one
         // workgroup per CU (automatic when a tile fills a 2048-slot chunk)
-        if ((v == 16 || (v == 0 && p.tile >= 8 * 64 * 4)) &&
+        if ((v == 16 || (v == 0 && p.tile >= 8 * 64 * 4 && !p.self)) &&
             try_wide_raw<NW, 4, 8>(p, items, dest, bases, out, dummy, s))
             return true;
     }
@@ -852,9 +1010,9 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
         // when a tile fills at least one of its chunks
         if (p.D <= 128 && p.n * (uint64_t)p.S <= (1ull << 28)) {
             if constexpr (NW == 8) {
-                if (try_staged<8, 4, 4, 3>(p, items, dest, bases, out, s)) return true;
+                if (try_staged<8, 4, 4, 3>(p, items, dest, bases, out, s, results)) return true;
             } else if constexpr (NW == 4) {
-                if (try_staged<4, 4, 4, 4>(p, items, dest, bases, out, s)) return true;
+                if (try_staged<4, 4, 4, 4>(p, items, dest, bases, out, s, results)) return true;
             }
         }
         if (line_spans_tiles(p)) {
@@ -872,15 +1030,15 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
     }
     if (v >= 8) {  // shapes 1-4 with double-buffered chunk loads
         if constexpr (NW == 8) {
-            if (v == 8) return try_staged<8, 7, 4, 2, true>(p, items, dest, bases, out, s);
-            if (v == 9) return try_staged<8, 4, 4, 3, true>(p, items, dest, bases, out, s);
-            if (v == 10) return try_staged<8, 3, 8, 2, true>(p, items, dest, bases, out, s);
-            if (v == 11) return try_staged<8, 2, 4, 4, true>(p, items, dest, bases, out, s);
+            if (v == 8) return try_staged<8, 7, 4, 2, true>(p, items, dest, bases, out, s, results);
+            if (v == 9) return try_staged<8, 4, 4, 3, true>(p, items, dest, bases, out, s, results);
+            if (v == 10) return try_staged<8, 3, 8, 2, true>(p, items, dest, bases, out, s, results);
+            if (v == 11) return try_staged<8, 2, 4, 4, true>(p, items, dest, bases, out, s, results);
         } else if constexpr (NW == 4) {
-            if (v == 8) return try_staged<4, 12, 4, 2, true>(p, items, dest, bases, out, s);
-            if (v == 9) return try_staged<4, 8, 4, 3, true>(p, items, dest, bases, out, s);
-            if (v == 10) return try_staged<4, 5, 8, 2, true>(p, items, dest, bases, out, s);
-            if (v == 11) return try_staged<4, 4, 4, 4, true>(p, items, dest, bases, out, s);
+            if (v == 8) return try_staged<4, 12, 4, 2, true>(p, items, dest, bases, out, s, results);
+            if (v == 9) return try_staged<4, 8, 4, 3, true>(p, items, dest, bases, out, s, results);
+            if (v == 10) return try_staged<4, 5, 8, 2, true>(p, items, dest, bases, out, s, results);
+            if (v == 11) return try_staged<4, 4, 4, 4, true>(p, items, dest, bases, out, s, results);
         }
         return false;
     }
@@ -891,21 +1049,21 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
         return false;
     }
     if constexpr (NW == 8) {
-        if ((v == 0 || v == 1) && try_staged<8, 7, 4, 2>(p, items, dest, bases, out, s)) return true;
-        if ((v == 0 || v == 2) && try_staged<8, 4, 4, 3>(p, items, dest, bases, out, s)) return true;
-        if ((v == 0 || v == 3) && try_staged<8, 3, 8, 2>(p, items, dest, bases, out, s)) return true;
-        if ((v == 0 || v == 4) && try_staged<8, 2, 4, 4>(p, items, dest, bases, out, s)) return true;
+        if ((v == 0 || v == 1) && try_staged<8, 7, 4, 2>(p, items, dest, bases, out, s, results)) return true;
+        if ((v == 0 || v == 2) && try_staged<8, 4, 4, 3>(p, items, dest, bases, out, s, results)) return true;
+        if ((v == 0 || v == 3) && try_staged<8, 3, 8, 2>(p, items, dest, bases, out, s, results)) return true;
+        if ((v == 0 || v == 4) && try_staged<8, 2, 4, 4>(p, items, dest, bases, out, s, results)) return true;
         return false;
     } else if constexpr (NW == 4) {
-        if ((v == 0 || v == 1) && try_staged<4, 12, 4, 2>(p, items, dest, bases, out, s)) return true;
-        if ((v == 0 || v == 2) && try_staged<4, 8, 4, 3>(p, items, dest, bases, out, s)) return true;
-        if ((v == 0 || v == 3) && try_staged<4, 5, 8, 2>(p, items, dest, bases, out, s)) return true;
-        if ((v == 0 || v == 4) && try_staged<4, 4, 4, 4>(p, items, dest, bases, out, s)) return true;
+        if ((v == 0 || v == 1) && try_staged<4, 12, 4, 2>(p, items, dest, bases, out, s, results)) return true;
+        if ((v == 0 || v == 2) && try_staged<4, 8, 4, 3>(p, items, dest, bases, out, s, results)) return true;
+        if ((v == 0 || v == 3) && try_staged<4, 5, 8, 2>(p, items, dest, bases, out, s, results)) return true;
+        if ((v == 0 || v == 4) && try_staged<4, 4, 4, 4>(p, items, dest, bases, out, s, results)) return true;
         return false;
     } else if constexpr (NW <= 3) {
-        return try_staged<NW, 16, 4, 2>(p, items, dest, bases, out, s);
+        return try_staged<NW, 16, 4, 2>(p, items, dest, bases, out, s, results);
     } else if constexpr (56 / NW > 0) {
-        return try_staged<NW, 56 / NW, 4, 2>(p, items, dest, bases, out, s);
+        return try_staged<NW, 56 / NW, 4, 2>(p, items, dest, bases, out, s, results);
     } else {
         return false;
     }
@@ -913,16 +1071,16 @@ bool launch_staged(const SplitPlan &p, const uint32_t *items, const int32_t *des
 
 template <int NW>
 void launch_scatter(const SplitPlan &p, const uint32_t *items, const int32_t *dest, const RunBases &bases,
-                    uint32_t *out, uint32_t *dummy, hipStream_t s)
+                    uint32_t *out, uint32_t *dummy, hipStream_t s, const Results &results)
 {
     if constexpr (NW > 0) {
-        if (launch_staged<NW>(p, items, dest, bases, out, dummy, s)) return;
+        if (launch_staged<NW>(p, items, dest, bases, out, dummy, s, results)) return;
     }
     int nbits = 1;
     while ((1 << nbits) < p.D) ++nbits;
-    const size_t lds = sizeof(uint32_t) * 4 * (size_t)p.D;
-    hipLaunchKernelGGL(scatter_kernel<NW>, dim3(p.n_tiles), dim3(256), lds, s, items, dest, p.n,
-                       p.D, nbits, p.tile, bases, out, p.S / 4);
+    const size_t lds = std::max(sizeof(uint32_t) * 4 * (size_t)p.D, p.self ? kSelfLds : 0);
+    hipLaunchKernelGGL(scatter_kernel<NW>, dim3(p.n_tiles + (p.self ? 1 : 0)), dim3(256), lds, s, items, dest, p.n,
+                       p.D, nbits, p.tile, bases, out, p.S / 4, results);
 }
 
 }  // namespace
@@ -964,6 +1122,41 @@ bool group_eligible(const SplitPlan &p)
 {
     return g_split_variant == 0 && p.D <= 128 && p.n * (uint64_t)p.S <= (1ull << 28) &&
            ((uint64_t)p.D + 2) * p.n_tiles > kOneScanMax && (uint64_t)p.tile * (kGroupTiles - 1) < 65536;
+}
+
+// Whether the scatter's workgroups find their run bases and the results
+// themselves. A round of few slots is a chain of launches, each some 5 us for
+// little work, and the scan is one workgroup. The shapes are those of the
+// grouped plans, with tiles below the raw shape's chunk.
+//   up to kCountTiles tiles every workgroup counts all destinations, and the
+//     split is one launch: 4 K slots 12.2 us, 15.5 with a histogram launch,
+//     19.0 with histogram and scan; at 16 tiles the count costs what the
+//     launch does;
+//   else every workgroup sums the table's columns: 64 domains, histogram and
+//     scatter of 584 K slots 6 + 14 us for 6 + 12 with a scan of 8 between.
+//     Columns stand for 4 tiles from kSelfPlain entries on (460 K slots 18 us
+//     for 24, 142 K the same, 84 K 15 for 14);
+//   not when the workgroups together read more than kSelfReads entries (1 M
+//     slots, 64 destinations: 18.4 us for 20.3, and twice the slots read four
+//     times as much).
+constexpr uint32_t kCountTiles = 8;
+constexpr uint64_t kSelfPlain = 1ull << 13, kSelfMax = 1ull << 15, kSelfReads = 1ull << 24;
+
+void finish_self_plan(SplitPlan &p)
+{
+    if (g_split_variant != 0 || p.D > kSelfD || p.n * (uint64_t)p.S > (1ull << 28) || p.tile >= 8 * 64 * 4 ||
+        p.n_tiles == 0)
+        return;
+    if (p.n_tiles <= kCountTiles) {
+        p.self = kCountSlots;
+        return;
+    }
+    SplitPlan c = p;
+    c.group_bits = c.rows * c.n_tiles > kSelfPlain ? kGroupBits : 0;
+    finish_plan(c);
+    if (c.M > kSelfMax || c.M * c.n_tiles > kSelfReads) return;
+    p = c;
+    p.self = kSumTable;
 }
 
 // The lockstep scatter takes items that are not whole 16-byte pieces (the
@@ -1016,6 +1209,7 @@ SplitPlan split_plan(uint64_t n, int32_t D, uint32_t S, bool allow_lock)
     p.n_tiles = (uint32_t)((n + t - 1) / t);
     if (group_eligible(p)) p.group_bits = kGroupBits;
     finish_plan(p);
+    finish_self_plan(p);
     return p;
 }
 
@@ -1047,31 +1241,32 @@ int split_run(const SplitPlan &p, const void *items, const int32_t *dest, void *
     uint32_t *dummy = reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + p.off_dummy);
     uint32_t *counters = reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + p.off_done);
     uint16_t *pre = reinterpret_cast<uint16_t *>(static_cast<char *>(workspace) + p.off_pre);
-    const uint32_t ti = tile_items ? tile_items : 1u;
+    const Results results{offsets, summary, tile_offsets, tile_items ? tile_items : 1u, dropped, host};
+    const TableLayout layout = p.self ? TableLayout{1, (uint32_t)p.rows} : TableLayout{p.n_cols, 1};
     // The fused launch costs one device-scope fence (an L2 write-back on this
     // multi-XCD part) per workgroup: worth it only for small tables.
-    if (p.n_tiles > 0 && fused && !p.lock && !p.group_bits && p.M <= kFusedMaxM && p.n_tiles <= kFusedMaxTiles) {
+    if (p.n_tiles > 0 && fused && !p.lock && !p.group_bits && !p.self && p.M <= kFusedMaxM && p.n_tiles <= kFusedMaxTiles) {
         hipLaunchKernelGGL(hist_scan_kernel, dim3(p.n_tiles), dim3(256), sizeof(uint32_t) * p.rows, s, dest, p.n,
-                           p.D, p.tile, p.n_tiles, table, p.M, counters, offsets, summary, tile_offsets, ti,
-                           dropped, host);
+                           p.D, p.tile, p.n_tiles, table, p.M, counters, results);
         RAFI_LAUNCH_CHECK();
     } else {
-        if (p.n_tiles > 0) {
+        if (p.n_tiles > 0 && p.self != kCountSlots) {
             if (p.lock)
                 hipLaunchKernelGGL(hist_lock_kernel, dim3(p.n_tiles), dim3(256), sizeof(uint32_t) * p.rows, s,
                                    dest, p.n, p.D, p.n_tiles, p.n_chunks, table, pre);
             else if (p.group_bits)
                 hipLaunchKernelGGL(hist_group_kernel, dim3(p.n_cols), dim3(64 * kGroupTiles),
                                    sizeof(uint32_t) * kGroupTiles * p.rows, s, dest, p.n, p.D, p.tile, p.n_tiles,
-                                   p.n_cols, table, pre);
+                                   layout, table, pre);
             else
                 hipLaunchKernelGGL(hist_kernel, dim3(p.n_tiles), dim3(256), sizeof(uint32_t) * p.rows, s,
-                                   dest, p.n, p.D, p.tile, p.n_tiles, table);
+                                   dest, p.n, p.D, p.tile, layout, table);
             RAFI_LAUNCH_CHECK();
         }
-        if (p.n_tiles > 0 && p.M <= kOneScanMax) {
-            hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(1024), 0, s, table, p.M, p.n_cols, p.D, p.n, offsets,
-                               summary, tile_offsets, ti, dropped, host);
+        if (p.self) {
+            // the scatter scans
+        } else if (p.n_tiles > 0 && p.M <= kOneScanMax) {
+            hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(1024), 0, s, table, p.M, p.n_cols, p.D, p.n, results);
             RAFI_LAUNCH_CHECK();
         } else {
             if (p.n_tiles > 0) {
@@ -1088,8 +1283,7 @@ int split_run(const SplitPlan &p, const void *items, const int32_t *dest, void *
                 }
                 RAFI_LAUNCH_CHECK();
             }
-            hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, s, table, p.n_cols, p.D, p.n, offsets,
-                               summary, tile_offsets, ti, dropped, host);
+            hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, s, table, p.n_cols, p.D, p.n, results);
             RAFI_LAUNCH_CHECK();
         }
     }
@@ -1100,19 +1294,19 @@ int split_run(const SplitPlan &p, const void *items, const int32_t *dest, void *
     }
     const uint32_t *it = static_cast<const uint32_t *>(items);
     uint32_t *o = static_cast<uint32_t *>(out);
-    const RunBases bases{table, pre, p.n_cols, p.group_bits};
+    const RunBases bases{table, pre, p.n_cols, p.group_bits, p.self};
     switch (p.S / 4) {
-    case 1: launch_scatter<1>(p, it, dest, bases, o, dummy, s); break;
-    case 2: launch_scatter<2>(p, it, dest, bases, o, dummy, s); break;
-    case 3: launch_scatter<3>(p, it, dest, bases, o, dummy, s); break;
-    case 4: launch_scatter<4>(p, it, dest, bases, o, dummy, s); break;
-    case 6: launch_scatter<6>(p, it, dest, bases, o, dummy, s); break;
-    case 8: launch_scatter<8>(p, it, dest, bases, o, dummy, s); break;
-    case 10: launch_scatter<10>(p, it, dest, bases, o, dummy, s); break;
-    case 11: launch_scatter<11>(p, it, dest, bases, o, dummy, s); break;
-    case 12: launch_scatter<12>(p, it, dest, bases, o, dummy, s); break;
-    case 16: launch_scatter<16>(p, it, dest, bases, o, dummy, s); break;
-    default: launch_scatter<0>(p, it, dest, bases, o, dummy, s); break;
+    case 1: launch_scatter<1>(p, it, dest, bases, o, dummy, s, results); break;
+    case 2: launch_scatter<2>(p, it, dest, bases, o, dummy, s, results); break;
+    case 3: launch_scatter<3>(p, it, dest, bases, o, dummy, s, results); break;
+    case 4: launch_scatter<4>(p, it, dest, bases, o, dummy, s, results); break;
+    case 6: launch_scatter<6>(p, it, dest, bases, o, dummy, s, results); break;
+    case 8: launch_scatter<8>(p, it, dest, bases, o, dummy, s, results); break;
+    case 10: launch_scatter<10>(p, it, dest, bases, o, dummy, s, results); break;
+    case 11: launch_scatter<11>(p, it, dest, bases, o, dummy, s, results); break;
+    case 12: launch_scatter<12>(p, it, dest, bases, o, dummy, s, results); break;
+    case 16: launch_scatter<16>(p, it, dest, bases, o, dummy, s, results); break;
+    default: launch_scatter<0>(p, it, dest, bases, o, dummy, s, results); break;
     }
     RAFI_LAUNCH_CHECK();
     if (ev) RAFI_HIP_CHECK(hipEventRecord(ev->end, s));

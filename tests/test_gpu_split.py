@@ -200,6 +200,32 @@ def test_split_grouped_histogram(orc, n, D, words):
     assert np.array_equal(out[:total].cpu().numpy(), e_out)
 
 
+@pytest.mark.parametrize("n,D,words", [
+    (1, 1, 4), (5, 2, 3), (1023, 64, 12), (8192, 64, 8), (8193, 64, 8), (8190, 128, 1), (8191, 129, 4),
+    (126_976, 64, 4), (126_977, 64, 4),            # 64 destinations: a column per tile, per 4 tiles
+    (1_019_905, 63, 12), (1_060_000, 64, 11),      # about the most a workgroup sums itself
+    (64_512, 128, 6), (300_001, 128, 2), (2_000_003, 3, 5), (4_194_304, 1, 1)])
+def test_split_without_scan(orc, n, D, words):
+    """Few destinations: the scatter's workgroups find their output slots from
+    the destinations (up to 8 tiles) or from the unscanned table; both sides of
+    each bound, every length of the last group of four slots, one destination,
+    long runs of one; stateless, and a context's rounds."""
+    for q in range(4):
+        if n - q > 0 and (q == 0 or n < 10_000):
+            _run_split(orc, n - q, D, words, seed=n + q + 31, dist="mixed")
+    _run_ctx_split(orc, n, D, words, seed=n + 32, dist="zipf")
+    dev = device()
+    rng = np.random.default_rng(n + 33)
+    dest = np.repeat(rng.integers(-1, D, n // 700 + 1).astype(np.int32), 700)[:n]
+    items = rng.integers(0, 2**31, (n, words)).astype(np.int32)
+    out, offsets, summary = rafi.multisplit(torch.from_numpy(items).to(dev), torch.from_numpy(dest).to(dev), D)
+    torch.cuda.synchronize()
+    e_out, _, e_off, e_done, _ = orc.multisplit(items, dest, D)
+    total = int(e_off[-1])
+    assert np.array_equal(offsets.cpu().numpy().astype(np.uint64), e_off) and int(summary[1]) == e_done
+    assert np.array_equal(out[:total].cpu().numpy(), e_out)
+
+
 def test_round_counts_through_pinned_memory(orc):
     """Per-domain counts and totals of consecutive rounds for the most domains
     a context takes: every round's results are its own, also when a round
