@@ -1,11 +1,9 @@
 // Host context: queue ownership, the device view and the forward step
 // (Sec. 3.4 of the paper: create a context, size its queues, hand kernels a
 // device interface, call forwardRays() between kernel launches).
-#include <chrono>
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <thread>
 
 #include "internal.h"
 
@@ -194,33 +192,9 @@ int round_enqueue(rafi_ctx *c, bool want_counts)
                      c->stream, evp, c->dropped, true, host);
 }
 
-namespace {
-// Waits until the scan of the last enqueued round has written its results.
-// The word is polled (a copy and an event cost each round a launch, 10 us);
-// after a second the stream is synchronised instead, which also reports a
-// failed launch.
-int wait_summary(rafi_ctx *c)
-{
-    const uint64_t *word = c->host_summary + 7;
-    auto arrived = [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == c->round_seq; };
-    const auto t0 = std::chrono::steady_clock::now();
-    for (uint32_t i = 1; !arrived(); ++i) {
-        __builtin_ia32_pause();
-        if (i % 256 != 0) continue;
-        const auto waited = std::chrono::steady_clock::now() - t0;
-        if (waited > std::chrono::seconds(1)) {
-            RAFI_HIP_CHECK(hipStreamSynchronize(c->stream));
-            return arrived() ? RAFI_OK : RAFI_ERR_HIP;
-        }
-        if (waited > std::chrono::microseconds(200)) std::this_thread::yield();
-    }
-    return RAFI_OK;
-}
-}  // namespace
-
 int round_finish(rafi_ctx *c, uint64_t *total, uint64_t *counts)
 {
-    const int wrc = wait_summary(c);
+    const int wrc = wait_host_word(c, 7, [&](uint64_t w) { return w == c->round_seq; });
     if (wrc != RAFI_OK) return wrc;
     const uint64_t *h = c->host_summary;
     if (counts)
@@ -335,7 +309,7 @@ int rafi_create(int32_t n_domains, uint32_t item_bytes, uint64_t capacity, rafi_
                        hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
          hipHostGetDevicePointer(reinterpret_cast<void **>(&c->host_summary_dev), c->host_summary, 0) != hipSuccess))
         rc = RAFI_ERR_OOM;
-    if (rc == RAFI_OK) c->host_summary[7] = 0;
+    if (rc == RAFI_OK) c->host_summary[7] = c->host_summary[kHostExtra] = 0;
     if (rc == RAFI_OK) rc = empty_queue(c);
     if (rc == RAFI_OK && hipStreamSynchronize(c->stream) != hipSuccess) rc = RAFI_ERR_HIP;
     if (rc != RAFI_OK) {

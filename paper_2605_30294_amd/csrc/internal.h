@@ -3,8 +3,10 @@
 
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cstdint>
 #include <cstdio>
+#include <thread>
 
 #include "rafi.h"
 
@@ -163,6 +165,32 @@ int round_finish(rafi_ctx *ctx, uint64_t *total, uint64_t *counts = nullptr);
 // Both halves and the refill of the slots in debug mode: rafi_round without
 // its synchronisation of the stream.
 int round_run(rafi_ctx *ctx, uint64_t *counts, uint64_t *total);
+
+// A word of host_summary free for what a step needs on the host besides its
+// rounds' results.
+constexpr int kHostExtra = 6;
+
+// Waits until a kernel on the context's stream has left a word that `arrived`
+// takes at host_summary[index]. The word is polled (a copy and an event cost
+// a launch, 10 us); after a second the stream is synchronised instead, which
+// also reports a failed launch.
+template <typename Arrived>
+int wait_host_word(rafi_ctx *c, int index, Arrived arrived)
+{
+    auto look = [&] { return arrived(__atomic_load_n(c->host_summary + index, __ATOMIC_ACQUIRE)); };
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint32_t i = 1; !look(); ++i) {
+        __builtin_ia32_pause();
+        if (i % 256 != 0) continue;
+        const auto waited = std::chrono::steady_clock::now() - t0;
+        if (waited > std::chrono::seconds(1)) {
+            RAFI_HIP_CHECK(hipStreamSynchronize(c->stream));
+            return look() ? RAFI_OK : RAFI_ERR_HIP;
+        }
+        if (waited > std::chrono::microseconds(200)) std::this_thread::yield();
+    }
+    return RAFI_OK;
+}
 
 // The round loop with the host one step ahead of the device. After a forward
 // step is enqueued, the next domain launch is enqueued at once as

@@ -158,9 +158,65 @@ T *at(void *ws, uint64_t off)
 }
 
 // ------------------------------------------------- exclusive scan, u32 ---
-// out[i] = sum of in[0..i); *total = the sum of all n. Blocks of kScanTile
-// elements scan locally, one block scans the block sums, a last pass adds
-// them. n < 2^32 and the sum fits 32 bits.
+// out[i] = sum of in[0..i); *total = the sum of all n; n < 2^32 and the sum
+// fits 32 bits. What else the last pass does, each optional: starts[out[i]] = i
+// where in[i] is set (flags; every out is then the index of a run), and the
+// total with `tag` in its upper half to a word of pinned memory.
+struct ScanExtra {
+    uint32_t *starts = nullptr;
+    uint64_t *host = nullptr;
+    uint32_t tag = 0;
+    __device__ void slot(uint32_t flag, uint32_t run, uint64_t i) const
+    {
+        if (starts && flag) starts[run] = (uint32_t)i;
+    }
+    __device__ void finish(uint32_t sum, uint32_t *total) const
+    {
+        *total = sum;
+        if (host)
+            __hip_atomic_store(host, (uint64_t)tag << 32 | sum, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+};
+
+// Launches this small are latency alone, 2 to 4 us and as much in the gap before
+// them: up to kScanSmall elements one workgroup takes 4096 a step (four steps
+// are about a launch), else two launches, the second of which sums the earlier
+// tiles' totals itself (4 bytes for each 1024 elements before it: at 10 M
+// elements still 20 KiB a workgroup). A step of 64 K bodies has one scan of each
+// kind: 884 -> 838 us against three launches each, with the cells' starts
+// written by the scan and its total sent to pinned memory.
+constexpr uint64_t kScanSmall = 16384;
+
+__global__ void __launch_bounds__(1024) scan_small_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out,
+                                                         uint32_t n, uint32_t *__restrict__ total, ScanExtra extra)
+{
+    __shared__ uint32_t lds[1024 / 64 + 1];
+    uint32_t carry = 0;
+    for (uint32_t b0 = 0; b0 < n; b0 += 4096) {
+        const uint32_t base = b0 + threadIdx.x * 4;
+        uint32_t v[4], s = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = base + k < n ? in[base + k] : 0u;
+            s += v[k];
+        }
+        uint32_t tot;
+        uint32_t run = dev::block_excl_scan<1024>(s, lds, &tot) + carry;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (base + k < n) {
+                out[base + k] = run;
+                extra.slot(v[k], run, base + k);
+            }
+            run += v[k];
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0) extra.finish(carry, total);
+}
+
+// More: blocks of kScanTile elements scan locally, then each adds the sums of
+// the blocks before it.
 __global__ void __launch_bounds__(256) scan_tiles_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out,
                                                         uint64_t n, uint32_t *__restrict__ part)
 {
@@ -182,35 +238,36 @@ __global__ void __launch_bounds__(256) scan_tiles_kernel(const uint32_t *__restr
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
-__global__ void __launch_bounds__(1024) scan_parts_kernel(uint32_t *__restrict__ part, uint32_t nb,
-                                                         uint32_t *__restrict__ total)
+__global__ void __launch_bounds__(256) scan_join_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out,
+                                                       uint64_t n, const uint32_t *__restrict__ part,
+                                                       uint32_t *__restrict__ total, ScanExtra extra)
 {
-    __shared__ uint32_t lds[1024 / 64 + 1];
-    uint32_t carry = 0;
-    for (uint32_t b0 = 0; b0 < nb; b0 += 1024) {
-        const uint32_t b = b0 + threadIdx.x;
-        const uint32_t v = b < nb ? part[b] : 0u;
-        uint32_t tot;
-        const uint32_t run = dev::block_excl_scan<1024>(v, lds, &tot);
-        if (b < nb) part[b] = carry + run;
-        carry += tot;
+    __shared__ uint32_t lds[256 / 64 + 1];
+    uint32_t mine = 0, before;
+    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += 256) mine += part[b];
+    (void)dev::block_excl_scan<256>(mine, lds, &before);
+#pragma unroll
+    for (uint32_t k = 0; k < kScanTile / 256; ++k) {
+        const uint64_t i = (uint64_t)blockIdx.x * kScanTile + k * 256 + threadIdx.x;
+        if (i < n) {
+            const uint32_t run = out[i] + before;
+            out[i] = run;
+            extra.slot(in[i], run, i);
+        }
     }
-    if (threadIdx.x == 0) *total = carry;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) extra.finish(before + part[blockIdx.x], total);
 }
 
-__global__ void __launch_bounds__(256) scan_add_kernel(uint32_t *__restrict__ out, uint64_t n,
-                                                      const uint32_t *__restrict__ part)
-{
-    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) out[i] += part[i / kScanTile];
-}
-
-int scan_u32(const uint32_t *in, uint32_t *out, uint64_t n, uint32_t *part, uint32_t *total, hipStream_t s)
+int scan_u32(const uint32_t *in, uint32_t *out, uint64_t n, uint32_t *part, uint32_t *total, const ScanExtra &extra,
+             hipStream_t s)
 {
     const uint32_t nb = (uint32_t)std::max<uint64_t>(1, (n + kScanTile - 1) / kScanTile);
-    hipLaunchKernelGGL(scan_tiles_kernel, dim3(nb), dim3(256), 0, s, in, out, n, part);
-    hipLaunchKernelGGL(scan_parts_kernel, dim3(1), dim3(1024), 0, s, part, nb, total);
-    if (n) hipLaunchKernelGGL(scan_add_kernel, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, out, n, part);
+    if (n <= kScanSmall) {
+        hipLaunchKernelGGL(scan_small_kernel, dim3(1), dim3(1024), 0, s, in, out, (uint32_t)n, total, extra);
+    } else {
+        hipLaunchKernelGGL(scan_tiles_kernel, dim3(nb), dim3(256), 0, s, in, out, n, part);
+        hipLaunchKernelGGL(scan_join_kernel, dim3(nb), dim3(256), 0, s, in, out, n, part, total, extra);
+    }
     RAFI_LAUNCH_CHECK();
     return RAFI_OK;
 }
@@ -320,14 +377,6 @@ __global__ void __launch_bounds__(kNBThreads) nb_flag_kernel(const NBParticle *_
         f = ((k >> shift) != (kp >> shift) || key_owner(K, D, k) != key_owner(K, D, kp)) ? 1u : 0u;
     }
     flags[i] = f;
-}
-
-__global__ void __launch_bounds__(kNBThreads) nb_cell_start_kernel(const uint32_t *__restrict__ flags,
-                                                                  const uint32_t *__restrict__ cell_of, uint64_t n,
-                                                                  uint32_t *__restrict__ cell_start)
-{
-    const uint64_t i = (uint64_t)blockIdx.x * kNBThreads + threadIdx.x;
-    if (i < n && flags[i]) cell_start[cell_of[i]] = (uint32_t)i;
 }
 
 // First virtual-particle round: slot s (D - 1) + k carries root s to domain
@@ -857,10 +906,10 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
         hipLaunchKernelGGL(nb_flag_kernel, dim3(blocks_for(n)), dim3(kNBThreads), 0, s, q, n, job->splitters, D,
                            30 - 3 * job->cell_level, flags);
         RAFI_LAUNCH_CHECK();
-        rc = scan_u32(flags, cell_of, n, part, counters, s);
+        ScanExtra extra;
+        extra.starts = cell_start;
+        rc = scan_u32(flags, cell_of, n, part, counters, extra, s);
         if (rc != RAFI_OK) return rc;
-        hipLaunchKernelGGL(nb_cell_start_kernel, dim3(blocks_for(n)), dim3(kNBThreads), 0, s, flags, cell_of, n,
-                           cell_start);
         hipLaunchKernelGGL(nb_cells_kernel, dim3((uint32_t)std::max<uint64_t>(n, 1)), dim3(256), 0, s, q, n,
                            counters, cell_start, cells);
         RAFI_LAUNCH_CHECK();
@@ -906,10 +955,16 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
         hipLaunchKernelGGL(nb_answer_size_wave_kernel, dim3(waves_blocks(nr)), dim3(kNBThreads), 0, s, rv, cells,
                            dcell, boxes, theta, csize, cnt);
         RAFI_LAUNCH_CHECK();
-        rc = scan_u32(cnt, aoff, nr, part, counters + 1, s);
+        // the total comes through pinned memory, as a round's results do
+        ScanExtra extra;
+        extra.host = Rq->host_summary_dev + kHostExtra;
+        extra.tag = (uint32_t)Rq->round_seq;
+        rc = scan_u32(cnt, aoff, nr, part, counters + 1, extra, s);
         if (rc != RAFI_OK) return rc;
-        RAFI_HIP_CHECK(hipMemcpyAsync(&answers, counters + 1, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-        RAFI_HIP_CHECK(hipStreamSynchronize(s));
+        uint64_t word = 0;
+        rc = wait_host_word(Rq, kHostExtra, [&](uint64_t w) { return (word = w) >> 32 == extra.tag; });
+        if (rc != RAFI_OK) return rc;
+        answers = (uint32_t)word;
     }
     const uint64_t n2_slots = n1 + answers;
     if (n2_slots > V->cap) return RAFI_ERR_OVERFLOW;

@@ -96,6 +96,14 @@ def test_nbody_matches_oracle(orc, n, D, level, theta, eps, dts):
     _run(orc, p, D, level, theta, eps, dts)
 
 
+@pytest.mark.parametrize("n,D,theta", [
+    (16_384, 16, 0.8), (16_385, 16, 0.8),   # the scan of one workgroup, of tiles
+])
+def test_nbody_scan_sizes(orc, n, D, theta):
+    announce(f"nbody scan n={n}")
+    _run(orc, W.nbody_particles(n, seed=n), D, 6, theta, 1e-3, [1e-3], debug=False)
+
+
 def test_nbody_migration_empties_domains(orc):
     """Few particles per domain and large velocities: domains empty out and
     fill up between steps; empty domains send and receive nothing."""
