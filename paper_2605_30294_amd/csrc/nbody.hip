@@ -327,40 +327,90 @@ __global__ void __launch_bounds__(kNBThreads) nb_digit_kernel(const NBParticle *
 }
 
 // Key order within each domain in one launch: workgroup d sorts its domain's
-// (key, queue position) pairs in LDS with a bitonic network (the pairs are
-// distinct, so this is exactly the stable sort by key) and gathers the
-// particles in that order into dst. For domains of at most kSortMax
-// particles; the host takes the three digit passes otherwise.
+// (key, queue position) pairs with a bitonic network (the pairs are distinct,
+// so this is exactly the stable sort by key) and gathers the particles in that
+// order into dst. Bound by the latency of the stages, with few workgroups: 64
+// domains of 1024 particles 31 us with every stage in LDS, 20 with the pairs in
+// registers. For domains of at most kSortMax particles; the host takes the
+// three digit passes otherwise.
 constexpr uint32_t kSortMax = 8192;
 constexpr uint32_t kSortThreads = 1024;
+
+// Bitonic sort of the m <= R * kSortThreads words v[r] at index
+// r * kSortThreads + threadIdx.x (m a power of two). A stage's partner is in
+// another register, in another lane of the wavefront or, for the strides from
+// 64 to kSortThreads / 2 alone, in another wavefront: 10 of the 55 stages of
+// 1024 words go through LDS and barriers.
+template <int R>
+__device__ inline void sort_words(uint64_t (&v)[R], uint32_t m, uint64_t *lds)
+{
+    const uint32_t t = threadIdx.x;
+    auto keep = [](uint64_t a, uint64_t b, bool low) { return (a < b) == low ? a : b; };
+    for (uint32_t k = 2; k <= m; k <<= 1)
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+            // the lower of a pair holds the smaller word where bit k of the index is clear
+            auto low = [&](int r) {
+                const uint32_t i = (uint32_t)r * kSortThreads + t;
+                return ((i & j) == 0) == ((i & k) == 0);
+            };
+            if (j >= kSortThreads) {
+#pragma unroll
+                for (int s = 1; s < R; s <<= 1)
+                    if (j == (uint32_t)s * kSortThreads) {
+#pragma unroll
+                        for (int r = 0; r < R; ++r)
+                            if ((r & s) == 0) {
+                                const uint64_t a = v[r], b = v[r | s];
+                                v[r] = keep(a, b, low(r));
+                                v[r | s] = keep(a, b, !low(r));
+                            }
+                    }
+            } else if (j >= 64) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) lds[r * kSortThreads + t] = v[r];
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < R; ++r) v[r] = keep(v[r], lds[r * kSortThreads + (t ^ j)], low(r));
+                __syncthreads();
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) v[r] = keep(v[r], __shfl_xor((unsigned long long)v[r], (int)j, 64), low(r));
+            }
+        }
+}
+
+template <int R>
+__device__ inline void sort_domain(const NBParticle *__restrict__ src, uint32_t first, uint32_t count,
+                                   NBParticle *__restrict__ dst, uint64_t *lds)
+{
+    uint32_t m = 1;  // a power of two >= count
+    while (m < count) m <<= 1;
+    uint64_t v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t i = r * kSortThreads + threadIdx.x;
+        v[r] = i < count ? ((uint64_t)morton_key(src[first + i].pos) << 32) | i : ~0ull;
+    }
+    sort_words<R>(v, m, lds);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t i = r * kSortThreads + threadIdx.x;
+        if (i < count) dst[first + i] = src[first + (uint32_t)v[r]];
+    }
+}
 
 __global__ void __launch_bounds__(kSortThreads) nb_domain_sort_kernel(const NBParticle *__restrict__ src,
                                                                       const uint64_t *__restrict__ off,
                                                                       NBParticle *__restrict__ dst)
 {
-    __shared__ uint64_t s_key[kSortMax];
+    __shared__ uint64_t lds[kSortMax];
     const uint32_t d = blockIdx.x;
     const uint32_t first = (uint32_t)off[d], count = (uint32_t)(off[d + 1] - off[d]);
-    uint32_t m = 1;  // a power of two >= count (count <= kSortMax)
-    while (m < count) m <<= 1;
-    for (uint32_t i = threadIdx.x; i < m; i += kSortThreads)
-        s_key[i] = i < count ? ((uint64_t)morton_key(src[first + i].pos) << 32) | i : ~0ull;
-    __syncthreads();
-    for (uint32_t k = 2; k <= m; k <<= 1)
-        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-            for (uint32_t i = threadIdx.x; i < m; i += kSortThreads) {
-                const uint32_t l = i ^ j;
-                if (l > i) {
-                    const uint64_t a = s_key[i], b = s_key[l];
-                    if ((a > b) == ((i & k) == 0)) {
-                        s_key[i] = b;
-                        s_key[l] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    for (uint32_t i = threadIdx.x; i < count; i += kSortThreads) dst[first + i] = src[first + (uint32_t)s_key[i]];
+    static_assert(kSortMax == 8 * kSortThreads, "up to eight words a thread");
+    if (count <= kSortThreads) sort_domain<1>(src, first, count, dst, lds);
+    else if (count <= 2 * kSortThreads) sort_domain<2>(src, first, count, dst, lds);
+    else if (count <= 4 * kSortThreads) sort_domain<4>(src, first, count, dst, lds);
+    else sort_domain<8>(src, first, count, dst, lds);
 }
 
 // flags[i] = 1 where a new cell starts: a new level-L key prefix or a new domain
@@ -728,36 +778,42 @@ __global__ void __launch_bounds__(kNBThreads) nb_fold_kernel(NBParticle *__restr
 // moments (mass, then mass times x, y, z) over its particles in key order from
 // zero (the same sums as the domain moments above); then the centre of mass
 // is the first moment over the mass.
+// A workgroup per cell, in turns: their number is known on the device alone, and
+// 64 K workgroups that mostly find no cell take 16 us, these 12.
+constexpr uint64_t kCellGrid = 4096;
+
 __global__ void __launch_bounds__(256) nb_cells_kernel(const NBParticle *__restrict__ q, uint64_t n,
                                                        const uint32_t *__restrict__ n_cells,
                                                        const uint32_t *__restrict__ cell_start,
                                                        NBNode *__restrict__ cells)
 {
     __shared__ float s_sum[4];
-    const uint32_t c = blockIdx.x;
     const uint32_t nc = *n_cells;
-    if (c >= nc) return;  // the whole workgroup
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-    const uint32_t first = cell_start[c];
-    const uint32_t count = (c + 1 < nc ? cell_start[c + 1] : (uint32_t)n) - first;
-    float lo[3], hi[3];  // unused here
-    float sum;
-    if (w == 0) sum = domain_moment<0>(q, first, count, lane, lo, hi);
-    else if (w == 1) sum = domain_moment<1>(q, first, count, lane, lo, hi);
-    else if (w == 2) sum = domain_moment<2>(q, first, count, lane, lo, hi);
-    else sum = domain_moment<3>(q, first, count, lane, lo, hi);
-    if (lane == 0) s_sum[w] = sum;
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    const float m = s_sum[0];
-    NBNode nd;
-    nd.com[0] = s_sum[1] / m;
-    nd.com[1] = s_sum[2] / m;
-    nd.com[2] = s_sum[3] / m;
-    nd.mass = m;
-    nd.first = first;
-    nd.count = count;
-    cells[c] = nd;
+    for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
+        const uint32_t first = cell_start[c];
+        const uint32_t count = (c + 1 < nc ? cell_start[c + 1] : (uint32_t)n) - first;
+        float lo[3], hi[3];  // unused here
+        float sum;
+        if (w == 0) sum = domain_moment<0>(q, first, count, lane, lo, hi);
+        else if (w == 1) sum = domain_moment<1>(q, first, count, lane, lo, hi);
+        else if (w == 2) sum = domain_moment<2>(q, first, count, lane, lo, hi);
+        else sum = domain_moment<3>(q, first, count, lane, lo, hi);
+        if (lane == 0) s_sum[w] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const float m = s_sum[0];
+            NBNode nd;
+            nd.com[0] = s_sum[1] / m;
+            nd.com[1] = s_sum[2] / m;
+            nd.com[2] = s_sum[3] / m;
+            nd.mass = m;
+            nd.first = first;
+            nd.count = count;
+            cells[c] = nd;
+        }
+        __syncthreads();  // s_sum is read before the next cell's sums
+    }
 }
 
 uint32_t blocks_for(uint64_t n) { return (uint32_t)std::max<uint64_t>(1, (n + kNBThreads - 1) / kNBThreads); }
@@ -910,7 +966,7 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
         extra.starts = cell_start;
         rc = scan_u32(flags, cell_of, n, part, counters, extra, s);
         if (rc != RAFI_OK) return rc;
-        hipLaunchKernelGGL(nb_cells_kernel, dim3((uint32_t)std::max<uint64_t>(n, 1)), dim3(256), 0, s, q, n,
+        hipLaunchKernelGGL(nb_cells_kernel, dim3((uint32_t)std::min<uint64_t>(n, kCellGrid)), dim3(256), 0, s, q, n,
                            counters, cell_start, cells);
         RAFI_LAUNCH_CHECK();
     }

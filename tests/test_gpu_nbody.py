@@ -96,6 +96,16 @@ def test_nbody_matches_oracle(orc, n, D, level, theta, eps, dts):
     _run(orc, p, D, level, theta, eps, dts)
 
 
+@pytest.mark.parametrize("n", [1, 63, 65, 1024, 1025, 2048, 2049, 4097, 8191])
+def test_nbody_domain_sort_sizes(orc, n):
+    """One domain at the sizes around each register count of the sort, with
+    equal keys (particles in pairs at one place): the stable order."""
+    announce(f"nbody sort n={n}")
+    p = W.nbody_particles(n, seed=n + 40)
+    p["pos"][1::2] = p["pos"][0:n - n % 2:2]
+    _run(orc, _unique_masses(p), 1, 4, 0.5, 1e-3, [1e-3])
+
+
 @pytest.mark.parametrize("n,D,theta", [
     (16_384, 16, 0.8), (16_385, 16, 0.8),   # the scan of one workgroup, of tiles
 ])
