@@ -388,13 +388,17 @@ __device__ inline bool march_slot(const BatchDev &b, const float *__restrict__ v
 }
 
 // March workgroups unless the caller sets another number; never more than the
-// rays fill. Visits differ in length up to eight times between scenes, and of
-// 2048 workgroups only 1280 fit on the card at once (95 VGPRs): a grid this
-// size leaves the balance to the hardware's dispatch. 256 scenes, 32.5 M rays:
-// 9.5 ms a render at 2048, 8.2 at 8192, 7.9 at 32768 and beyond.
+// rays fill. Visits differ in length up to eight times between scenes, and the
+// register use that a compiler finds may let fewer workgroups on the card than
+// a grid made for it: a grid this size leaves the balance to the hardware's
+// dispatch. 256 scenes, 32.5 M rays, when 1280 workgroups fit: 9.5 ms a render
+// at 2048, 8.2 at 8192, 7.9 at 32768 and beyond.
 constexpr uint32_t kMarchGrid = 32768;
 
-__global__ void batch_march_kernel(BatchDev b, const float *__restrict__ volumes, float *__restrict__ image,
+// Bound by VALU issue, with the latency of a plane's loads behind it: with the
+// scene in vector registers (95) five wavefronts a SIMD, 7.9 ms a render, with
+// the scene in scalar ones (69) seven, 7.3, held to 64 registers eight, 7.1.
+__global__ void __launch_bounds__(512, 8) batch_march_kernel(BatchDev b, const float *__restrict__ volumes, float *__restrict__ image,
                                    uint32_t n_rays)
 {
     const uint64_t n_in = b.summary[S_TOTAL];
@@ -403,10 +407,18 @@ __global__ void batch_march_kernel(BatchDev b, const float *__restrict__ volumes
     for (uint64_t i0 = blockIdx.x * (uint64_t)blockDim.x + wave; i0 < n_in; i0 += (uint64_t)gridDim.x * blockDim.x) {
         // A wavefront's 64 slots mostly lie in one domain: its first slot's.
         int32_t d = wave_last_le(b.offsets, b.Dt, i0);
-        const uint64_t i = i0 + (threadIdx.x & 63u);
-        if (i < n_in) {
-            if (i >= b.offsets[d + 1]) d = ea::find_domain(b.offsets, b.Dt, i);
-            alive |= march_slot(b, volumes, image, n_rays, d, i);
+        const uint32_t lane = threadIdx.x & 63u;
+        const uint64_t i = i0 + lane;
+        const bool in = i < n_in;
+        if (in && i >= b.offsets[d + 1]) d = ea::find_domain(b.offsets, b.Dt, i);
+        // One domain at a time, so that its scene is in scalar registers. The
+        // mask, not the comparison, decides: the compiler would take d for the
+        // equal `one`, and d is per lane.
+        for (uint64_t left = __ballot(in); left;) {
+            const int32_t one = __builtin_amdgcn_readlane(d, __ffsll((unsigned long long)left) - 1);
+            const uint64_t now = __ballot(in && d == one);
+            if (now >> lane & 1u) alive |= march_slot(b, volumes, image, n_rays, one, i);
+            left &= ~now;
         }
     }
     if (alive) b.summary[S_ALIVE] = 1;
