@@ -51,6 +51,22 @@ struct TableLayout {
     __device__ uint64_t at(uint32_t e, uint32_t c) const { return (uint64_t)e * row + (uint64_t)c * col; }
 };
 
+// Four destinations into an LDS histogram; four equal ones are one addition
+// (lanes that add to one word take turns).
+__device__ inline void add_four(uint32_t *h, const uint4 &d, int32_t D)
+{
+    const uint32_t x = bucket_of((int32_t)d.x, D), y = bucket_of((int32_t)d.y, D), z = bucket_of((int32_t)d.z, D),
+                   w = bucket_of((int32_t)d.w, D);
+    if (x == y && x == z && x == w) {
+        atomicAdd(&h[x], 4u);
+    } else {
+        atomicAdd(&h[x], 1u);
+        atomicAdd(&h[y], 1u);
+        atomicAdd(&h[z], 1u);
+        atomicAdd(&h[w], 1u);
+    }
+}
+
 // Destination histogram of tile blockIdx.x into column blockIdx.x of table.
 __device__ inline void hist_tile(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint32_t T,
                                  TableLayout layout, uint32_t *__restrict__ table, uint32_t *h)
@@ -71,19 +87,10 @@ __device__ inline void hist_tile(const int32_t *__restrict__ dest, uint64_t n, i
 #pragma unroll
         for (int u = 0; u < kU; ++u) d4[u] = load_nt4(dest + i + u * stride);
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            atomicAdd(&h[bucket_of((int32_t)d4[u].x, D)], 1u);
-            atomicAdd(&h[bucket_of((int32_t)d4[u].y, D)], 1u);
-            atomicAdd(&h[bucket_of((int32_t)d4[u].z, D)], 1u);
-            atomicAdd(&h[bucket_of((int32_t)d4[u].w, D)], 1u);
-        }
+        for (int u = 0; u < kU; ++u) add_four(h, d4[u], D);
     }
     for (; i < vend; i += stride) {
-        int4 d4 = *reinterpret_cast<const int4 *>(dest + i);
-        atomicAdd(&h[bucket_of(d4.x, D)], 1u);
-        atomicAdd(&h[bucket_of(d4.y, D)], 1u);
-        atomicAdd(&h[bucket_of(d4.z, D)], 1u);
-        atomicAdd(&h[bucket_of(d4.w, D)], 1u);
+        add_four(h, *reinterpret_cast<const uint4 *>(dest + i), D);
     }
     for (uint64_t j = vend + threadIdx.x; j < end; j += blockDim.x) atomicAdd(&h[bucket_of(dest[j], D)], 1u);
     __syncthreads();
@@ -345,40 +352,23 @@ finalize_kernel(const uint32_t *__restrict__ table, uint32_t n_cols, int32_t D, 
         [&](int32_t e) { return n_cols ? (uint64_t)table[(uint64_t)e * n_cols] : 0ull; }, D, n, to, lds);
 }
 
-// Exclusive scan of table[0, M) in place by one workgroup of 1024 threads,
-// 16384 entries a step, the next step's loads in flight (about 5 us for one
-// step, 4 for each further one).
-__device__ inline void scan_steps(uint32_t *table, uint64_t M, uint32_t *lds)
-{
-    constexpr uint64_t kStep = 1024ull * kScanPer;
-    const uint64_t mine = (uint64_t)threadIdx.x * kScanPer;
-    uint32_t v[kScanPer], next[kScanPer], carry = 0;
-    load16(table, M, mine, v);
-    for (uint64_t base = 0; base < M; base += kStep) {
-        load16(table, M, base + kStep + mine, next);
-        uint32_t s = 0;
-#pragma unroll
-        for (int k = 0; k < kScanPer; ++k) s += v[k];
-        uint32_t tot;
-        const uint32_t run = block_excl_scan<1024>(s, lds, &tot) + carry;
-        store16_excl(table, M, base + mine, v, run);
-        carry += tot;
-#pragma unroll
-        for (int k = 0; k < kScanPer; ++k) v[k] = next[k];
-    }
-    __syncthreads();
-}
-
-// The scan and finalize in one launch, for tables of at most two steps: 5 and
-// 9 us (three steps 13), where the three launches take 13.8 at any of these
-// sizes.
-constexpr uint64_t kOneScanMax = 1ull << 15;
+// The scan and finalize in one launch by one workgroup, 16 entries a thread:
+// 5 us, where the three launches take about 8 back to back; a loop over twice
+// the entries takes 9.
+constexpr uint64_t kOneScanMax = 1024ull * kScanPer;
 
 __global__ void __launch_bounds__(1024)
 scan_one_kernel(uint32_t *__restrict__ table, uint64_t M, uint32_t n_cols, int32_t D, uint64_t n, Results to)
 {
     __shared__ uint32_t lds[1024 / 64 + 1];
-    scan_steps(table, M, lds);
+    const uint64_t mine = (uint64_t)threadIdx.x * kScanPer;
+    uint32_t v[kScanPer], s = 0, tot;
+    load16(table, M, mine, v);
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) s += v[k];
+    const uint32_t run = block_excl_scan<1024>(s, lds, &tot);
+    store16_excl(table, M, mine, v, run);
+    __syncthreads();
     finalize_body<1024>([&](int32_t e) { return (uint64_t)table[(uint64_t)e * n_cols]; }, D, n, to, lds);
 }
 
@@ -443,7 +433,7 @@ hist_scan_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint32
 // Grouped plans: one workgroup per table column of 4 tiles, a wave per tile
 // with a histogram of its own. The tiles' running sums go to pre, the sum of
 // all to the table, which is 4 times smaller than with a column per tile: for
-// 64 destinations up to 2M slots then fit scan_one_kernel (a round of 1M slots:
+// 64 destinations up to 1M slots then fit scan_one_kernel (a round of 1M slots:
 // histogram and scan 10 us for 18 in four launches). Wider groups are slower:
 // queues hold long runs of one destination, whose LDS adds are serial, and 16
 // tiles in one workgroup took 20 to 50 us.
@@ -468,12 +458,7 @@ hist_group_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint3
 #pragma unroll
         for (int u = 0; u < 4; ++u) d4[u] = load_nt4(dest + i + 256 * u);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            atomicAdd(&mine[bucket_of((int32_t)d4[u].x, D)], 1u);
-            atomicAdd(&mine[bucket_of((int32_t)d4[u].y, D)], 1u);
-            atomicAdd(&mine[bucket_of((int32_t)d4[u].z, D)], 1u);
-            atomicAdd(&mine[bucket_of((int32_t)d4[u].w, D)], 1u);
-        }
+        for (int u = 0; u < 4; ++u) add_four(mine, d4[u], D);
     }
     for (; i < end; i += 256)
         for (uint64_t j = i; j < min(i + 4, end); ++j) atomicAdd(&mine[bucket_of(dest[j], D)], 1u);
@@ -511,8 +496,9 @@ struct RunBases {
 };
 
 // Sums of the first `rows` counts over all columns and over those before col,
-// for row threadIdx.x, by a workgroup of NT threads: up to 16 threads share a
-// row, 16 loads in flight each. scratch: 2 NT words.
+// for row threadIdx.x, by a workgroup of NT threads: up to kSumParts threads
+// share a row, 16 loads in flight each. scratch: 2 NT words.
+constexpr uint32_t kSumParts = 16;
 constexpr int kSelfD = 128;                                  // destinations at most
 constexpr size_t kSelfLds = (2 * 256 + kSelfD + 2 + 8) * 4;  // bytes of LDS for 256 threads
 
@@ -522,7 +508,7 @@ __device__ inline void sum_columns(const RunBases &b, uint32_t col, uint32_t row
 {
     uint32_t lg = 0;
     while ((1u << lg) < rows) ++lg;
-    const uint32_t parts = min((uint32_t)NT >> lg, 16u), e = threadIdx.x & ((1u << lg) - 1), part = threadIdx.x >> lg;
+    const uint32_t parts = min((uint32_t)NT >> lg, kSumParts), e = threadIdx.x & ((1u << lg) - 1), part = threadIdx.x >> lg;
     all = before = 0;
     if (e < rows && part < parts) {
         for (uint32_t c0 = part; c0 < b.n_cols; c0 += 16 * parts) {
@@ -551,8 +537,7 @@ __device__ inline void sum_columns(const RunBases &b, uint32_t col, uint32_t row
 }
 
 // The same from the destinations of all n slots, of which those before `mid` (a
-// multiple of 4) count as before. Runs of four equal destinations are added
-// at once.
+// multiple of 4) count as before.
 template <int NT>
 __device__ inline void count_slots(const int32_t *__restrict__ dest, uint64_t n, uint64_t mid, int32_t D,
                                    uint32_t *scratch, uint32_t &all, uint32_t &before)
@@ -574,16 +559,7 @@ __device__ inline void count_slots(const int32_t *__restrict__ dest, uint64_t n,
             const uint64_t i = i0 + u * 4ull * NT;
             uint32_t *h = i < mid ? h0 : h1;
             if (i + 4 <= n) {
-                const uint32_t x = bucket_of((int32_t)d[u].x, D), y = bucket_of((int32_t)d[u].y, D),
-                               z = bucket_of((int32_t)d[u].z, D), w = bucket_of((int32_t)d[u].w, D);
-                if (x == y && x == z && x == w) {
-                    atomicAdd(&h[x], 4u);
-                } else {
-                    atomicAdd(&h[x], 1u);
-                    atomicAdd(&h[y], 1u);
-                    atomicAdd(&h[z], 1u);
-                    atomicAdd(&h[w], 1u);
-                }
+                add_four(h, d[u], D);
             } else {
                 for (uint64_t j = i; j < n; ++j) atomicAdd(&h[bucket_of(dest[j], D)], 1u);
             }
@@ -1115,13 +1091,18 @@ void finish_plan(SplitPlan &p)
 // The grouped histogram: where the automatic scatter shape is one of the
 // small staged ones or the plain one (at most 128 destinations and 256 MiB of
 // items: every context round of the workloads here), a tile's prefix fits 16
-// bits, and the ungrouped table is too large for the scans of one launch.
+// bits, and the ungrouped table is too large for the one-launch scan. Not where
+// the grouped one is just too large as well: the wavefront a tile gets then
+// costs what the smaller table saves (64 destinations, 1.4 M slots: 26 us
+// grouped, 23 not; 4 M slots: 46 grouped, 49 not).
 // Other shapes read the table by tile. The workspace is smaller than without:
 // 3 (D + 2) bytes of table per tile saved, 2 D for the prefixes.
 bool group_eligible(const SplitPlan &p)
 {
+    const uint64_t rows = (uint64_t)p.D + 2, m = rows * ((p.n_tiles + kGroupTiles - 1) / kGroupTiles);
     return g_split_variant == 0 && p.D <= 128 && p.n * (uint64_t)p.S <= (1ull << 28) &&
-           ((uint64_t)p.D + 2) * p.n_tiles > kOneScanMax && (uint64_t)p.tile * (kGroupTiles - 1) < 65536;
+           rows * p.n_tiles > kOneScanMax && (m <= kOneScanMax || m > 2 * kOneScanMax) &&
+           (uint64_t)p.tile * (kGroupTiles - 1) < 65536;
 }
 
 // Whether the scatter's workgroups find their run bases and the results
@@ -1136,11 +1117,13 @@ bool group_eligible(const SplitPlan &p)
 //     scatter of 584 K slots 6 + 14 us for 6 + 12 with a scan of 8 between.
 //     Columns stand for 4 tiles from kSelfPlain entries on (460 K slots 18 us
 //     for 24, 142 K the same, 84 K 15 for 14);
-//   not when the workgroups together read more than kSelfReads entries (1 M
-//     slots, 64 destinations: 18.4 us for 20.3, and twice the slots read four
-//     times as much).
+//   with few destinations a row has many columns: columns of 4 tiles also
+//     beyond 32 loads a thread (1 destination, 2 M slots: 23.5 us for 37);
+//   not when the workgroups' threads make more than kSelfLoads loads one after
+//     another, all workgroups together: 64 destinations, 1 M slots (60 K loads)
+//     18.4 us for 21.6 with a scan, 1.4 M slots (117 K) 26.8 for 23.2.
 constexpr uint32_t kCountTiles = 8;
-constexpr uint64_t kSelfPlain = 1ull << 13, kSelfMax = 1ull << 15, kSelfReads = 1ull << 24;
+constexpr uint64_t kSelfPlain = 1ull << 13, kSelfMax = 1ull << 15, kSelfLoads = 1ull << 16;
 
 void finish_self_plan(SplitPlan &p)
 {
@@ -1151,10 +1134,13 @@ void finish_self_plan(SplitPlan &p)
         p.self = kCountSlots;
         return;
     }
+    uint32_t parts = 256;  // threads that share a row (sum_columns)
+    while (parts > 1 && parts * (uint32_t)p.D > 256) parts /= 2;
+    parts = std::min(parts, kSumParts);
     SplitPlan c = p;
-    c.group_bits = c.rows * c.n_tiles > kSelfPlain ? kGroupBits : 0;
+    c.group_bits = c.rows * c.n_tiles > kSelfPlain || c.n_tiles > 32 * parts ? kGroupBits : 0;
     finish_plan(c);
-    if (c.M > kSelfMax || c.M * c.n_tiles > kSelfReads) return;
+    if (c.M > kSelfMax || (uint64_t)c.n_tiles * ((c.n_cols + parts - 1) / parts) > kSelfLoads) return;
     p = c;
     p.self = kSumTable;
 }

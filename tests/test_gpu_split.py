@@ -203,7 +203,8 @@ def test_split_grouped_histogram(orc, n, D, words):
 @pytest.mark.parametrize("n,D,words", [
     (1, 1, 4), (5, 2, 3), (1023, 64, 12), (8192, 64, 8), (8193, 64, 8), (8190, 128, 1), (8191, 129, 4),
     (126_976, 64, 4), (126_977, 64, 4),            # 64 destinations: a column per tile, per 4 tiles
-    (1_019_905, 63, 12), (1_060_000, 64, 11),      # about the most a workgroup sums itself
+    (1_048_576, 64, 12), (1_048_577, 64, 11),      # the most loads the workgroups make for the sums, and more
+    (524_288, 1, 4), (524_289, 2, 4), (2_097_153, 2, 3),   # few rows, many columns
     (64_512, 128, 6), (300_001, 128, 2), (2_000_003, 3, 5), (4_194_304, 1, 1)])
 def test_split_without_scan(orc, n, D, words):
     """Few destinations: the scatter's workgroups find their output slots from
