@@ -93,14 +93,22 @@ __device__ inline float dt_logf(float x)
 // residual (Markstein 1990), 5 instructions for about 13. That needs a
 // majorant far from the ends of the exponent range (the same test in every
 // lane) and quotients that are zero, normal or, where only 1 - q is used, too
-// small to count.
+// small to count. divide: |a| at most 2^80, whose quotients stay finite (the
+// free flights: a below 17). divide_any: any a; the corrections of a quotient
+// that overflows, or of an infinite a, would be inf - inf.
 struct Majorant {
     float smax, inv;
     bool plain;
     __device__ explicit Majorant(float s) : smax(s), inv(1.0f / s), plain(!(s >= 0x1p-40f && s <= 0x1p40f)) {}
-    __device__ float divide(float a) const
+    __device__ float divide(float a) const { return plain ? a / smax : corrected(a); }
+    __device__ float divide_any(float a) const
     {
-        if (plain) return a / smax;
+        return plain || !(fabsf(a) < 0x1p80f) ? a / smax : corrected(a);
+    }
+
+private:
+    __device__ float corrected(float a) const
+    {
         const float q0 = a * inv;
         const float q1 = __fmaf_rn(__fmaf_rn(-smax, q0, a), inv, q0);
         return __fmaf_rn(__fmaf_rn(-smax, q1, a), inv, q1);
@@ -344,7 +352,7 @@ dt_trace_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
                 if (it.kind == kPath) {
                     hit = draw(job, it) * job.smax < sigma;
                 } else {
-                    it.w = it.w * (1.0f - mj.divide(sigma));
+                    it.w = it.w * (1.0f - mj.divide_any(sigma));
                 }
                 if (!hit) {
                     fly(job, mj, it);
@@ -458,7 +466,7 @@ dt_trace_half_kernel(rafi_device_view view, rafi_dt_job job, uint64_t n_paths)
         const bool stays = box.contains(q);
         const uint32_t ends = (uint32_t)(__ballot(collides || !stays) >> upper);
         const uint32_t last = ends ? (uint32_t)__ffs((int)ends) - 1 : 31;
-        if (!path) it.w = chain_weights(1.0f - mj.divide(sigma), last, it.w);
+        if (!path) it.w = chain_weights(1.0f - mj.divide_any(sigma), last, it.w);
         hit = __shfl((int)collides, (int)last, 32) != 0;
         inside = hit || ends == 0;
         it.px = __shfl(hit ? p[0] : q[0], (int)last, 32);

@@ -107,6 +107,33 @@ def test_launch_sizes_and_majorants(orc, n, grid, nv, w, B, scale):
     _compare(g, o)
 
 
+@pytest.mark.parametrize("w", [24, 420])            # 32 lanes an item, one lane an item
+@pytest.mark.parametrize("kappa,smax", [(1e20, 0.3),   # an infinite extinction
+                                        (3e8, 0.3)])   # a finite one whose quotient by the majorant overflows
+def test_extinction_far_above_the_majorant(orc, w, kappa, smax):
+    """A block whose extinction is infinite, or overflows divided by the
+    majorant, as the float32 division has it: shadow rays through it weigh an
+    infinity of the oracle's sign (float64 there, rounded to float32 here),
+    never a NaN; the routing is the oracle's."""
+    n, grid = 24, (2, 1, 2)
+    vol = np.zeros((n, n, n), dtype=np.float32)
+    vol[4:16, 6:20, 5:17] = 1e30
+    views = W.random_views(1, n, w, w, seed=63)
+    announce(f"dt overflow kappa={kappa} w={w}")
+    args = (kappa, smax, 0.7, (0.6, 0.0, 0.8), 1.0, 2, 9)
+    g = _stepwise(vol, grid, views, *args)
+    o = orc.dt_render(vol, grid, views, *args, queue_cap=1 << 24)
+    assert np.array_equal(g["counts"], o["round_counts"])
+    assert np.array_equal(g["queue"][:, [0, 1, 2, 3, 4, 5, 7, 8, 9, 10, 11]], o["queue"])
+    with np.errstate(over="ignore"):
+        want = o["contrib"].astype(np.float32)
+    assert np.isinf(want).sum() > want.size // 100 and not np.isnan(want).any()
+    big = np.isinf(want)
+    assert np.array_equal(g["contrib"][big], want[big])
+    ok, i, r = rel_close(g["contrib"][~big], want[~big], RTOL, ATOL)
+    assert ok, (i, r)
+
+
 def test_render_entry_point_deterministic(orc):
     dev = device()
     n, grid = 64, (4, 4, 4)
