@@ -257,10 +257,11 @@ __device__ inline int32_t first_inside(const Geo &g, const float org[3], const f
         auto ltn = [&](int32_t k) { return coord(k) < fn; };
         const float r = __builtin_amdgcn_rcpf(dir[a]) * rdt;
         const float k0 = ceilf(-org[a] * r - 0.5f), kn = ceilf((fn - org[a]) * r - 0.5f);
-        if (dir[a] > 0.0f) {
+        const bool moves = dir[a] > 0.0f || dir[a] < 0.0f;
+        if (moves && (dir[a] > 0.0f) == (dt > 0.0f)) {  // the coordinate rises with k
             k_lo = max(k_lo, first_flip(K, false, k0, ge0));   // becomes true
             k_hi = min(k_hi, first_flip(K, true, kn, ltn));    // becomes false
-        } else if (dir[a] < 0.0f) {
+        } else if (moves) {
             k_lo = max(k_lo, first_flip(K, false, kn, ltn));
             k_hi = min(k_hi, first_flip(K, true, k0, ge0));
         } else if (!(org[a] >= 0.0f && org[a] < fn)) {

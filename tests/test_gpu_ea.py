@@ -190,6 +190,29 @@ def test_axis_and_grazing_views(orc, direction, n, grid, dt):
     _compare(g, o)
 
 
+@pytest.mark.parametrize("K", [20, 56, 111])
+def test_negative_spacing(orc, K):
+    """A negative sample spacing walks a ray against its direction: rays that
+    start inside the volume and leave it before, or after, half of their
+    samples, rays that start outside and enter it, and rays along an axis. The
+    oracle tests every sample."""
+    dev = device()
+    n, grid, w = 32, (2, 4, 1), 24
+    vol = W.blob_volume(n, 140)
+    views = W.random_views(3, n, w, w, seed=141)
+    for i, back in enumerate((0.5, 0.3)):                 # starts inside, W/2 before the centre moved onto it
+        views["org0"][i] += views["dir"][i] * np.float32(n * np.sqrt(3.0) * back)
+    views["dir"] *= np.float32(-1.0)
+    views = np.concatenate([views, W.plusz_view(n, w, w)])
+    views["org0"][3, 2] = 20.25
+    views["n_samples"] = K
+    announce(f"ea negative spacing K={K}")
+    g = _stepwise(torch.from_numpy(vol).to(dev), grid, views, dt=-0.5)
+    o = orc.ea_render(vol, grid, views, dt=-0.5, c=C32, queue_cap=1 << 20)
+    assert (o["klast"] > 0).mean() > 0.3
+    _compare(g, o)
+
+
 @pytest.mark.parametrize("n,grid,nv,w", [(48, (3, 2, 4), 7, 260), (32, (1, 1, 1), 25, 128), (40, (5, 10, 4), 9, 225),
                                          (24, (2, 2, 2), 1, 640)])
 def test_brick_march(orc, n, grid, nv, w):
