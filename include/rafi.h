@@ -126,7 +126,11 @@ int rafi_set_stream(rafi_ctx *ctx, void *hip_stream);
  * as bad destinations. */
 int rafi_set_debug(rafi_ctx *ctx, int32_t on);
 
-/* Tile size used to build in_tile_offsets (default 256; any value >= 1). */
+/* Tile size used to build in_tile_offsets (default 256; any value >= 1). With
+ * 512 or more, and bricks that fit in a workgroup's LDS, the
+ * emission-absorption march takes its two exponentials from the math library
+ * (expf, expm1f) instead of the hardware's base-2 exponential and a series:
+ * each within an ulp or two at every optical depth, and slower. */
 int rafi_set_tile_items(rafi_ctx *ctx, uint32_t tile_items);
 
 /* Fill *out with the current device view (getDeviceInterface, Sec. 3.4). */

@@ -90,6 +90,7 @@ __device__ inline void emit_ray(const rafi_device_view &view, const rafi_ea_job 
 // in its brick (a counting sort through LDS), where chords can differ and
 // unless they all fall in one bucket. Every ray is marched as if alone and written to its own output
 // slot, so results do not depend on the lane.
+template <bool kLib>
 __global__ void __launch_bounds__(256)
 march_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
 {
@@ -133,7 +134,8 @@ march_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
         float org[3], dir[3];
         int32_t K;
         job_ray(job, it.ray, org, dir, &K);
-        const int32_t dest = ea::march_through(job.volume, g, ea::box_of(d, g), org, dir, K, job.dt, job.c, it);
+        const int32_t dest =
+            ea::march_through<kLib>(job.volume, g, ea::box_of(d, g), org, dir, K, job.dt, job.c, it);
         emit_ray(view, job, slot, it, dest);
         return;
     }
@@ -194,7 +196,8 @@ march_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
     float org[3], dir[3];
     int32_t K;
     job_ray(job, it.ray, org, dir, &K);
-    const int32_t dest = ea::march_through(job.volume, g, ea::box_of(d, g), org, dir, K, job.dt, job.c, it);
+    const int32_t dest =
+        ea::march_through<kLib>(job.volume, g, ea::box_of(d, g), org, dir, K, job.dt, job.c, it);
     emit_ray(view, job, slot, it, dest);
 }
 
@@ -256,6 +259,7 @@ __device__ inline uint32_t next_places(BrickOrder &o)
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
 }
 
+template <bool kLib>
 __global__ void __launch_bounds__(kBrickThreads)
 march_brick_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
 {
@@ -298,9 +302,9 @@ march_brick_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
                 float org[3], dir[3];
                 int32_t K;
                 job_ray(job, it.ray, org, dir, &K);
-                const int32_t dest = K <= ea::kFloatK
-                                         ? ea::march_through_lds(vol, g, box, org, dir, K, job.dt, job.c, it)
-                                         : ea::march_through(job.volume, g, box, org, dir, K, job.dt, job.c, it);
+                const int32_t dest =
+                    K <= ea::kFloatK ? ea::march_through_lds<kLib>(vol, g, box, org, dir, K, job.dt, job.c, it)
+                                     : ea::march_through<kLib>(job.volume, g, box, org, dir, K, job.dt, job.c, it);
                 emit_ray(view, job, slot, it, dest);
             }
             __syncthreads();  // the order and the region are reused
@@ -745,21 +749,28 @@ uint32_t n_rays_of(const rafi_ea_job *j) { return (uint32_t)((uint64_t)j->n_view
 constexpr uint64_t kBrickRaysPerCu = 1536;
 
 // One march launch over the view's n_in queued rays (an upper bound is enough).
+template <bool kLib>
+void launch_march_as(const rafi_device_view &v, const rafi_ea_job *job, int cus, hipStream_t s)
+{
+    if (!v.n_in) return;
+    const size_t lds = region_bytes(job) + kOrderBytes;
+    if (job->n <= ea::kSmallN && v.n_in >= kBrickRaysPerCu * cus && lds + kBrickStatic <= max_lds_bytes())
+        hipLaunchKernelGGL(march_brick_kernel<kLib>, dim3(cus), dim3(kBrickThreads), lds, s, v, *job,
+                           n_rays_of(job));
+    else
+        hipLaunchKernelGGL(march_kernel<kLib>, dim3((uint32_t)((v.n_in + 255) / 256)), dim3(256), 0, s, v, *job,
+                           n_rays_of(job));
+}
+
+// Contexts with tiles of 512 items or more, and bricks that fit in LDS, march
+// with the library's exponentials (rafi_set_tile_items).
 int launch_march(rafi_ctx *c, const rafi_device_view &v, const rafi_ea_job *job)
 {
     int cus = 0;
     if (cu_count(&cus) != RAFI_OK) return RAFI_ERR_HIP;
     const int ph = prof_domain_begin(c);
-    if (v.n_in) {
-        const size_t lds = region_bytes(job) + kOrderBytes;
-        if (job->n <= ea::kSmallN && v.n_in >= kBrickRaysPerCu * cus && lds + kBrickStatic <= max_lds_bytes()) {
-            hipLaunchKernelGGL(march_brick_kernel, dim3(cus), dim3(kBrickThreads), lds, c->stream, v, *job,
-                               n_rays_of(job));
-        } else {
-            hipLaunchKernelGGL(march_kernel, dim3((uint32_t)((v.n_in + 255) / 256)), dim3(256), 0, c->stream, v,
-                               *job, n_rays_of(job));
-        }
-    }
+    if (v.tile_items >= 512 && region_bytes(job) <= max_lds_bytes()) launch_march_as<true>(v, job, cus, c->stream);
+    else launch_march_as<false>(v, job, cus, c->stream);
     prof_domain_end(c, ph);
     RAFI_LAUNCH_CHECK();
     return RAFI_OK;

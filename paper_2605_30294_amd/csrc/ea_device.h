@@ -343,14 +343,17 @@ __device__ inline int32_t entry_sample(const Box &box, const float org[3], const
 // exponential of -tau log2(e)); its relative error, about 1e-6 for the
 // optical depths of a ray, stays well inside the integrals' tolerance; the
 // emission weight 1 - exp(-sigma) keeps full relative accuracy for small
-// sigma (one_minus_exp_neg).
+// sigma (one_minus_exp_neg). kLib: the library's expf and expm1 instead, both
+// within an ulp or two at every optical depth (contexts with large tiles,
+// rafi_set_tile_items).
+template <bool kLib>
 struct Sums {
     float tau, I, ctau = 0.0f, cI = 0.0f;
     __device__ Sums(const Item &it) : tau(it.tau), I(it.I) {}
     __device__ void add(float rho, float c)
     {
         const float sigma = c * rho;
-        const float w = __expf(-tau) * one_minus_exp_neg(sigma);
+        const float w = kLib ? expf(-tau) * -expm1f(-sigma) : __expf(-tau) * one_minus_exp_neg(sigma);
         // compensated I += w * rho
         const float yI = w * rho - cI;
         const float tI = I + yI;
@@ -426,7 +429,7 @@ struct LdsVol {
 // interp_corners. Bound by VALU issue, 45 instructions a sample for 80: 256
 // scenes of axis views (7.4 G samples) 18.5 -> 10.8 ms with a floor and two
 // clamps a sample to find the cell, 10.4 ms without.
-template <typename Vol>
+template <typename Vol, typename Sums>
 __device__ __forceinline__ void march_z(const Vol &vol, int32_t n, const float org[3], float dirz, bool up, float dt,
                                         float c, int32_t k, int32_t end, Sums &s)
 {
@@ -488,14 +491,14 @@ __device__ __forceinline__ void march_z(const Vol &vol, int32_t n, const float o
 // I and leaves it.k at the first sample not taken. Returns the brick that owns
 // that sample, or -1 when the ray left the volume or ran out of samples.
 // kSmall: the volume has at most kSmallN^3 voxels (tri_setup_small) and the
-// ray at most kFloatK samples.
-template <bool kSmall>
+// ray at most kFloatK samples. kLib: see Sums.
+template <bool kSmall, bool kLib>
 __device__ inline int32_t march_through_n(const float *__restrict__ vol, const Geo &g, const Box &box,
                                           const float org[3], const float dir[3], int32_t K, float dt, float c,
                                           Item &it)
 {
     const int32_t end = exit_sample(box, org, dir, dt, it.k, K);
-    Sums s(it);
+    Sums<kLib> s(it);
     if (kSmall && dir[0] == 0.0f && dir[1] == 0.0f) {
         if (dir[2] * dt > 0.0f)
             march_z(GlobalVol{vol, g.n}, g.n, org, dir[2], true, dt, c, it.k, end, s);
@@ -526,23 +529,25 @@ __device__ inline int32_t march_through_n(const float *__restrict__ vol, const G
     return owner_of(p, g);
 }
 
+template <bool kLib = false>
 __device__ inline int32_t march_through(const float *__restrict__ vol, const Geo &g, const Box &box,
                                         const float org[3], const float dir[3], int32_t K, float dt, float c,
                                         Item &it)
 {
-    return g.n <= kSmallN && K <= kFloatK ? march_through_n<true>(vol, g, box, org, dir, K, dt, c, it)
-                                          : march_through_n<false>(vol, g, box, org, dir, K, dt, c, it);
+    return g.n <= kSmallN && K <= kFloatK ? march_through_n<true, kLib>(vol, g, box, org, dir, K, dt, c, it)
+                                          : march_through_n<false, kLib>(vol, g, box, org, dir, K, dt, c, it);
 }
 
 // march_through with the brick's densities read from a staged region, for
 // volumes of at most kSmallN^3 voxels and rays of at most kFloatK samples: the
 // same values and operations. No cell is kept in registers here: eight LDS
 // reads cost less than testing for a new cell and branching.
+template <bool kLib>
 __device__ inline int32_t march_through_lds(const LdsVol &vol, const Geo &g, const Box &box, const float org[3],
                                             const float dir[3], int32_t K, float dt, float c, Item &it)
 {
     const int32_t end = exit_sample(box, org, dir, dt, it.k, K);
-    Sums s(it);
+    Sums<kLib> s(it);
     if (dir[0] == 0.0f && dir[1] == 0.0f) {
         // one loop for both directions: wavefronts here hold rays of all views
         march_z(vol, g.n, org, dir[2], dir[2] * dt > 0.0f, dt, c, it.k, end, s);

@@ -235,6 +235,41 @@ def test_brick_march(orc, n, grid, nv, w):
     _compare(g, o)
 
 
+@pytest.mark.parametrize("w", [40, 640])               # the gather march, the LDS-staged one
+def test_large_tiles_march_with_the_library_exponentials(w):
+    """Tiles of 512 items or more: each sample's weight is
+    expf(-tau) * -expm1f(-sigma). One sample per ray at an optical depth of 60
+    to 80, where the hardware's base-2 exponential of the rounded product is
+    up to 40 ulp off, in a uniform volume (whose interpolation is exact):
+    within an ulp each for the two functions and half an ulp for each of the
+    two products, relative to float64."""
+    dev = device()
+    n, rho, n_rays = 16, np.float32(0.37), w * w
+    vol = torch.full((n, n, n), float(rho), dtype=torch.float32, device=dev)
+    views = W.plusz_view(n, w, w)
+    K = int(views[0]["n_samples"])
+    tau = np.random.default_rng(3).uniform(60.0, 80.0, n_rays).astype(np.float32)
+    items = np.zeros((n_rays, 4), dtype=np.int32)
+    items[:, 0], items[:, 1], items[:, 2] = np.arange(n_rays), K - 1, tau.view(np.int32)
+    announce(f"ea library exponentials rays={n_rays}")
+    ctx = rafi.Context(1, rafi.EA_ITEM_BYTES, n_rays)
+    ctx.set_tile_items(1024)
+    image = torch.zeros(n_rays, dtype=torch.float32, device=dev)
+    job = rafi.ea_job(vol, (1, 1, 1), rafi.views_to_device(views, dev), 1, w, w, image, c=C32)
+    ctx.begin(n_rays)
+    ctx.emit_bulk(torch.from_numpy(items).to(dev), torch.zeros(n_rays, dtype=torch.int32, device=dev))
+    _, total, _ = ctx.round(counts=False)
+    assert total == n_rays
+    assert (total >= 1536 * torch.cuda.get_device_properties(dev).multi_processor_count) == (w == 640)
+    rafi.ea_march(ctx, job)
+    torch.cuda.synchronize()
+    sigma = float(np.float32(C32) * rho)
+    want = np.exp(-tau.astype(np.float64)) * -np.expm1(-sigma) * float(rho)
+    ok, i, r = rel_close(image.cpu().numpy(), want, 3.01 * 2.0 ** -23)
+    assert ok, (i, r)
+    ctx.close()
+
+
 def _segments(queue, counts):
     """Split a concatenation of per-round, per-domain queues into its segments."""
     ends = np.cumsum(counts.reshape(-1).astype(np.int64))
