@@ -14,8 +14,11 @@
  *     of caller memory. A context owns its queues (Sec. 3.2: the library
  *     manages the arrays itself once told their capacity).
  *   - Work is stream-ordered on the context's stream (rafi_set_stream;
- *     default: the null stream). Calls that return host-visible results
- *     (rafi_round's counts and total) synchronise that stream.
+ *     default: the null stream). rafi_round and rafi_nb_seed return with that
+ *     stream drained, as do the whole renders and traces where they return an
+ *     error of their rounds; otherwise these return with their results written
+ *     (rafi_dt_render's image: enqueued) and the queue empty. rafi_nb_step
+ *     returns with its queues whole and the forces enqueued.
  *   - A context is not thread-safe: one host thread per context.
  *   - Every int-returning call returns RAFI_OK (0) or a negative RAFI_ERR_*
  *     code; rafi_strerror() names it. On RAFI_ERR_ARG nothing was launched.
@@ -115,7 +118,8 @@ void rafi_destroy(rafi_ctx *ctx);
 int rafi_resize(rafi_ctx *ctx, uint64_t capacity);
 
 /* Stream for all later work on this context (a hipStream_t, passed as void*).
- * The stream must outlive its use by the context. The paper's library runs on
+ * The stream must outlive its use by the context. After a render or trace a
+ * change of stream waits (on the host) for what is left of it. The paper's library runs on
  * one stream and leaves several asynchronous streams to future work (Sec. 7);
  * here each context has one stream of the caller's choice, so contexts on
  * different streams (and the batched form) can overlap. */

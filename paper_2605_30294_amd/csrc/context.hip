@@ -333,6 +333,7 @@ void rafi_destroy(rafi_ctx *c)
     if (c->work) (void)hipFree(c->work);
     if (c->append) (void)hipFree(c->append);
     if (c->host_summary) (void)hipHostFree(c->host_summary);
+    if (c->settled) (void)hipEventDestroy(c->settled);
     for (int i = 0; i < c->n_pending; ++i)
         for (int k = 0; k < (c->pending[i].kind == 0 ? 3 : 2); ++k)
             if (c->pending[i].e[k]) (void)hipEventDestroy(c->pending[i].e[k]);
@@ -354,7 +355,17 @@ int rafi_resize(rafi_ctx *c, uint64_t capacity)
 int rafi_set_stream(rafi_ctx *c, void *hip_stream)
 {
     if (!c) return RAFI_ERR_ARG;
-    c->stream = static_cast<hipStream_t>(hip_stream);
+    const hipStream_t next = static_cast<hipStream_t>(hip_stream);
+    if (c->in_flight && next != c->stream) {
+        // a wait on the host, allowed while this thread captures another stream
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (hipStreamSynchronize(c->stream) != hipSuccess) (void)hipDeviceSynchronize();
+        (void)hipGetLastError();
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        c->in_flight = false;
+    }
+    c->stream = next;
     return RAFI_OK;
 }
 
@@ -428,6 +439,7 @@ int rafi_round(rafi_ctx *c, uint64_t *counts, uint64_t *total)
     const int rc = round_run(c, counts, total);
     if (rc != RAFI_OK && rc != RAFI_ERR_BAD_DEST && rc != RAFI_ERR_OVERFLOW) return rc;
     RAFI_HIP_CHECK(hipStreamSynchronize(c->stream));
+    c->in_flight = false;
     return rc;
 }
 

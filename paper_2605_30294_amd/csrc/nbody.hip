@@ -886,11 +886,13 @@ int rafi_nb_seed(rafi_ctx *P, const rafi_nb_job *job, const void *particles, uin
                            static_cast<const NBParticle *>(particles), n);
     RAFI_LAUNCH_CHECK();
     uint64_t total = 0;
-    return round_run(P, nullptr, &total);
+    return rafi_round(P, nullptr, &total);
 }
 
-int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job, uint64_t *round_counts,
-                 uint64_t *sizes)
+namespace {
+// rafi_nb_step without its wait for the rounds' queues; V->settled is recorded
+// behind the last round.
+int nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job, uint64_t *round_counts, uint64_t *sizes)
 {
     if (!P || !V || !Rq || !job_ok(job) || P->S != RAFI_NB_PARTICLE_BYTES || V->S != RAFI_NB_VIRTUAL_BYTES ||
         Rq->S != RAFI_NB_REQUEST_BYTES || P->D != job->n_domains || V->D != job->n_domains ||
@@ -1035,6 +1037,8 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
     uint64_t n2 = 0;
     rc = round_run(V, counts_at(3), &n2);
     if (rc != RAFI_OK) return rc;
+    if (!V->settled) RAFI_HIP_CHECK(hipEventCreateWithFlags(&V->settled, hipEventDisableTiming));
+    RAFI_HIP_CHECK(hipEventRecord(V->settled, s));
     rafi_view(V, &vv);
 
     // 7. forces in chunks (a workgroup per particle tile and chunk), then
@@ -1062,6 +1066,20 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
         sizes[2] = n2;
     }
     return RAFI_OK;
+}
+
+}  // namespace
+
+int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job, uint64_t *round_counts,
+                 uint64_t *sizes)
+{
+    const int rc = nb_step(P, V, Rq, job, round_counts, sizes);
+    if (rc == RAFI_ERR_ARG) return rc;
+    // The rounds end before their scatters do. The queues are whole on return,
+    // for callers on other streams too; the forces may still be running.
+    if (rc == RAFI_OK) RAFI_HIP_CHECK(hipEventSynchronize(V->settled));
+    else (void)hipStreamSynchronize(P->stream);
+    return rc;
 }
 
 }  // extern "C"

@@ -255,7 +255,8 @@ def test_large_tiles_march_with_the_library_exponentials(w):
     ctx = rafi.Context(1, rafi.EA_ITEM_BYTES, n_rays)
     ctx.set_tile_items(1024)
     image = torch.zeros(n_rays, dtype=torch.float32, device=dev)
-    job = rafi.ea_job(vol, (1, 1, 1), rafi.views_to_device(views, dev), 1, w, w, image, c=C32)
+    vdev = rafi.views_to_device(views, dev)
+    job = rafi.ea_job(vol, (1, 1, 1), vdev, 1, w, w, image, c=C32)
     ctx.begin(n_rays)
     ctx.emit_bulk(torch.from_numpy(items).to(dev), torch.zeros(n_rays, dtype=torch.int32, device=dev))
     _, total, _ = ctx.round(counts=False)
