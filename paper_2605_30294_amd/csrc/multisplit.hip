@@ -1101,42 +1101,58 @@ void finish_plan(SplitPlan &p)
     if (p.group_bits) p.bytes += ((uint64_t)p.n_tiles * (uint64_t)p.D * 2 + 255) / 256 * 256;
 }
 
+// Items the per-thread scatter takes (launch_staged, launch_scatter), at most
+// 128 destinations: sizes without staged shapes, and 44 bytes and more up to
+// 64 MiB.
+bool plain_scatter(const SplitPlan &p)
+{
+    const uint32_t nw = p.S / 4;
+    if (nw >= 11) return p.n * (uint64_t)p.S <= (1ull << 26) || (nw != 11 && nw != 12 && nw != 16);
+    return nw == 5 || nw == 7 || nw == 9;
+}
+
 // The grouped histogram: where the automatic scatter shape is one of the
-// small staged ones or the plain one (at most 128 destinations and 256 MiB of
-// items: every context round of the workloads here), a tile's prefix fits 16
-// bits, and the ungrouped table is too large for the one-launch scan. Not where
-// the grouped one is just too large as well: the wavefront a tile gets then
-// costs what the smaller table saves (64 destinations, 1.4 M slots: 26 us
-// grouped, 23 not; 4 M slots: 46 grouped, 49 not).
-// Other shapes read the table by tile. The workspace is smaller than without:
-// 3 (D + 2) bytes of table per tile saved, 2 D for the prefixes.
+// small staged ones (at most 128 destinations and 256 MiB of items), a tile's
+// prefix fits 16 bits, and the ungrouped table is too large for the one-launch
+// scan. Not where the grouped one is just too large as well: the wavefront a
+// tile gets then costs what the smaller table saves (16-byte items, 100
+// destinations, 1.4 M slots: 27.8 us grouped, 25.7 not; up to 30 K entries
+// 0.5% slower, from 50 K on 1 to 2% faster). Not before the
+// plain scatter, which reads the destinations twice and finds them in its XCD's
+// L2 when workgroup t has read tile t before (44-byte items, 100 destinations,
+// 1.4 M slots: 62 us grouped, 51 not). Other shapes read the table by tile.
 bool group_eligible(const SplitPlan &p)
 {
     const uint64_t rows = (uint64_t)p.D + 2, m = rows * ((p.n_tiles + kGroupTiles - 1) / kGroupTiles);
-    return g_split_variant == 0 && p.D <= 128 && p.n * (uint64_t)p.S <= (1ull << 28) &&
-           rows * p.n_tiles > kOneScanMax && (m <= kOneScanMax || m > 2 * kOneScanMax) &&
+    return g_split_variant == 0 && p.D <= 128 && p.n * (uint64_t)p.S <= (1ull << 28) && !plain_scatter(p) &&
+           rows * p.n_tiles > kOneScanMax && (m <= kOneScanMax || m > 3 * kOneScanMax) &&
            (uint64_t)p.tile * (kGroupTiles - 1) < 65536;
 }
 
 // Whether the scatter's workgroups find their run bases and the results
 // themselves. A round of few slots is a chain of launches, each some 5 us for
 // little work, and the scan is one workgroup. The shapes are those of the
-// grouped plans, with tiles below the raw shape's chunk.
+// grouped plans and the plain one, with tiles below the raw shape's chunk.
 //   up to kCountTiles tiles every workgroup counts all destinations, and the
 //     split is one launch: 4 K slots 12.2 us, 15.5 with a histogram launch,
 //     19.0 with histogram and scan; at 16 tiles the count costs what the
 //     launch does;
-//   else every workgroup sums the table's columns: 64 domains, histogram and
-//     scatter of 584 K slots 6 + 14 us for 6 + 12 with a scan of 8 between.
-//     Columns stand for 4 tiles from kSelfPlain entries on (460 K slots 18 us
-//     for 24, 142 K the same, 84 K 15 for 14);
-//   with few destinations a row has many columns: columns of 4 tiles also
-//     beyond 32 loads a thread (1 destination, 2 M slots: 23.5 us for 37);
-//   not when the workgroups' threads make more than kSelfLoads loads one after
-//     another, all workgroups together: 64 destinations, 1 M slots (60 K loads)
-//     18.4 us for 21.6 with a scan, 1.4 M slots (117 K) 26.8 for 23.2.
-constexpr uint32_t kCountTiles = 8;
-constexpr uint64_t kSelfPlain = 1ull << 13, kSelfMax = 1ull << 15, kSelfLoads = 1ull << 16;
+//   else every workgroup sums the table's columns, in turns of 16 loads a
+//     thread, each turn a trip past the L2. Measured over 4- to 64-byte items, 1
+//     to 128 destinations and 9 K to 4 M slots, us with the sums and with a scan:
+//     staged scatters: up to 7 turns where all tiles are on the card at once
+//       (24 bytes, 64 destinations, 492 K slots 20.2 for 21.9), up to 2 where
+//       a second generation of workgroups makes them again (32 bytes, 16
+//       destinations, 1 M slots 24.9 for 27.5; 64 destinations 28.1 for 25.2;
+//       12 bytes, 8 destinations, 1.5 M slots 43.4 for 40.0);
+//     plain scatter, all of it on the card at once: up to 8 turns (44 bytes, 16
+//       destinations, 1 M slots 28.5 for 32.2; 50 destinations, 830 K slots, 13
+//       turns, 38.9 for 34.7).
+//   Columns stand for 4 tiles where that saves turns: before a staged scatter
+//   from kSelfPlain entries or 16 loads a thread on, before the plain one, for
+//   which see group_eligible, up to kPlainGroupTiles tiles only.
+constexpr uint32_t kCountTiles = 8, kPlainGroupTiles = 350, kCus = 256;
+constexpr uint64_t kSelfPlain = 1ull << 13;
 
 void finish_self_plan(SplitPlan &p)
 {
@@ -1150,11 +1166,21 @@ void finish_self_plan(SplitPlan &p)
     uint32_t parts = 256;  // threads that share a row (sum_columns)
     while (parts > 1 && parts * (uint32_t)p.D > 256) parts /= 2;
     parts = std::min(parts, kSumParts);
-    SplitPlan c = p;
-    c.group_bits = c.rows * c.n_tiles > kSelfPlain || c.n_tiles > 32 * parts ? kGroupBits : 0;
-    finish_plan(c);
-    if (c.M > kSelfMax || (uint64_t)c.n_tiles * ((c.n_cols + parts - 1) / parts) > kSelfLoads) return;
-    p = c;
+    auto turns = [&](uint32_t cols) { return ((cols + parts - 1) / parts + 15) / 16; };
+    const uint32_t groups = (p.n_tiles + kGroupTiles - 1) / kGroupTiles;
+    bool group = p.rows * p.n_tiles > kSelfPlain;
+    if (plain_scatter(p)) {
+        group = group && p.n_tiles <= kPlainGroupTiles;
+        if (!group && turns(p.n_tiles) > 8) return;
+    } else {
+        group = group || p.n_tiles > 16 * parts;
+        // workgroups a CU of the shapes that launch_staged takes
+        const uint32_t resident = kCus * (p.S == 16 ? 4 : p.S == 32 ? 3 : 2);
+        const uint32_t most = p.n_tiles <= resident ? 7 : p.n_tiles <= 2 * resident ? 2 : 0;
+        if (turns(group ? groups : p.n_tiles) > most) return;
+    }
+    p.group_bits = group ? kGroupBits : 0;
+    finish_plan(p);
     p.self = kSumTable;
 }
 
