@@ -481,6 +481,7 @@ hist_group_kernel(const int32_t *__restrict__ dest, uint64_t n, int32_t D, uint3
 // unscanned table, column by column (kSumTable), or from the destinations
 // (kCountSlots); workgroup 0 then has no tile and writes the results
 // (self_results).
+enum { kScanned, kGrouped, kSelf };  // which of these, an instance of each kernel for each
 struct RunBases {
     const uint32_t *__restrict__ table;
     const uint16_t *__restrict__ pre;
@@ -489,8 +490,10 @@ struct RunBases {
     {
         return group_bits ? pre[(uint64_t)tile * (uint32_t)D + (uint32_t)e] : 0u;
     }
+    template <int KIND>
     __device__ uint32_t at(uint32_t tile, int32_t e, int32_t D) const
     {
+        if constexpr (KIND == kScanned) return table[(uint64_t)e * n_cols + tile];
         return table[(uint64_t)e * n_cols + (tile >> group_bits)] + in_group(tile, e, D);
     }
 };
@@ -627,10 +630,10 @@ __device__ inline void copy_item(const uint32_t *__restrict__ src, uint32_t *__r
     }
 }
 
-// SELF: bases.self is set. An instance of its own here and in the staged
-// shapes: the code beside the others' cost them 4% (1.67 M x 12-byte items,
-// 45 destinations: 44.4 us, 46.2 with it).
-template <int NW, bool SELF>
+// KIND: where the run bases come from. In one instance the three cost the
+// plain table's splits 4% (1.67 M x 12-byte items, 45 destinations: 44.4 us,
+// 46.2 with them).
+template <int NW, int KIND>
 __global__ void __launch_bounds__(256)
 scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest, uint64_t n,
                int32_t D, int nbits, uint32_t T, RunBases bases, uint32_t *__restrict__ out, uint32_t nw_runtime,
@@ -640,7 +643,7 @@ scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ d
     const uint32_t nw = NW > 0 ? (uint32_t)NW : nw_runtime;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     uint32_t tile = blockIdx.x, own_base = 0;
-    if constexpr (SELF) {
+    if constexpr (KIND == kSelf) {
         if (tile == 0) {
             self_results<256>(bases, dest, D, n, results, cnt);
             return;
@@ -662,7 +665,7 @@ scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ d
     }
     __syncthreads();
     for (int32_t e = tid; e < D; e += 256) {
-        uint32_t run = SELF ? own_base : bases.at(tile, e, D);  // SELF: D <= 128, so e is tid
+        uint32_t run = KIND == kSelf ? own_base : bases.at<KIND>(tile, e, D);  // kSelf: D <= 128, so e is tid
 #pragma unroll
         for (int ww = 0; ww < 4; ++ww) {
             const uint32_t c = cnt[ww * D + e];
@@ -697,14 +700,14 @@ scatter_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ d
 }
 
 // ------------------------------------------------------- pass 3, staged ---
-template <int NW, int R, int W, int OCC, bool DB, bool SELF>
+template <int NW, int R, int W, int OCC, bool DB, int KIND>
 __global__ void __launch_bounds__(64 * W, OCC)
 scatter_staged_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest, uint64_t n,
                       int32_t D, int nbits, uint32_t T, RunBases bases, uint32_t *__restrict__ out, Results results)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     uint32_t tile = blockIdx.x, own_base = 0;
-    if constexpr (SELF) {
+    if constexpr (KIND == kSelf) {
         if (tile == 0) {
             self_results<256>(bases, dest, D, n, results, lds);
             return;
@@ -716,7 +719,7 @@ scatter_staged_kernel(const uint32_t *__restrict__ items, const int32_t *__restr
     const uint64_t tend = min(tstart + T, n);
     dev::staged_scatter_tile<NW, R, W, DB>(
         items, dest, tstart, tend, D, 0, nbits,
-        [&](int32_t e) { return SELF ? own_base : bases.at(tile, e, D); }, out, n, lds);
+        [&](int32_t e) { return KIND == kSelf ? own_base : bases.at<KIND>(tile, e, D); }, out, n, lds);
 }
 
 // One (rounds, waves, workgroups per CU) shape of the staged scatter; it is
@@ -730,17 +733,22 @@ bool try_staged(const SplitPlan &p, const uint32_t *items, const int32_t *dest, 
     int nbits = 1;
     while ((1 << nbits) < p.D) ++nbits;
     constexpr int OCC = (W * BPC + 3) / 4;  // waves per SIMD
-    if (p.self) {
+    if (p.self || p.group_bits) {  // plans for the automatic shapes
         if constexpr (W == 4 && !DB) {
-            if (lds < kSelfLds) return false;
-            hipLaunchKernelGGL((scatter_staged_kernel<NW, R, W, OCC, false, true>), dim3(p.n_tiles + 1), dim3(64 * W),
-                               lds, s, items, dest, p.n, p.D, nbits, p.tile, bases, out, results);
+            if (p.self) {
+                if (lds < kSelfLds) return false;
+                hipLaunchKernelGGL((scatter_staged_kernel<NW, R, W, OCC, false, kSelf>), dim3(p.n_tiles + 1),
+                                   dim3(64 * W), lds, s, items, dest, p.n, p.D, nbits, p.tile, bases, out, results);
+            } else {
+                hipLaunchKernelGGL((scatter_staged_kernel<NW, R, W, OCC, false, kGrouped>), dim3(p.n_tiles),
+                                   dim3(64 * W), lds, s, items, dest, p.n, p.D, nbits, p.tile, bases, out, results);
+            }
             return true;
         }
         return false;
     }
-    hipLaunchKernelGGL((scatter_staged_kernel<NW, R, W, OCC, DB, false>), dim3(p.n_tiles), dim3(64 * W), lds, s, items,
-                       dest, p.n, p.D, nbits, p.tile, bases, out, results);
+    hipLaunchKernelGGL((scatter_staged_kernel<NW, R, W, OCC, DB, kScanned>), dim3(p.n_tiles), dim3(64 * W), lds, s,
+                       items, dest, p.n, p.D, nbits, p.tile, bases, out, results);
     return true;
 }
 
@@ -822,7 +830,7 @@ scatter_line_kernel(const uint32_t *__restrict__ items, const int32_t *__restric
 
 // The wide shape with raw staging (item sizes that are not a multiple of 16
 // bytes): one workgroup per CU, the chunk's bytes in LDS in load order.
-template <int NW, int R, int W>
+template <int NW, int R, int W, int KIND, bool TAIL>
 __global__ void __launch_bounds__(64 * W, (W + 3) / 4)
 scatter_wide_raw_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest, uint64_t n,
                         uint64_t words, int32_t D, int nbits, uint32_t T, RunBases bases,
@@ -832,9 +840,9 @@ scatter_wide_raw_kernel(const uint32_t *__restrict__ items, const int32_t *__res
     const uint64_t tstart = (uint64_t)blockIdx.x * T;
     const uint64_t tend = min(tstart + T, n);
     const uint32_t tile = blockIdx.x;
-    dev::wide_raw_scatter_tile<NW, R, W>(
-        items, dest, tstart, tend, words, D, nbits, [&](int32_t e) { return bases.at(tile, e, D); }, out, n, dummy,
-        lds);
+    dev::wide_raw_scatter_tile<NW, R, W, TAIL>(
+        items, dest, tstart, tend, words, D, nbits, [&](int32_t e) { return bases.at<KIND>(tile, e, D); }, out, n,
+        dummy, lds);
 }
 
 template <int NW, int R, int W>
@@ -847,8 +855,15 @@ bool try_wide_raw(const SplitPlan &p, const uint32_t *items, const int32_t *dest
     if (words < 4) return false;
     int nbits = 1;
     while ((1 << nbits) < p.D) ++nbits;
-    hipLaunchKernelGGL((scatter_wide_raw_kernel<NW, R, W>), dim3(p.n_tiles), dim3(64 * W), lds, s, items, dest, p.n,
-                       words, p.D, nbits, p.tile, bases, out, dummy);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(p.n_tiles), dim3(64 * W), lds, s, items, dest, p.n, words, p.D, nbits, p.tile,
+                           bases, out, dummy);
+    };
+    const bool tail = words % 4 != 0;
+    if (p.group_bits && tail) launch(scatter_wide_raw_kernel<NW, R, W, kGrouped, true>);
+    else if (p.group_bits) launch(scatter_wide_raw_kernel<NW, R, W, kGrouped, false>);
+    else if (tail) launch(scatter_wide_raw_kernel<NW, R, W, kScanned, true>);
+    else launch(scatter_wide_raw_kernel<NW, R, W, kScanned, false>);
     return true;
 }
 
@@ -860,7 +875,7 @@ bool try_wide_raw(const SplitPlan &p, const uint32_t *items, const int32_t *dest
 // into one L2 within the same step and leaves it whole, where chunks far
 // apart in time would each send a partial line to HBM. Every workgroup loads
 // its next chunk (and that chunk's run bases) while it writes the current one.
-template <int NW, int R, int W>
+template <int NW, int R, int W, bool TAIL>
 __global__ void __launch_bounds__(64 * W, (W + 3) / 4)
 scatter_lock_raw_kernel(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest, uint64_t n,
                         uint64_t words, int32_t D, int nbits, uint32_t n_tiles, uint32_t n_chunks,
@@ -872,7 +887,7 @@ scatter_lock_raw_kernel(const uint32_t *__restrict__ items, const int32_t *__res
     const uint32_t x = blockIdx.x % kLockXcds, k = blockIdx.x / kLockXcds;
     const dev::LockChunks<kLockChunk, kLockTile> sched{n, x * kLockTile + k, kLockXcds * kLockTile, n_chunks,
                                                        n_tiles, D, table, pre};
-    dev::wide_raw_scatter<NW, R, W>(items, dest, words, D, nbits, sched, out, n, dummy, lds);
+    dev::wide_raw_scatter<NW, R, W, TAIL>(items, dest, words, D, nbits, sched, out, n, dummy, lds);
 }
 
 template <int NW>
@@ -885,8 +900,12 @@ bool try_lock_raw(const SplitPlan &p, const uint32_t *items, const int32_t *dest
     const uint64_t words = p.n * (uint64_t)NW;  // n >= kLockMinN: at least 4
     int nbits = 1;
     while ((1 << nbits) < p.D) ++nbits;
-    hipLaunchKernelGGL((scatter_lock_raw_kernel<NW, R, W>), dim3(kLockXcds * kLockTile), dim3(64 * W), lds, s,
-                       items, dest, p.n, words, p.D, nbits, p.n_tiles, p.n_chunks, table, pre, out, dummy);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(kLockXcds * kLockTile), dim3(64 * W), lds, s, items, dest, p.n, words, p.D,
+                           nbits, p.n_tiles, p.n_chunks, table, pre, out, dummy);
+    };
+    if (words % 4 != 0) launch(scatter_lock_raw_kernel<NW, R, W, true>);
+    else launch(scatter_lock_raw_kernel<NW, R, W, false>);
     return true;
 }
 
@@ -1065,10 +1084,13 @@ void launch_scatter(const SplitPlan &p, const uint32_t *items, const int32_t *de
     while ((1 << nbits) < p.D) ++nbits;
     const size_t lds = sizeof(uint32_t) * 4 * (size_t)p.D;
     if (p.self)
-        hipLaunchKernelGGL((scatter_kernel<NW, true>), dim3(p.n_tiles + 1), dim3(256), std::max(lds, kSelfLds), s,
+        hipLaunchKernelGGL((scatter_kernel<NW, kSelf>), dim3(p.n_tiles + 1), dim3(256), std::max(lds, kSelfLds), s,
                            items, dest, p.n, p.D, nbits, p.tile, bases, out, p.S / 4, results);
+    else if (p.group_bits)
+        hipLaunchKernelGGL((scatter_kernel<NW, kGrouped>), dim3(p.n_tiles), dim3(256), lds, s, items, dest, p.n, p.D,
+                           nbits, p.tile, bases, out, p.S / 4, results);
     else
-        hipLaunchKernelGGL((scatter_kernel<NW, false>), dim3(p.n_tiles), dim3(256), lds, s, items, dest, p.n, p.D,
+        hipLaunchKernelGGL((scatter_kernel<NW, kScanned>), dim3(p.n_tiles), dim3(256), lds, s, items, dest, p.n, p.D,
                            nbits, p.tile, bases, out, p.S / 4, results);
 }
 
@@ -1113,19 +1135,20 @@ bool plain_scatter(const SplitPlan &p)
 
 // The grouped histogram: where the automatic scatter shape is one of the
 // small staged ones (at most 128 destinations and 256 MiB of items), a tile's
-// prefix fits 16 bits, and the ungrouped table is too large for the one-launch
-// scan. Not where the grouped one is just too large as well: the wavefront a
-// tile gets then costs what the smaller table saves (16-byte items, 100
-// destinations, 1.4 M slots: 27.8 us grouped, 25.7 not; up to 30 K entries
-// 0.5% slower, from 50 K on 1 to 2% faster). Not before the
-// plain scatter, which reads the destinations twice and finds them in its XCD's
-// L2 when workgroup t has read tile t before (44-byte items, 100 destinations,
-// 1.4 M slots: 62 us grouped, 51 not). Other shapes read the table by tile.
+// prefix fits 16 bits, and the one-launch scan takes the grouped table but not
+// the other, with over 24 destinations only up to 1280 tiles (32-byte items,
+// 35 destinations, 1.2 M slots 28.8 us for 29.9, 1.5 M 35.2 for 34.2). Beyond
+// that the wavefront a tile gets and the prefixes' reads cost
+// more than the smaller table saves (16-byte items, 128 destinations, 1.8 M
+// slots: 35.4 us grouped, 33.2 not). Not before the plain scatter, which reads
+// the destinations twice and finds them in its XCD's L2 when workgroup t has
+// read tile t before (44-byte items, 100 destinations, 1.4 M slots: 62 us
+// grouped, 51 not). Other shapes read the table by tile.
 bool group_eligible(const SplitPlan &p)
 {
     const uint64_t rows = (uint64_t)p.D + 2, m = rows * ((p.n_tiles + kGroupTiles - 1) / kGroupTiles);
     return g_split_variant == 0 && p.D <= 128 && p.n * (uint64_t)p.S <= (1ull << 28) && !plain_scatter(p) &&
-           rows * p.n_tiles > kOneScanMax && (m <= kOneScanMax || m > 3 * kOneScanMax) &&
+           rows * p.n_tiles > kOneScanMax && m <= kOneScanMax && (p.n_tiles <= 1280 || p.D <= 24) &&
            (uint64_t)p.tile * (kGroupTiles - 1) < 65536;
 }
 

@@ -993,8 +993,10 @@ struct LockChunks {
 // whole number of 16-byte pieces ends in 1 to 3 words that no piece load may
 // cover: they are staged one by one with the last chunk, so ragged lengths
 // take this path too (16,000,001 x 44 bytes, 1024 Zipf destinations: 0.86 ms
-// with the staged shape they took before, 0.52 ms here).
-template <int NW, int R, int W, typename Sched>
+// with the staged shape they took before, 0.52 ms here). TAIL: there are such
+// words; the test in every chunk costs the others 1% (18.1 M x 24 bytes, 539
+// destinations: 325 us without it, 329 with).
+template <int NW, int R, int W, bool TAIL, typename Sched>
 __device__ inline void wide_raw_scatter(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest,
                                         uint64_t words, int32_t D, int nbits, const Sched &sched,
                                         uint32_t *__restrict__ out, uint64_t out_cap, uint32_t *__restrict__ dummy,
@@ -1066,7 +1068,7 @@ __device__ inline void wide_raw_scatter(const uint32_t *__restrict__ items, cons
         uint16_t rank[R];
         for (int k = tid; k < (W * D + 2) / 2; k += NT) reinterpret_cast<uint32_t *>(cnt)[k] = 0;
         __syncthreads();
-        stage_tail(cbase, cend);  // read after the barriers below
+        if constexpr (TAIL) stage_tail(cbase, cend);  // read after the barriers below
 
         uint16_t *mycnt = cnt + w * D;
 #pragma unroll
@@ -1166,14 +1168,14 @@ __device__ inline void wide_raw_scatter(const uint32_t *__restrict__ items, cons
     }
 }
 
-template <int NW, int R, int W, typename RunBase>
+template <int NW, int R, int W, bool TAIL, typename RunBase>
 __device__ inline void wide_raw_scatter_tile(const uint32_t *__restrict__ items, const int32_t *__restrict__ dest,
                                              uint64_t tstart, uint64_t tend, uint64_t words, int32_t D, int nbits,
                                              RunBase run_base, uint32_t *__restrict__ out, uint64_t out_cap,
                                              uint32_t *__restrict__ dummy, uint32_t *lds)
 {
     const TileChunks<W * 64 * R, RunBase> sched{tstart, tend, run_base};
-    wide_raw_scatter<NW, R, W>(items, dest, words, D, nbits, sched, out, out_cap, dummy, lds);
+    wide_raw_scatter<NW, R, W, TAIL>(items, dest, words, D, nbits, sched, out, out_cap, dummy, lds);
 }
 
 }  // namespace dev
