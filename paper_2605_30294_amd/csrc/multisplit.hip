@@ -1120,7 +1120,18 @@ void finish_plan(SplitPlan &p)
     p.bytes = p.off_part + ((uint64_t)std::max<uint32_t>(p.scan_blocks, 1) * 4 + 255) / 256 * 256;
     p.off_pre = p.bytes;
     if (p.lock) p.bytes += ((uint64_t)p.n_chunks * (uint64_t)p.D * 2 + 255) / 256 * 256;
-    if (p.group_bits) p.bytes += ((uint64_t)p.n_tiles * (uint64_t)p.D * 2 + 255) / 256 * 256;
+    if (p.group_bits) {
+        // The prefixes take the partial sums' place (a grouped table is scanned
+        // in one launch or by the scatter). The size asked for is that of a
+        // column per tile: with the smaller one a workspace made for n slots
+        // would not do for fewer, nor for another scatter shape.
+        p.off_pre = p.off_part;
+        p.bytes = p.off_pre + ((uint64_t)p.n_tiles * (uint64_t)p.D * 2 + 255) / 256 * 256;
+        SplitPlan u = p;
+        u.group_bits = 0;
+        finish_plan(u);
+        p.bytes = std::max(p.bytes, u.bytes);
+    }
 }
 
 // Items the per-thread scatter takes (launch_staged, launch_scatter), at most

@@ -74,6 +74,51 @@ def test_argument_validation_without_device():
     assert L.rafi_split_set_variant(-1) == rafi.ERR_ARG
 
 
+@pytest.mark.parametrize("item_bytes", [4, 12, 32, 44, 48, 64, 20])
+def test_split_workspace_serves_smaller_splits_and_other_shapes(item_bytes):
+    """A workspace asked for once, for a caller's largest split, is enough for
+    every smaller one (up to 4096 tiles of 1024 slots, where the tiles begin
+    to grow) and under every scatter shape: its size is that of a table with a
+    column of n_domains + 2 counts per tile of 1024 slots, the 512-byte head
+    and the scan's partial sums, whatever plan the split takes. Sizes that the
+    lockstep shape takes are left out from 2^21 slots on (it needs more)."""
+    L = rafi.lib()
+    b = C.c_uint64(0)
+
+    def size(n, D):
+        assert L.rafi_multisplit_workspace(n, D, item_bytes, C.byref(b)) == rafi.RAFI_OK
+        return b.value
+
+    def up(x):
+        return -(-x // 256) * 256
+
+    end = (1 << 21) - 1 if item_bytes in (12, 44, 20) else 4096 * 1024
+    sizes = [1, 1024, 1025, 4096, 8192, 8193, 33_000, 126_976, 128_000, 258_049, 507_904, 507_905, 524_288, 525_312,
+             1_000_000, 1_032_192, 1_036_288, 2_031_616, 2_032_640, 3_000_000, end]
+    sizes = sorted({n for n in sizes if n <= end} | {1024 * k for k in range(1, end // 1024, 37)})
+    try:
+        for D in (1, 2, 5, 16, 64, 100, 128, 129, 200):
+            got = []
+            for n in sizes:
+                tiles = -(-n // 1024)
+                table = (D + 2) * tiles
+                want = 512 + up(4 * table) + up(4 * -(-table // 4096))
+                assert size(n, D) == want, (n, D)
+                got.append(want)
+            assert got == sorted(got)
+        for variant in range(1, 17):
+            rafi.split_set_variant(variant)
+            for D in (2, 64, 128):
+                for n in (8192, 126_976, 1_000_000, 2_031_616):
+                    if n <= end:
+                        other = size(n, D)
+                        rafi.split_set_variant(0)
+                        assert size(n, D) == other, (n, D, variant)
+                        rafi.split_set_variant(variant)
+    finally:
+        rafi.split_set_variant(0)
+
+
 def test_dt_capacity_bound():
     """Capacity for delta tracking: 2 slots per visit x (the path + one shadow
     ray per scattering event) per path."""

@@ -317,6 +317,38 @@ def test_split_lockstep_workspace_fallback(orc):
     assert np.array_equal(out[:total].cpu().numpy().view(np.uint32), e_out)
 
 
+@pytest.mark.parametrize("largest,n,D,words", [
+    (128_000, 126_976, 64, 12), (2_032_640, 2_031_616, 64, 8), (525_312, 524_288, 2, 4), (1_036_288, 1_032_192, 128, 8)])
+def test_split_workspace_of_a_larger_split(orc, largest, n, D, words):
+    """One workspace for the caller's largest split, and for a smaller one whose
+    plan has a table column per tile, under the automatic shape and the others
+    that take these items."""
+    dev = device()
+    ws = torch.empty(rafi.multisplit_workspace(largest, D, 4 * words), dtype=torch.uint8, device=dev)
+    rng = np.random.default_rng(n)
+    dest = rng.integers(-1, D, n).astype(np.int32)
+    items = rng.integers(0, 2**31, (n, words)).astype(np.int32)
+    d_items, d_dest = torch.from_numpy(items).to(dev), torch.from_numpy(dest).to(dev)
+    e_out, _, e_off, e_done, _ = orc.multisplit(items, dest, D)
+    total = int(e_off[-1])
+    announce(f"split workspace of {largest} for {n} slots D={D}")
+    out = torch.empty_like(d_items)
+    offsets = torch.empty(D + 1, dtype=torch.int64, device=dev)
+    summary = torch.empty(4, dtype=torch.int64, device=dev)
+    try:
+        for variant in [0] + [v for v in range(1, 17) if words in (4, 8)]:
+            rafi.split_set_variant(variant)
+            out.fill_(-3)
+            rc = rafi.lib().rafi_multisplit(rafi._dptr(d_items), rafi._dptr(d_dest), n, 4 * words, D, rafi._dptr(out),
+                                            rafi._dptr(offsets), rafi._dptr(summary), rafi._dptr(ws), ws.numel(), None)
+            assert rc == 0, variant
+            torch.cuda.synchronize()
+            assert np.array_equal(offsets.cpu().numpy().astype(np.uint64), e_off) and int(summary[1]) == e_done
+            assert np.array_equal(out[:total].cpu().numpy(), e_out), variant
+    finally:
+        rafi.split_set_variant(0)
+
+
 @pytest.mark.parametrize("dist", ["uniform", "zipf"])
 def test_split_full_size_44_bytes(orc, dist):
     """The microbenchmark at the paper's 44-byte ray size: 64M items, 1024
