@@ -508,18 +508,26 @@ int size_workspace(rafi_batch *b)
     }
     const uint32_t parts = (uint32_t)((table + kScanChunk - 1) / kScanChunk);
     if (parts > (uint32_t)kPartMax || table >= (1ull << 32)) return RAFI_ERR_ARG;
+    // A captured round holds these pointers: it goes with them.
+    auto grow = [&](uint32_t *&p, uint64_t words) -> int {
+        uint32_t *q = nullptr;
+        if (hipMalloc(reinterpret_cast<void **>(&q), words * 4) != hipSuccess) {
+            (void)hipGetLastError();
+            return RAFI_ERR_OOM;  // p stays, with its size
+        }
+        free_graph(b);
+        if (p) (void)hipFree(p);
+        p = q;
+        return RAFI_OK;
+    };
     if (table > b->table_cap) {
-        if (b->d_table) (void)hipFree(b->d_table);
-        b->d_table = nullptr;
-        if (hipMalloc(reinterpret_cast<void **>(&b->d_table), std::max<uint64_t>(table, 1) * 4) != hipSuccess)
-            return RAFI_ERR_OOM;
+        const int rc = grow(b->d_table, table);
+        if (rc != RAFI_OK) return rc;
         b->table_cap = table;
     }
     if (parts > b->part_cap) {
-        if (b->d_part) (void)hipFree(b->d_part);
-        b->d_part = nullptr;
-        if (hipMalloc(reinterpret_cast<void **>(&b->d_part), std::max<uint32_t>(parts, 1) * 4) != hipSuccess)
-            return RAFI_ERR_OOM;
+        const int rc = grow(b->d_part, parts);
+        if (rc != RAFI_OK) return rc;
         b->part_cap = parts;
     }
     b->tiles_cap = (uint32_t)tiles;

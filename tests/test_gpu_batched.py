@@ -164,3 +164,27 @@ def test_batched_round_limit():
     torch.cuda.synchronize()
     assert torch.equal(image, want)
     b.close()
+
+
+def test_batched_graph_follows_its_workspace():
+    """A tuning that grows the count table and is then put back: the round
+    captured before held the table that the change freed. The render after it
+    is the first one's, and allocations made in between keep their contents."""
+    dev = device()
+    _, vols, scenes = _small_batch(dev)
+    announce("batched graph and workspace")
+    b = rafi.Batch(scenes, c=C32)
+    image = torch.empty(b.n_rays, dtype=torch.float32, device=dev)
+    b.render(vols, image)
+    want = image.clone()
+    base = dict(split_tile=4096, march_block=256, march_grid=32768, use_graph=True, rounds_per_sync=4)
+    for tile in (1024, 2048):
+        b.set_tuning(**{**base, "split_tile": tile})
+        held = [torch.full((1 << k,), 7, dtype=torch.int32, device=dev) for k in range(4, 14)]
+        b.set_tuning(**base)
+        image.fill_(-7.0)
+        b.render(vols, image)
+        torch.cuda.synchronize()
+        assert torch.equal(image, want)
+        assert all(bool((t == 7).all()) for t in held)
+    b.close()
