@@ -36,7 +36,8 @@ constexpr int kPartMax = 16384;
 
 // summary words (u64)
 // S_ALIVE: the last march left something for another round.
-enum { S_TOTAL = 0, S_DONE, S_BAD, S_TILES, S_TABLE, S_SLOTS, S_ROUNDS, S_ALIVE, S_COUNT };
+// S_MIXED: wavefronts of queue slots listed in `mixed`.
+enum { S_TOTAL = 0, S_DONE, S_BAD, S_TILES, S_TABLE, S_SLOTS, S_ROUNDS, S_ALIVE, S_MIXED, S_COUNT };
 
 struct BatchDev {
     const rafi_ea_scene *scenes;   // [S]
@@ -53,6 +54,7 @@ struct BatchDev {
     unsigned long long *summary;   // [S_COUNT]
     void *items_in, *items_out;    // queues
     int32_t *dest;                 // [cap]
+    uint32_t *mixed;               // [cap / 64, rounded up] wavefronts left to batch_march_lanes_kernel
     int32_t S, Dt;
     uint32_t tile;                 // split tile (slots)
     uint64_t table_cap;
@@ -168,6 +170,7 @@ batch_plan_kernel(BatchDev b)
         b.summary[S_DONE] = 0;
         b.summary[S_BAD] = 0;
         b.summary[S_ALIVE] = 0;
+        b.summary[S_MIXED] = 0;
     }
 }
 
@@ -393,11 +396,24 @@ __device__ inline bool march_slot(const BatchDev &b, const float *__restrict__ v
 // a grid made for it: a grid this size leaves the balance to the hardware's
 // dispatch. 256 scenes, 32.5 M rays, when 1280 workgroups fit: 9.5 ms a render
 // at 2048, 8.2 at 8192, 7.9 at 32768 and beyond.
-constexpr uint32_t kMarchGrid = 32768;
+constexpr uint32_t kMarchGrid = 32768, kMixedGrid = 4096;
 
+// batch_march_kernel is taken where most rays go along z and a domain holds
+// kTurnRays of them or more on average: 256 scenes along z 7.1 ms, 7.8 with the
+// lanes' kernel alone; the same tilted 17.3 and 14.7 (their gathers hide behind
+// each other, not behind more wavefronts); 1024 scenes of 64^2 rays in 64
+// domains (64 a domain) 1.49 and 1.56; 4096 of 16^2 (4 a domain) 3.7 and 2.9.
+constexpr uint64_t kTurnRays = 32;
+
+// A wavefront's 64 slots mostly lie in one domain or two: these are marched one
+// after the other, each with its scene in scalar registers. A wavefront with
+// more of them (short queues, the ends of many small domains) is listed for
+// batch_march_lanes_kernel: in turns, 64 domains take 64 times as long as one.
 // Bound by VALU issue, with the latency of a plane's loads behind it: with the
 // scene in vector registers (95) five wavefronts a SIMD, 7.9 ms a render, with
 // the scene in scalar ones (69) seven, 7.3, held to 64 registers eight, 7.1.
+constexpr int kMarchTurns = 2;
+
 __global__ void __launch_bounds__(512, 8) batch_march_kernel(BatchDev b, const float *__restrict__ volumes, float *__restrict__ image,
                                    uint32_t n_rays)
 {
@@ -405,20 +421,44 @@ __global__ void __launch_bounds__(512, 8) batch_march_kernel(BatchDev b, const f
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
     bool alive = false;
     for (uint64_t i0 = blockIdx.x * (uint64_t)blockDim.x + wave; i0 < n_in; i0 += (uint64_t)gridDim.x * blockDim.x) {
-        // A wavefront's 64 slots mostly lie in one domain: its first slot's.
         int32_t d = wave_last_le(b.offsets, b.Dt, i0);
         const uint32_t lane = threadIdx.x & 63u;
         const uint64_t i = i0 + lane;
         const bool in = i < n_in;
         if (in && i >= b.offsets[d + 1]) d = ea::find_domain(b.offsets, b.Dt, i);
-        // One domain at a time, so that its scene is in scalar registers. The
-        // mask, not the comparison, decides: the compiler would take d for the
-        // equal `one`, and d is per lane.
+        const int32_t before = __shfl_up(d, 1);  // the slots are in domain order
+        if (__popcll(__ballot(in && (lane == 0 || d != before))) > kMarchTurns) {
+            if (lane == 0) b.mixed[atomicAdd(&b.summary[S_MIXED], 1ull)] = (uint32_t)(i0 / 64);
+            continue;
+        }
+        // The mask, not the comparison, decides: the compiler would take d for
+        // the equal `one`, and d is per lane.
         for (uint64_t left = __ballot(in); left;) {
             const int32_t one = __builtin_amdgcn_readlane(d, __ffsll((unsigned long long)left) - 1);
             const uint64_t now = __ballot(in && d == one);
             if (now >> lane & 1u) alive |= march_slot(b, volumes, image, n_rays, one, i);
             left &= ~now;
+        }
+    }
+    if (alive) b.summary[S_ALIVE] = 1;
+}
+
+// The wavefronts that the other kernel listed (all = 0), or all of them: every
+// lane in its own domain.
+__global__ void __launch_bounds__(512) batch_march_lanes_kernel(BatchDev b, const float *__restrict__ volumes, float *__restrict__ image,
+                                   uint32_t n_rays, int all)
+{
+    const uint64_t n_in = b.summary[S_TOTAL];
+    const uint64_t waves = all ? (n_in + 63) / 64 : b.summary[S_MIXED];
+    const uint32_t lane = threadIdx.x & 63u, per = blockDim.x / 64;
+    bool alive = false;
+    for (uint64_t w = blockIdx.x * (uint64_t)per + __builtin_amdgcn_readfirstlane(threadIdx.x / 64); w < waves;
+         w += (uint64_t)gridDim.x * per) {
+        const uint64_t i0 = (all ? w : b.mixed[w]) * 64, i = i0 + lane;
+        int32_t d = wave_last_le(b.offsets, b.Dt, i0);
+        if (i < n_in) {
+            if (i >= b.offsets[d + 1]) d = ea::find_domain(b.offsets, b.Dt, i);
+            alive |= march_slot(b, volumes, image, n_rays, d, i);
         }
     }
     if (alive) b.summary[S_ALIVE] = 1;
@@ -431,7 +471,7 @@ __global__ void __launch_bounds__(512, 8) batch_march_kernel(BatchDev b, const f
 struct rafi_batch {
     hipStream_t stream = nullptr;
     int32_t S = 0, Dt = 0;
-    uint64_t n_rays = 0;
+    uint64_t n_rays = 0, z_rays = 0;  // all, and those of views along z
     float dt = 0.5f, c = 0.025f;
     std::vector<rafi_ea_scene> scenes;
     std::vector<uint32_t> rays_per_scene;
@@ -445,6 +485,7 @@ struct rafi_batch {
     unsigned long long *d_summary = nullptr;
     void *d_buf[2] = {nullptr, nullptr};
     int32_t *d_dest = nullptr;
+    uint32_t *d_mixed = nullptr;
     uint64_t *h_summary = nullptr;
     uint64_t table_cap = 0;
     uint32_t part_cap = 0, tiles_cap = 0;
@@ -479,6 +520,7 @@ BatchDev make_dev(rafi_batch *b)
     d.items_in = b->d_buf[0];
     d.items_out = b->d_buf[1];
     d.dest = b->d_dest;
+    d.mixed = b->d_mixed;
     d.S = b->S;
     d.Dt = b->Dt;
     d.tile = b->tune.split_tile;
@@ -550,8 +592,12 @@ int launch_round(rafi_batch *b, const float *volumes, float *image, hipStream_t 
     hipLaunchKernelGGL(batch_scatter_kernel, dim3(tiles), dim3(64 * kW), lds, st, d, (uint64_t)b->n_rays);
     const uint64_t march = (b->n_rays + b->tune.march_block - 1) / b->tune.march_block;  // a round has no more items
     const uint32_t grid = (uint32_t)std::min<uint64_t>(b->tune.march_grid, std::max<uint64_t>(march, 1));
-    hipLaunchKernelGGL(batch_march_kernel, dim3(grid), dim3(b->tune.march_block), 0, st, d, volumes,
-                       image, (uint32_t)b->n_rays);
+    const bool lanes = 2 * b->z_rays < b->n_rays || b->n_rays < kTurnRays * (uint64_t)b->Dt;
+    if (!lanes)
+        hipLaunchKernelGGL(batch_march_kernel, dim3(grid), dim3(b->tune.march_block), 0, st, d, volumes, image,
+                           (uint32_t)b->n_rays);
+    hipLaunchKernelGGL(batch_march_lanes_kernel, dim3(lanes ? grid : std::min(grid, kMixedGrid)),
+                       dim3(b->tune.march_block), 0, st, d, volumes, image, (uint32_t)b->n_rays, lanes ? 1 : 0);
     RAFI_LAUNCH_CHECK();
     return RAFI_OK;
 }
@@ -599,7 +645,7 @@ void destroy_batch(rafi_batch *b)
     (void)hipStreamSynchronize(b->stream);
     free_graph(b);
     void *ptrs[] = {b->d_scenes, b->d_dom_scene, b->d_scene_dom, b->d_scene_ray, b->d_offsets, b->d_dom_count,
-                    b->d_seg, b->d_table, b->d_part, b->d_summary, b->d_buf[0], b->d_buf[1], b->d_dest};
+                    b->d_seg, b->d_table, b->d_part, b->d_summary, b->d_buf[0], b->d_buf[1], b->d_dest, b->d_mixed};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (b->h_summary) (void)hipHostFree(b->h_summary);
@@ -619,7 +665,7 @@ int rafi_batch_create(rafi_ea_scene *scenes, int32_t n_scenes, float dt, float c
     *out = nullptr;
     std::vector<int32_t> dom_scene, scene_dom(n_scenes + 1), scene_ray_v;
     std::vector<uint32_t> scene_ray(n_scenes + 1), rays(n_scenes);
-    uint64_t R = 0;
+    uint64_t R = 0, z_rays = 0;
     int32_t Dt = 0;
     for (int32_t s = 0; s < n_scenes; ++s) {
         rafi_ea_scene &sc = scenes[s];
@@ -636,6 +682,7 @@ int rafi_batch_create(rafi_ea_scene *scenes, int32_t n_scenes, float dt, float c
         scene_dom[s] = Dt;
         rays[s] = (uint32_t)((uint64_t)sc.view.width * sc.view.height);
         R += rays[s];
+        if (sc.view.dir[0] == 0.0f && sc.view.dir[1] == 0.0f) z_rays += rays[s];
         for (int32_t k = 0; k < D; ++k) dom_scene.push_back(s);
         Dt += D;
         if (R >= (1ull << 31)) return RAFI_ERR_ARG;
@@ -648,6 +695,7 @@ int rafi_batch_create(rafi_ea_scene *scenes, int32_t n_scenes, float dt, float c
     b->S = n_scenes;
     b->Dt = Dt;
     b->n_rays = R;
+    b->z_rays = z_rays;
     b->dt = dt;
     b->c = c;
     b->scenes.assign(scenes, scenes + n_scenes);
@@ -664,6 +712,7 @@ int rafi_batch_create(rafi_ea_scene *scenes, int32_t n_scenes, float dt, float c
               hipMalloc(&b->d_buf[0], cap * RAFI_EA_ITEM_BYTES) == hipSuccess &&
               hipMalloc(&b->d_buf[1], cap * RAFI_EA_ITEM_BYTES) == hipSuccess &&
               hipMalloc(reinterpret_cast<void **>(&b->d_dest), cap * sizeof(int32_t)) == hipSuccess &&
+              hipMalloc(reinterpret_cast<void **>(&b->d_mixed), (cap + 63) / 64 * sizeof(uint32_t)) == hipSuccess &&
               hipHostMalloc(reinterpret_cast<void **>(&b->h_summary), sizeof(uint64_t) * S_COUNT,
                             hipHostMallocDefault) == hipSuccess;
     int rc = ok ? RAFI_OK : RAFI_ERR_OOM;

@@ -188,3 +188,36 @@ def test_batched_graph_follows_its_workspace():
         assert torch.equal(image, want)
         assert all(bool((t == 7).all()) for t in held)
     b.close()
+
+
+@pytest.mark.parametrize("kind", ["along z", "tilted", "thumbnails"])
+def test_batched_march_kernels(kind):
+    """Two large scenes and thirty of 5 x 5 to 6 x 6 rays over 64 bricks, whose
+    wavefronts hold the slots of up to a dozen domains: along z the wavefronts of
+    one or two domains and the listed others, tilted or without the large scenes
+    every lane in its own domain. The plain renders' bits, twice (graph replay),
+    and with the fewest workgroups."""
+    dev = device()
+    rng = np.random.default_rng(8)
+    sizes = ([] if kind == "thumbnails" else [(32, (1, 2, 1), 311), (24, (2, 1, 3), 290)]) + \
+        [(16, (4, 4, 4), 5 + i % 2) for i in range(30)]
+    vols, scenes, off = [], [], 0
+    for i, (n, grid, w) in enumerate(sizes):
+        vols.append(torch.from_numpy(rng.random(n ** 3).astype(np.float32)).to(dev))
+        tilt = i % 3 == 1 if kind == "along z" and i > 1 else kind != "along z"
+        view = W.random_views(1, n, w, w, seed=70 + i)[0] if tilt else W.plusz_view(n, w, w)[0]
+        scenes.append((n, grid, view, off))
+        off += n ** 3
+    vols = torch.cat(vols)
+    announce(f"batched march {kind}")
+    want, want_rounds = _plain_images(vols, scenes)
+    b = rafi.Batch(scenes, c=C32)
+    image = torch.full((b.n_rays,), -7.0, dtype=torch.float32, device=dev)
+    for k in range(3):
+        if k == 2:
+            b.set_tuning(march_block=64, march_grid=1)
+        image.fill_(-7.0)
+        assert b.render(vols, image) == want_rounds
+        torch.cuda.synchronize()
+        assert torch.equal(image, want)
+    b.close()
