@@ -541,7 +541,7 @@ class Batch:
         except Exception:
             pass
 
-    def set_tuning(self, split_tile=4096, march_block=256, march_grid=2048, use_graph=True, rounds_per_sync=4):
+    def set_tuning(self, split_tile=4096, march_block=256, march_grid=32768, use_graph=True, rounds_per_sync=4):
         t = BatchTuning(split_tile, march_block, march_grid, int(use_graph), rounds_per_sync)
         _check(lib().rafi_batch_set_tuning(self._h, C.byref(t)), "rafi_batch_set_tuning")
 

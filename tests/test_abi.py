@@ -119,6 +119,18 @@ def test_split_workspace_serves_smaller_splits_and_other_shapes(item_bytes):
         rafi.split_set_variant(0)
 
 
+def test_batch_tuning_defaults_are_the_librarys():
+    """Batch.set_tuning fills in what a caller leaves out: a call that changes
+    one field must not move the others from the library's defaults, which the
+    header states."""
+    import inspect
+    text = open(os.path.join(ROOT, "include", "rafi.h")).read()
+    struct = text[text.index("typedef struct rafi_batch_tuning {"):text.index("} rafi_batch_tuning;")]
+    stated = {m.group(1): int(m.group(2)) for m in re.finditer(r"(\w+);\s*/\*[^*]*\(default (\d+)\)", struct)}
+    given = {k: int(p.default) for k, p in inspect.signature(rafi.Batch.set_tuning).parameters.items() if k != "self"}
+    assert len(stated) == 5 and given == stated
+
+
 def test_dt_capacity_bound():
     """Capacity for delta tracking: 2 slots per visit x (the path + one shadow
     ray per scattering event) per path."""
