@@ -742,11 +742,16 @@ int cu_count(int *cus)
 
 uint32_t n_rays_of(const rafi_ea_job *j) { return (uint32_t)((uint64_t)j->n_views * j->width * j->height); }
 
-// The brick kernel is taken when every CU gets at least 1536 rays: below that
-// the bricks' loads and the longest chords of a part-filled batch cost more
-// than the gathers (64-view render of 128^3: all launches brick 1.77 ms, from
-// 100 K rays 1.72, from 400 K 1.645, never 2.26).
-constexpr uint64_t kBrickRaysPerCu = 1536;
+// The brick kernel is taken when a segment holds 1536 rays or more on average:
+// the part of a workgroup's slice that lies in one brick, of which there are at
+// most the workgroups' number and the bricks' together. Below that the bricks'
+// loads and barriers, and the longest chords of a part-filled batch, cost more
+// than the gathers. 64-view render of 128^3 in 64 bricks: all launches brick 1.77
+// ms, from 100 K rays 1.72, from 400 K 1.645, never 2.26. Launches of 0.5 to 2 M
+// rays over 64 to 8000 bricks, us brick and gather: 2.0 M in 512 bricks 143 and
+// 230 (2700 rays a segment), in 1024 bricks 1.9 M 207 and 166 (1480), in 8000
+// 0.49 M 590 and 53 (60).
+constexpr uint64_t kBrickRays = 1536;
 
 // One march launch over the view's n_in queued rays (an upper bound is enough).
 template <bool kLib>
@@ -754,7 +759,8 @@ void launch_march_as(const rafi_device_view &v, const rafi_ea_job *job, int cus,
 {
     if (!v.n_in) return;
     const size_t lds = region_bytes(job) + kOrderBytes;
-    if (job->n <= ea::kSmallN && v.n_in >= kBrickRaysPerCu * cus && lds + kBrickStatic <= max_lds_bytes())
+    const uint64_t segments = (uint64_t)cus + (uint64_t)v.n_domains;
+    if (job->n <= ea::kSmallN && v.n_in >= kBrickRays * segments && lds + kBrickStatic <= max_lds_bytes())
         hipLaunchKernelGGL(march_brick_kernel<kLib>, dim3(cus), dim3(kBrickThreads), lds, s, v, *job,
                            n_rays_of(job));
     else
