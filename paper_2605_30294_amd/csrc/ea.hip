@@ -624,10 +624,11 @@ __device__ inline void bwd_ray(const rafi_device_view &view, const rafi_ea_job &
 // through the brick accumulating into it, then add its non-zero entries to
 // the global gradient. Rays go through in batches of kBrickBatch ordered by
 // the samples they have left in the brick; ordered = 0: in queue order, where
-// the LDS has no room for the order.
+// the LDS has no room for the order; order = nullptr: by a fixed stride, where it
+// has none beside the region (8 x 62 x 62 voxels and their rim).
 __device__ inline void bwd_segment(const rafi_device_view &view, const rafi_ea_job &job,
                                    const float *__restrict__ grad_image, float *__restrict__ grad, uint32_t n_rays,
-                                   int32_t d, uint64_t first, uint64_t last, int ordered, float *gl, BrickOrder &order)
+                                   int32_t d, uint64_t first, uint64_t last, int ordered, float *gl, BrickOrder *order)
 {
     const Geo g = job_geo(job);
     const Box box = ea::box_of(d, g);
@@ -637,10 +638,17 @@ __device__ inline void bwd_segment(const rafi_device_view &view, const rafi_ea_j
     for (int32_t k = threadIdx.x; k < nl; k += kBrickThreads) gl[k] = 0.0f;
     uint16_t *s_idx = reinterpret_cast<uint16_t *>(gl + nl);
     const float per_key = (float)kBrickKeys * job.dt / (float)(g.b0 + g.b1 + g.b2);
+    if (!order) {
+        __syncthreads();
+        for (uint64_t i = first + threadIdx.x; i < last; i += kBrickThreads)
+            bwd_ray(view, job, grad_image, n_rays, d, g, box, r, i, gl);
+        __syncthreads();
+        first = last;
+    }
     for (uint64_t i = first; i < last; i += kBrickBatch) {
         const uint32_t m = (uint32_t)min((uint64_t)kBrickBatch, last - i);
         if (ordered) {
-            order_batch(order, s_idx, m, per_key, [&](uint32_t q) {
+            order_batch(*order, s_idx, m, per_key, [&](uint32_t q) {
                 const Item it = static_cast<const Item *>(view.in_items)[i + q];
                 if ((uint32_t)it.ray >= n_rays) return 0.0f;
                 float org[3], dir[3];
@@ -649,10 +657,10 @@ __device__ inline void bwd_segment(const rafi_device_view &view, const rafi_ea_j
                 return (float)it.k - fmaxf(ea::entry_estimate(box, org, dir, job.dt), 0.0f);
             });
         } else {
-            if (threadIdx.x == 0) order.next = 0;
+            if (threadIdx.x == 0) order->next = 0;
             __syncthreads();
         }
-        for (uint32_t c; (c = next_places(order)) < m;)
+        for (uint32_t c; (c = next_places(*order)) < m;)
             if (c + lane < m)
                 bwd_ray(view, job, grad_image, n_rays, d, g, box, r, i + (ordered ? s_idx[c + lane] : c + lane), gl);
         __syncthreads();  // the order is reused, and after the last batch the region is complete
@@ -665,28 +673,39 @@ __device__ inline void bwd_segment(const rafi_device_view &view, const rafi_ea_j
     __syncthreads();  // the region is reused by the next segment
 }
 
+// The brick's order outside the dynamic LDS, or none (kOrder = false).
+template <bool kOrder>
+__device__ inline BrickOrder *brick_order()
+{
+    if constexpr (kOrder) {
+        __shared__ BrickOrder order;
+        return &order;
+    }
+    return nullptr;
+}
+
 // One workgroup per domain-pure tile of the input queue.
+template <bool kOrder>
 __global__ void __launch_bounds__(kBrickThreads)
 bwd_march_lds_kernel(rafi_device_view view, rafi_ea_job job, const float *__restrict__ grad_image,
                      float *__restrict__ grad, uint32_t n_rays, int ordered)
 {
     extern __shared__ float gl[];
-    __shared__ BrickOrder order;
     uint64_t tb, te;
     const int32_t d = rafi_tile(view, rafi_xcd_block(blockIdx.x, gridDim.x), &tb, &te);
-    bwd_segment(view, job, grad_image, grad, n_rays, d, tb, te, ordered, gl, order);
+    bwd_segment(view, job, grad_image, grad, n_rays, d, tb, te, ordered, gl, brick_order<kOrder>());
 }
 
 // One workgroup per CU, each taking an equal contiguous slice of the queue
 // and working through the brick segments it spans (usually one or two), so
 // every CU is busy for the whole launch and the gradient region is flushed
 // about once per workgroup.
+template <bool kOrder>
 __global__ void __launch_bounds__(kBrickThreads)
 bwd_march_range_kernel(rafi_device_view view, rafi_ea_job job, const float *__restrict__ grad_image,
                        float *__restrict__ grad, uint32_t n_rays, int ordered)
 {
     extern __shared__ float gl[];
-    __shared__ BrickOrder order;
     const uint64_t w = rafi_xcd_block(blockIdx.x, gridDim.x);
     const uint64_t n = rafi_queue_length(view);
     uint64_t i = n * w / gridDim.x;
@@ -694,7 +713,7 @@ bwd_march_range_kernel(rafi_device_view view, rafi_ea_job job, const float *__re
     while (i < end) {
         const int32_t d = ea::find_domain(view.in_offsets, view.n_domains, i);
         const uint64_t seg_end = min(end, view.in_offsets[d + 1]);
-        bwd_segment(view, job, grad_image, grad, n_rays, d, i, seg_end, ordered, gl, order);
+        bwd_segment(view, job, grad_image, grad, n_rays, d, i, seg_end, ordered, gl, brick_order<kOrder>());
         i = seg_end;
     }
 }
@@ -846,7 +865,7 @@ int rafi_ea_backward(rafi_ctx *c, const rafi_ea_job *job, const float *grad_imag
     // LDS privatisation when the brick's region fits a workgroup's LDS
     const size_t room = max_lds_bytes(), need = region_bytes(job) + kBrickStatic;
     // (a brick that fits, of at most 8192, makes n < 690: the 32-bit cell index)
-    const bool use_lds = need <= room && job->n <= ea::kSmallN;
+    const bool use_lds = region_bytes(job) <= room && job->n <= ea::kSmallN, alone = need > room;
     const int ordered = need + kOrderBytes <= room;
     const size_t lds = region_bytes(job) + (ordered ? kOrderBytes : 0);
     int cus = 0;
@@ -863,8 +882,9 @@ int rafi_ea_backward(rafi_ctx *c, const rafi_ea_job *job, const float *grad_imag
             if (r >= max_rounds) { rc = RAFI_ERR_MAX_ROUNDS; break; }
             rafi_view(c, &v);
             const int ph = prof_domain_begin(c);
-            hipLaunchKernelGGL(bwd_march_lds_kernel, dim3(v.n_tiles), dim3(kBrickThreads), lds, c->stream, v, *job,
-                               grad_image, grad_volume, (uint32_t)rays, ordered);
+            hipLaunchKernelGGL(alone ? bwd_march_lds_kernel<false> : bwd_march_lds_kernel<true>, dim3(v.n_tiles),
+                               dim3(kBrickThreads), lds, c->stream, v, *job, grad_image, grad_volume, (uint32_t)rays,
+                               ordered);
             prof_domain_end(c, ph);
             rc = hipGetLastError() == hipSuccess ? RAFI_OK : RAFI_ERR_HIP;
             if (rc != RAFI_OK) break;
@@ -888,8 +908,9 @@ int rafi_ea_backward(rafi_ctx *c, const rafi_ea_job *job, const float *grad_imag
             // the 100 K rays of round 9 241 us in 100 workgroups, 229 in 256)
             const uint64_t want = (bound + 255) / 256;
             const uint32_t blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, cus));
-            hipLaunchKernelGGL(bwd_march_range_kernel, dim3(blocks), dim3(kBrickThreads), lds, c->stream, lv, *job,
-                               grad_image, grad_volume, (uint32_t)rays, ordered);
+            hipLaunchKernelGGL(alone ? bwd_march_range_kernel<false> : bwd_march_range_kernel<true>, dim3(blocks),
+                               dim3(kBrickThreads), lds, c->stream, lv, *job, grad_image, grad_volume, (uint32_t)rays,
+                               ordered);
         } else if (bound) {
             hipLaunchKernelGGL(bwd_march_kernel, dim3((uint32_t)((bound + 255) / 256)), dim3(256), 0, c->stream,
                                lv, *job, grad_image, grad_volume, (uint32_t)rays);

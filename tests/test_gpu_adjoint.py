@@ -122,6 +122,23 @@ def test_gradient_cell_walk(orc, n, grid, dt):
     assert _rel_l2(g, g64) <= 1e-5, _rel_l2(g, g64)
 
 
+@pytest.mark.parametrize("bwd_tile", [0, 512])
+def test_gradient_region_that_fills_the_lds(orc, bwd_tile):
+    """Bricks of 8 x 62 x 62 voxels: with their rim 10 x 64 x 64 floats, all of
+    a workgroup's LDS, which takes the gradient region as before with nothing
+    beside it. Within 1e-5 (relative L2) of the float64 oracle."""
+    dev = device()
+    n, grid, w = 248, (31, 4, 4), 40
+    vol = torch.from_numpy(W.blob_volume(n, 68)).to(dev).requires_grad_(True)
+    views = W.random_views(2, n, w, w, seed=69)
+    announce(f"adjoint full LDS bwd_tile={bwd_tile}")
+    img = rafi.ea_render_differentiable(vol, grid, views, c=C32, bwd_tile_items=bwd_tile)
+    (img ** 2).sum().backward()
+    g = vol.grad.cpu().numpy().astype(np.float64)
+    _, g64, _ = orc.ea_loss_grad(vol.detach().cpu().numpy(), grid, views, np.zeros(img.numel()), c=C32)
+    assert _rel_l2(g, g64) <= 1e-5, _rel_l2(g, g64)
+
+
 def test_backward_replays_reversed_visits():
     dev = device()
     n, grid = 64, (4, 4, 4)
