@@ -169,7 +169,7 @@ void prof_domain_end(rafi_ctx *c, int h)
 
 int round_enqueue(rafi_ctx *c, bool want_counts)
 {
-    const SplitPlan p = split_plan(c->n_slots, c->D, c->S);
+    const SplitPlan p = split_plan(c->n_slots, c->D, c->S, true, true);
     if (p.bytes > c->ws_bytes) return RAFI_ERR_STATE;
     SplitEvents ev;
     const SplitEvents *evp = nullptr;

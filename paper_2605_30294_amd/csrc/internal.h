@@ -67,8 +67,9 @@ struct SplitPlan {
 };
 
 // allow_lock: the plan may use the lockstep scatter (its workspace grows by
-// 2 bytes per chunk and destination).
-SplitPlan split_plan(uint64_t n, int32_t D, uint32_t S, bool allow_lock = true);
+// 2 bytes per chunk and destination). round: the plan of a context's round, whose
+// host waits for its launches.
+SplitPlan split_plan(uint64_t n, int32_t D, uint32_t S, bool allow_lock = true, bool round = false);
 // Select the staged scatter shape (0 = automatic, 1..17 = fixed shapes).
 int split_set_variant(int v);
 // A plan whose workspace covers every n <= cap.

@@ -1121,12 +1121,11 @@ void finish_plan(SplitPlan &p)
     p.off_pre = p.bytes;
     if (p.lock) p.bytes += ((uint64_t)p.n_chunks * (uint64_t)p.D * 2 + 255) / 256 * 256;
     if (p.group_bits) {
-        // The prefixes take the partial sums' place (a grouped table is scanned
-        // in one launch or by the scatter). The size asked for is that of a
-        // column per tile: with the smaller one a workspace made for n slots
-        // would not do for fewer, nor for another scatter shape.
-        p.off_pre = p.off_part;
-        p.bytes = p.off_pre + ((uint64_t)p.n_tiles * (uint64_t)p.D * 2 + 255) / 256 * 256;
+        // 3 (D + 2) bytes of table per tile are saved, 2 D go to the prefixes.
+        // The size asked for is that of a column per tile all the same: with
+        // the smaller one a workspace made for n slots would not do for fewer,
+        // nor for another scatter shape.
+        p.bytes += ((uint64_t)p.n_tiles * (uint64_t)p.D * 2 + 255) / 256 * 256;
         SplitPlan u = p;
         u.group_bits = 0;
         finish_plan(u);
@@ -1144,51 +1143,67 @@ bool plain_scatter(const SplitPlan &p)
     return nw == 5 || nw == 7 || nw == 9;
 }
 
+// What a launch costs besides its work. A context's round waits on the host
+// for its results: a launch more is 3 to 5 us more, and its destinations come in
+// long runs. Stateless splits are queued ahead of the card, where only the
+// kernels' times count. So the two differ in where fewer launches with more
+// work in them pay (a round of 1 M slots of 48 bytes over 64 destinations 131 us
+// in two launches, 147 in five; the split alone, queued, 42 and 37).
+
 // The grouped histogram: where the automatic scatter shape is one of the
-// small staged ones (at most 128 destinations and 256 MiB of items), a tile's
-// prefix fits 16 bits, and the one-launch scan takes the grouped table but not
-// the other, with over 24 destinations only up to 1280 tiles (32-byte items,
-// 35 destinations, 1.2 M slots 28.8 us for 29.9, 1.5 M 35.2 for 34.2). Beyond
-// that the wavefront a tile gets and the prefixes' reads cost
-// more than the smaller table saves (16-byte items, 128 destinations, 1.8 M
-// slots: 35.4 us grouped, 33.2 not). Not before the plain scatter, which reads
-// the destinations twice and finds them in its XCD's L2 when workgroup t has
-// read tile t before (44-byte items, 100 destinations, 1.4 M slots: 62 us
-// grouped, 51 not). Other shapes read the table by tile.
-bool group_eligible(const SplitPlan &p)
+// small staged ones or the plain one (at most 128 destinations and 256 MiB of
+// items), a tile's prefix fits 16 bits, and the one-launch scan takes the grouped
+// table but not the other. Other shapes read the table by tile.
+// Stateless, with over 24 destinations only up to 1280 tiles (32-byte items, 35
+// destinations, 1.2 M slots 28.8 us for 29.9, 1.5 M 35.2 for 34.2), and not before
+// the plain scatter, which reads the destinations twice and finds them in its
+// XCD's L2 when workgroup t has read tile t before (44-byte items, 100
+// destinations, 1.4 M slots: 62 us grouped, 51 not).
+// Rounds also where both tables are too large by far, not where the grouped one is
+// just too large as well: the wavefront a tile gets then costs what the smaller
+// table saves (64 destinations, 1.4 M slots: 26 us grouped, 23 not; 4 M slots: 46
+// grouped, 49 not).
+bool group_eligible(const SplitPlan &p, bool round)
 {
     const uint64_t rows = (uint64_t)p.D + 2, m = rows * ((p.n_tiles + kGroupTiles - 1) / kGroupTiles);
-    return g_split_variant == 0 && p.D <= 128 && p.n * (uint64_t)p.S <= (1ull << 28) && !plain_scatter(p) &&
-           rows * p.n_tiles > kOneScanMax && m <= kOneScanMax && (p.n_tiles <= 1280 || p.D <= 24) &&
-           (uint64_t)p.tile * (kGroupTiles - 1) < 65536;
+    if (g_split_variant != 0 || p.D > 128 || p.n * (uint64_t)p.S > (1ull << 28) || rows * p.n_tiles <= kOneScanMax ||
+        (uint64_t)p.tile * (kGroupTiles - 1) >= 65536)
+        return false;
+    if (round) return m <= kOneScanMax || m > 2 * kOneScanMax;
+    return m <= kOneScanMax && !plain_scatter(p) && (p.n_tiles <= 1280 || p.D <= 24);
 }
 
 // Whether the scatter's workgroups find their run bases and the results
 // themselves. A round of few slots is a chain of launches, each some 5 us for
 // little work, and the scan is one workgroup. The shapes are those of the
-// grouped plans and the plain one, with tiles below the raw shape's chunk.
+// grouped plans, with tiles below the raw shape's chunk.
 //   up to kCountTiles tiles every workgroup counts all destinations, and the
 //     split is one launch: 4 K slots 12.2 us, 15.5 with a histogram launch,
 //     19.0 with histogram and scan; at 16 tiles the count costs what the
 //     launch does;
 //   else every workgroup sums the table's columns, in turns of 16 loads a
-//     thread, each turn a trip past the L2. Measured over 4- to 64-byte items, 1
-//     to 128 destinations and 9 K to 4 M slots, us with the sums and with a scan:
-//     staged scatters: up to 7 turns where all tiles are on the card at once
-//       (24 bytes, 64 destinations, 492 K slots 20.2 for 21.9), up to 2 where
-//       a second generation of workgroups makes them again (32 bytes, 16
-//       destinations, 1 M slots 24.9 for 27.5; 64 destinations 28.1 for 25.2;
-//       12 bytes, 8 destinations, 1.5 M slots 43.4 for 40.0);
-//     plain scatter, all of it on the card at once: up to 8 turns (44 bytes, 16
-//       destinations, 1 M slots 28.5 for 32.2; 50 destinations, 830 K slots, 13
-//       turns, 38.9 for 34.7).
-//   Columns stand for 4 tiles where that saves turns: before a staged scatter
-//   from kSelfPlain entries or 16 loads a thread on, before the plain one, for
-//   which see group_eligible, up to kPlainGroupTiles tiles only.
+//     thread, each turn a trip past the L2.
+// Rounds: not when the workgroups' threads make more than kSelfLoads loads one
+//   after another, all workgroups together: 64 destinations, 1 M slots (60 K
+//   loads) 18.4 us for 21.6 with a scan, 1.4 M slots (117 K) 26.8 for 23.2.
+//   Columns stand for 4 tiles from kSelfPlain entries or 32 loads a thread on
+//   (460 K slots 18 us for 24; 1 destination, 2 M slots 23.5 for 37).
+// Stateless, measured over 4- to 64-byte items, 1 to 128 destinations and 9 K to
+//   4 M slots, us with the sums and with a scan:
+//   staged scatters: up to 7 turns where all tiles are on the card at once (24
+//     bytes, 64 destinations, 492 K slots 20.2 for 21.9), up to 2 where a
+//     second generation of workgroups makes them again (32 bytes, 16
+//     destinations, 1 M slots 24.9 for 27.5; 64 destinations 28.1 for 25.2; 12
+//     bytes, 8 destinations, 1.5 M slots 43.4 for 40.0). Columns stand for 4
+//     tiles from kSelfPlain entries or 16 loads a thread on;
+//   plain scatter, all of it on the card at once: up to 8 turns (44 bytes, 16
+//     destinations, 1 M slots 28.5 for 32.2; 50 destinations, 830 K slots, 13
+//     turns, 38.9 for 34.7). Columns stand for 4 tiles from kSelfPlain entries
+//     on, up to kPlainGroupTiles tiles (see group_eligible).
 constexpr uint32_t kCountTiles = 8, kPlainGroupTiles = 350, kCus = 256;
-constexpr uint64_t kSelfPlain = 1ull << 13;
+constexpr uint64_t kSelfPlain = 1ull << 13, kSelfMax = 1ull << 15, kSelfLoads = 1ull << 16;
 
-void finish_self_plan(SplitPlan &p)
+void finish_self_plan(SplitPlan &p, bool round)
 {
     if (g_split_variant != 0 || p.D > kSelfD || p.n * (uint64_t)p.S > (1ull << 28) || p.tile >= 8 * 64 * 4 ||
         p.n_tiles == 0)
@@ -1200,21 +1215,25 @@ void finish_self_plan(SplitPlan &p)
     uint32_t parts = 256;  // threads that share a row (sum_columns)
     while (parts > 1 && parts * (uint32_t)p.D > 256) parts /= 2;
     parts = std::min(parts, kSumParts);
-    auto turns = [&](uint32_t cols) { return ((cols + parts - 1) / parts + 15) / 16; };
-    const uint32_t groups = (p.n_tiles + kGroupTiles - 1) / kGroupTiles;
+    const bool plain = plain_scatter(p);
     bool group = p.rows * p.n_tiles > kSelfPlain;
-    if (plain_scatter(p)) {
-        group = group && p.n_tiles <= kPlainGroupTiles;
-        if (!group && turns(p.n_tiles) > 8) return;
+    if (round) group = group || p.n_tiles > 32 * parts;
+    else if (plain) group = group && p.n_tiles <= kPlainGroupTiles;
+    else group = group || p.n_tiles > 16 * parts;
+    SplitPlan c = p;
+    c.group_bits = group ? kGroupBits : 0;
+    finish_plan(c);
+    const uint32_t loads = (c.n_cols + parts - 1) / parts, turns = (loads + 15) / 16;
+    if (round) {
+        if (c.M > kSelfMax || (uint64_t)c.n_tiles * loads > kSelfLoads) return;
+    } else if (plain) {
+        if (!group && turns > 8) return;
     } else {
-        group = group || p.n_tiles > 16 * parts;
         // workgroups a CU of the shapes that launch_staged takes
         const uint32_t resident = kCus * (p.S == 16 ? 4 : p.S == 32 ? 3 : 2);
-        const uint32_t most = p.n_tiles <= resident ? 7 : p.n_tiles <= 2 * resident ? 2 : 0;
-        if (turns(group ? groups : p.n_tiles) > most) return;
+        if (turns > (c.n_tiles <= resident ? 7u : c.n_tiles <= 2 * resident ? 2u : 0u)) return;
     }
-    p.group_bits = group ? kGroupBits : 0;
-    finish_plan(p);
+    p = c;
     p.self = kSumTable;
 }
 
@@ -1254,7 +1273,7 @@ int split_set_variant(int v)
     return RAFI_OK;
 }
 
-SplitPlan split_plan(uint64_t n, int32_t D, uint32_t S, bool allow_lock)
+SplitPlan split_plan(uint64_t n, int32_t D, uint32_t S, bool allow_lock, bool round)
 {
     if (allow_lock && (g_split_variant == 0 || g_split_variant == 17) && lock_eligible(n, D, S))
         return lock_plan(n, D, S);
@@ -1266,9 +1285,9 @@ SplitPlan split_plan(uint64_t n, int32_t D, uint32_t S, bool allow_lock)
     t = (t + 1023) / 1024 * 1024;
     p.tile = (uint32_t)t;
     p.n_tiles = (uint32_t)((n + t - 1) / t);
-    if (group_eligible(p)) p.group_bits = kGroupBits;
+    if (group_eligible(p, round)) p.group_bits = kGroupBits;
     finish_plan(p);
-    finish_self_plan(p);
+    finish_self_plan(p, round);
     return p;
 }
 
