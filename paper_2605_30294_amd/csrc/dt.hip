@@ -93,23 +93,26 @@ __device__ inline float dt_logf(float x)
 // residual (Markstein 1990), 5 instructions for about 13. That needs a
 // majorant far from the ends of the exponent range (the same test in every
 // lane) and quotients that are zero, normal or, where only 1 - q is used, too
-// small to count. divide: |a| at most 2^80, whose quotients stay finite (the
-// free flights: a below 17). divide_any: any a; the corrections of a quotient
-// that overflows, or of an infinite a, would be inf - inf.
+// small to count. divide: quotients that stay finite (the free flights: a
+// below 17). divide_any: any a; where the quotient overflows, or a is infinite,
+// the corrections are inf - inf and the product that they start from stands (at
+// the last step below FLT_MAX it may be that or the infinity). A branch to the
+// division there costs 2% of a render, the choice nothing that was measured.
 struct Majorant {
     float smax, inv;
     bool plain;
     __device__ explicit Majorant(float s) : smax(s), inv(1.0f / s), plain(!(s >= 0x1p-40f && s <= 0x1p40f)) {}
-    __device__ float divide(float a) const { return plain ? a / smax : corrected(a); }
+    __device__ float divide(float a) const { return plain ? a / smax : corrected(a, a * inv); }
     __device__ float divide_any(float a) const
     {
-        return plain || !(fabsf(a) < 0x1p80f) ? a / smax : corrected(a);
+        if (plain) return a / smax;
+        const float q0 = a * inv, q = corrected(a, q0);
+        return q == q ? q : q0;
     }
 
 private:
-    __device__ float corrected(float a) const
+    __device__ float corrected(float a, float q0) const
     {
-        const float q0 = a * inv;
         const float q1 = __fmaf_rn(__fmaf_rn(-smax, q0, a), inv, q0);
         return __fmaf_rn(__fmaf_rn(-smax, q1, a), inv, q1);
     }
