@@ -119,10 +119,10 @@ int rafi_resize(rafi_ctx *ctx, uint64_t capacity);
 
 /* Stream for all later work on this context (a hipStream_t, passed as void*).
  * The stream must outlive its use by the context. After a render or trace a
- * change of stream waits (on the host) for what is left of it. The paper's library runs on
- * one stream and leaves several asynchronous streams to future work (Sec. 7);
- * here each context has one stream of the caller's choice, so contexts on
- * different streams (and the batched form) can overlap. */
+ * change of stream waits (on the host) for what is left of it. The paper's
+ * library runs on one stream and leaves several asynchronous streams to future
+ * work (Sec. 7); here each context has one stream of the caller's choice, so
+ * contexts on different streams (and the batched form) can overlap. */
 int rafi_set_stream(rafi_ctx *ctx, void *hip_stream);
 
 /* Debug mode: when on, every rafi_begin/rafi_round pre-fills the output
@@ -224,6 +224,10 @@ const char *rafi_strerror(int code);
  * at least rafi_multisplit_workspace() bytes. item_bytes, n_domains as for
  * rafi_create; n < 2^32. Follows Sec. 4.2.1-4.2.2.
  */
+/* Bytes for a split of n slots. Does not fall with n up to 4096 tiles (of 1024
+ * slots for at most 254 destinations), so that a workspace made for the largest
+ * split serves the smaller ones there, and is the same for every scatter shape
+ * but 17 (below). */
 int rafi_multisplit_workspace(uint64_t n, int32_t n_domains, uint32_t item_bytes,
                               uint64_t *bytes);
 

@@ -360,8 +360,10 @@ int rafi_set_stream(rafi_ctx *c, void *hip_stream)
         // a wait on the host, allowed while this thread captures another stream
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (hipStreamSynchronize(c->stream) != hipSuccess) (void)hipDeviceSynchronize();
-        (void)hipGetLastError();
+        if (hipStreamSynchronize(c->stream) != hipSuccess) {
+            (void)hipDeviceSynchronize();
+            (void)hipGetLastError();
+        }
         (void)hipThreadExchangeStreamCaptureMode(&mode);
         c->in_flight = false;
     }
