@@ -17,6 +17,12 @@ __global__ void fill_i32_kernel(int32_t *p, uint64_t n, int32_t v)
         p[i] = v;
 }
 
+// Behind the work before it on the stream: `seq` to a word of pinned memory.
+__global__ void settle_kernel(uint64_t *word, uint64_t seq)
+{
+    __hip_atomic_store(word, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Empty queue: offsets, tile offsets and summary all zero; dropped counter reset.
 __global__ void reset_kernel(uint64_t *offsets, uint32_t *tile_offsets, int32_t D, uint64_t *summary,
                              unsigned long long *dropped)
@@ -228,6 +234,29 @@ int round_run(rafi_ctx *c, uint64_t *counts, uint64_t *total)
     return rc != RAFI_OK ? rc : fill;
 }
 
+int settle_enqueue(rafi_ctx *c)
+{
+    hipLaunchKernelGGL(settle_kernel, dim3(1), dim3(1), 0, c->stream, c->host_summary_dev + kHostExtra, c->round_seq);
+    RAFI_LAUNCH_CHECK();
+    return RAFI_OK;
+}
+
+int settle_finish(rafi_ctx *c)
+{
+    return wait_host_word(c, kHostExtra, [&](uint64_t w) { return w == c->round_seq; });
+}
+
+int round_settled(rafi_ctx *c, uint64_t *total)
+{
+    int rc = round_enqueue(c);
+    if (rc == RAFI_OK) rc = settle_enqueue(c);
+    if (rc != RAFI_OK) return rc;
+    rc = round_finish(c, total);
+    const int wait = settle_finish(c);
+    const int fill = ctx_fill_poison(c, c->n_slots);
+    return rc != RAFI_OK ? rc : wait != RAFI_OK ? wait : fill;
+}
+
 }  // namespace rafi
 
 using namespace rafi;
@@ -333,7 +362,6 @@ void rafi_destroy(rafi_ctx *c)
     if (c->work) (void)hipFree(c->work);
     if (c->append) (void)hipFree(c->append);
     if (c->host_summary) (void)hipHostFree(c->host_summary);
-    if (c->settled) (void)hipEventDestroy(c->settled);
     for (int i = 0; i < c->n_pending; ++i)
         for (int k = 0; k < (c->pending[i].kind == 0 ? 3 : 2); ++k)
             if (c->pending[i].e[k]) (void)hipEventDestroy(c->pending[i].e[k]);

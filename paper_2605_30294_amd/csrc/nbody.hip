@@ -886,12 +886,11 @@ int rafi_nb_seed(rafi_ctx *P, const rafi_nb_job *job, const void *particles, uin
                            static_cast<const NBParticle *>(particles), n);
     RAFI_LAUNCH_CHECK();
     uint64_t total = 0;
-    return rafi_round(P, nullptr, &total);
+    return round_settled(P, &total);
 }
 
 namespace {
-// rafi_nb_step without its wait for the rounds' queues; V->settled is recorded
-// behind the last round.
+// rafi_nb_step without its wait for the rounds' queues.
 int nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job, uint64_t *round_counts, uint64_t *sizes)
 {
     if (!P || !V || !Rq || !job_ok(job) || P->S != RAFI_NB_PARTICLE_BYTES || V->S != RAFI_NB_VIRTUAL_BYTES ||
@@ -1037,8 +1036,7 @@ int nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job, uint
     uint64_t n2 = 0;
     rc = round_run(V, counts_at(3), &n2);
     if (rc != RAFI_OK) return rc;
-    if (!V->settled) RAFI_HIP_CHECK(hipEventCreateWithFlags(&V->settled, hipEventDisableTiming));
-    RAFI_HIP_CHECK(hipEventRecord(V->settled, s));
+    if ((rc = settle_enqueue(V)) != RAFI_OK) return rc;  // before the forces
     rafi_view(V, &vv);
 
     // 7. forces in chunks (a workgroup per particle tile and chunk), then
@@ -1077,8 +1075,8 @@ int rafi_nb_step(rafi_ctx *P, rafi_ctx *V, rafi_ctx *Rq, const rafi_nb_job *job,
     if (rc == RAFI_ERR_ARG) return rc;
     // The rounds end before their scatters do. The queues are whole on return,
     // for callers on other streams too; the forces may still be running.
-    if (rc == RAFI_OK) RAFI_HIP_CHECK(hipEventSynchronize(V->settled));
-    else (void)hipStreamSynchronize(P->stream);
+    if (rc == RAFI_OK) return settle_finish(V);
+    (void)hipStreamSynchronize(P->stream);
     return rc;
 }
 
