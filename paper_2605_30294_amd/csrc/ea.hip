@@ -88,8 +88,8 @@ __device__ inline void emit_ray(const rafi_device_view &view, const rafi_ea_job 
 // One lane per ray. A wave marches until the longest chord among its 64 rays
 // ends, so each workgroup first orders its rays by the samples each has left
 // in its brick (a counting sort through LDS), where chords can differ and
-// unless they all fall in one bucket. Every ray is marched as if alone and written to its own output
-// slot, so results do not depend on the lane.
+// unless they all fall in one bucket. Every ray is marched as if alone and
+// written to its own output slot, so results do not depend on the lane.
 template <bool kLib>
 __global__ void __launch_bounds__(256)
 march_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
@@ -211,8 +211,9 @@ march_kernel(rafi_device_view view, rafi_ea_job job, uint32_t n_rays)
 // takes the next 64 when it is done, so lanes and waves stay busy (94% of the
 // issued lanes live, 66% with gathers). Every ray is marched as if alone and
 // written to its own output slot, so results do not depend on the lane. Bound
-// by VALU issue (62% of the slots, 63 instructions a sample) and the brick
-// loads (first launch of the 64-view render of 128^3: 243 us for 2.1 M rays).
+// by VALU issue (62% of the slots, 83 instructions a live sample) and the brick
+// loads (first launch of the 64-view render of 128^3: 243 us for 2.1 M rays,
+// 90.1 M samples).
 constexpr uint32_t kBrickThreads = 1024, kBrickBatch = 2 * kBrickThreads, kBrickKeys = 64;
 
 struct BrickOrder {
